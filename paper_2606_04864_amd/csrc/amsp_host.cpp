@@ -712,6 +712,7 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
   p.eptr = upload(h, P.eptr, ok);
   p.uptr = upload(h, P.uptr, ok);
   p.ebase = upload(h, P.ebase, ok);
+  p.env_mean = (int)(P.nenv / std::max(1, P.trow_ptr.back()));
   {
     // per-sweep streams of the mixed form's factor: start of every 64-row
     // block inside its region's stream, and of every region's stream
@@ -855,14 +856,14 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
     double *dgB64 = nullptr, *erB64 = nullptr, *ecB64 = nullptr;
     if (mixed) {
       ALLOC(dgB32, float, ndiag);
-      ALLOC(erB32, float, nenv);
-      ALLOC(ecB32, float, nenv);
+      ALLOC(erB32, float, nenv + 1);
+      ALLOC(ecB32, float, nenv + 1);
       launch_tiles_to_f32(h->stream, dsrcB, dgB32, ndiag);
       launch_env_from_tiles<float>(h->stream, p, h->ntilerows, facB, erB32, ecB32);
     } else {
       ALLOC(dgB64, double, ndiag);
-      ALLOC(erB64, double, nenv);
-      ALLOC(ecB64, double, nenv);
+      ALLOC(erB64, double, nenv + 1);
+      ALLOC(ecB64, double, nenv + 1);
       HIP_TRY(hipMemcpyAsync(dgB64, dsrcB, ndiag * sizeof(double), hipMemcpyDeviceToDevice,
                              h->stream));
       launch_env_from_tiles<double>(h->stream, p, h->ntilerows, facB, erB64, ecB64);
@@ -1084,8 +1085,8 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
       launch_stream_from_tiles(h->stream, p, h->ntilerows, h->fac64, h->fst32, h->bst32);
     } else {
       ALLOC(h->dg64, double, ndiag);
-      ALLOC(h->erow64, double, nenv);
-      ALLOC(h->ecol64, double, nenv);
+      ALLOC(h->erow64, double, nenv + 1);
+      ALLOC(h->ecol64, double, nenv + 1);
       HIP_TRY(hipMemcpyAsync(h->dg64, dsrc, ndiag * sizeof(double), hipMemcpyDeviceToDevice,
                              h->stream));
       launch_env_from_tiles<double>(h->stream, p, h->ntilerows, h->fac64, h->erow64, h->ecol64);
@@ -1496,8 +1497,8 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
   if (mixed && do_local && !h->dg32) {
     const size_t nenv = (size_t)h->hp.nenv;
     ALLOC(h->dg32, float, (size_t)h->ntilerows * DE);
-    ALLOC(h->er32, float, std::max<size_t>(nenv, 1));
-    ALLOC(h->ec32, float, std::max<size_t>(nenv, 1));
+    ALLOC(h->er32, float, nenv + 1);
+    ALLOC(h->ec32, float, nenv + 1);
     launch_streams_to_env(s, p, h->ntilerows, h->fst32, h->bst32, h->dg32, h->er32, h->ec32);
   }
   launch_gather_multi(s, p, n, nr, r, bX);

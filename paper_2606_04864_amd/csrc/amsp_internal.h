@@ -31,6 +31,7 @@ struct Plan {
   const int *eptr;          // [sum npad_i + N] envelope of the factor below the diagonal
   const int *uptr;          //   tiles, per region npad_i + 1 segment starts relative to
   const long long *ebase;   //   ebase[i]: row form (eptr) and column form (uptr)
+  int env_mean;             // envelope entries per 64-row block, on average
   const int *sfb, *sbb;     // [sum nt_i] start of each 64-row block in its region's forward
   const long long *sfr;     //   / backward stream; [N+1] region starts of the forward
   const long long *sbr;     //   / backward streams (see launch_local_apply_stream)

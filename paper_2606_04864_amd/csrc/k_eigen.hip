@@ -590,29 +590,46 @@ __global__ void k_basis_round(double *__restrict__ phi, size_t count, int bf16) 
 // region, one workgroup per region (regions flagged in skip[] are left
 // untouched), with L in the local apply's layout: packed inverse diagonal
 // tiles and the envelope below them (row form forward, column form
-// backward).  Per 64-row block the envelope part is a dot product of each
-// row's segment with finished rows; the diagonal part multiplies the
-// 64 x EIGP block by inv(L_II) (or its transpose) on the matrix cores:
-// wavefront w owns rows 16w..16w+15, and K-slot q of MFMA step s stands for
-// column k = 16q + s.  A block's segments are contiguous, so the workgroup
-// stages them in LDS with one coalesced load (EVC entries at a time).  The
-// last RING finished rows stay in LDS (row g in slot g mod RING), so a block
-// whose segments reach back (forward) or ahead (backward) at most RING rows
-// reads them there; longer segments read the finished rows from global
-// memory.  Each block's loads are issued together at its start, its segment
-// bounds one block earlier.
-template <typename T>
-__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4)))
+// backward).
+//
+// A sweep is a chain of nt 64-row blocks, and a block's two products are what
+// bounds it: the finished rows that its envelope reaches, then inv(L_II) (or
+// its transpose) times the 64 x EIGP remainder.  Both run on the matrix
+// cores, wavefront w owning rows 16w..16w+15 of both:
+//   - the envelope part takes the rows' segments as a 16 x 4 ns operand, ns
+//     from the wavefront's longest segment (its first row's forward, its last
+//     one's backward: segment lengths are monotone in a block), entries
+//     outside a segment being zero;
+//   - the diagonal part takes only the 16-column groups of the triangle that
+//     the wavefront's rows meet: 4, 8, 12, 16 steps instead of 16 each.
+// The two loads are opposite (the wavefront with the longest segments has the
+// fewest groups), so that the four SIMDs carry about the same number of
+// steps.  MFMA step (g, u), lane quarter q stands for column 16g + 4q + u of
+// the triangle, so a lane reads four neighbouring entries per group.
+// A block's segments are contiguous: the workgroup stages them in LDS with
+// one coalesced load (EVU entries per thread; a block with more reads its
+// entries from global memory).  The last RING finished rows stay in LDS (row
+// g in slot g mod RING); a wavefront with a longer segment reads the rows
+// from global memory.  Every lane loads and stores the same rows and columns
+// of X, Xin and the accumulator (the MFMA result layout).
+// Measured (21 blocks of 64 rows per region, float64 / float32 factor): 64
+// regions 200 -> 91 / 84 us (1.4 us a block of products, 0.6 of waiting),
+// 1024 regions 430 -> 315 / 357 -> 220 us (5 TB/s of factor and rows); in
+// three dimensions (1728 regions of 16 blocks) 1320 -> 352 us with a float32
+// factor, whose segments of ~100 entries were a serial loop before.
+template <typename T, int EVU, int PF>
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(EVU <= 4 && PF == 1 ? 4 : 2)))
 k_env_solve_block(Plan p, const T *__restrict__ diag, const T *__restrict__ erow,
                   const T *__restrict__ ecol, const double *Xin, double *X,
                   const int *__restrict__ skip) {
   const int i = blockIdx.x;
   if (skip && skip[i]) return;
-  constexpr int LV = EIGP + 1;   // padded LDS row
+  constexpr int LVA = EIGP + 4;  // row strides of the two LDS blocks: rows 4 apart (Acc) and
+  constexpr int LVR = EIGP;      // neighbouring rows (ring) fall into different banks
   constexpr int RING = 2 * TS;   // finished rows kept in LDS
-  constexpr int EVC = 4 * WG;    // envelope entries staged per pass (4 per thread)
-  __shared__ double Rg[RING * LV];
-  __shared__ double Acc[TS * LV];
+  constexpr int EVC = EVU * WG;  // envelope entries staged per block
+  __shared__ double Rg[RING * LVR];
+  __shared__ double Acc[TS * LVA];
   __shared__ T Ev[EVC];
   const int g0 = p.trow_ptr[i], nt = p.trow_ptr[i + 1] - g0;
   const int *ep = p.eptr + p.vp_ptr[i] + i, *up = p.uptr + p.vp_ptr[i] + i;
@@ -621,168 +638,216 @@ k_env_solve_block(Plan p, const T *__restrict__ diag, const T *__restrict__ erow
   double *Xi = X + (size_t)p.vp_ptr[i] * EIGP;
   const double *Xin_i = Xin + (size_t)p.vp_ptr[i] * EIGP;
   const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63;
-  const int mi = l & 15, mq = l >> 4;        // MFMA operand lane roles
-  const int rb = 16 * w + (l >> 4);          // D register r: row rb + 4r, column mi
-  const int rr = tid >> 2, q = tid & 3;      // envelope: row rr, columns 4q..4q+3
-  // Segment bounds of one block: this thread's row (e0, len), the block's
-  // entries [base, base + total) and its longest segment ltop.
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int mi = l & 15, mq = l >> 4;  // MFMA operand lane roles
+  const int rb = 16 * w + mq;          // D register r: row rb + 4r, column mi
+  const int npad = nt * TS;
+  // the ring's rows meet zero entries before they are first written
+  for (int e = tid; e < RING * LVR; e += WG) Rg[e] = 0.0;
+  // Segment bounds of one block: row 16w + mi's first entry within the
+  // block's entries [base, base + total) and its length.  The loads are kept
+  // as they came (Raw) until the bounds come into use, so that nothing waits
+  // for them before; base and total, the same for every lane, then go to
+  // scalar registers.
+  struct Raw {
+    int b0, b1, e0, e1;
+  };
   struct Seg {
-    int e0, len, base, total, ltop;
+    int off, len, base, total;
   };
-  auto seg_row = [&](int r0) {  // row form: the longest segment is the first row's
-    Seg g;
-    g.e0 = ep[r0 + rr];
-    g.len = ep[r0 + rr + 1] - g.e0;
-    g.base = ep[r0];
-    g.total = ep[r0 + TS] - g.base;
-    g.ltop = ep[r0 + 1] - g.base;
-    return g;
+  auto seg_load = [&](const int *ptr, int r0) {
+    const int *row = ptr + r0 + 16 * w + mi;
+    return Raw{ptr[r0], ptr[r0 + TS], row[0], row[1]};
   };
-  auto seg_col = [&](int r0) {  // column form: the longest segment is the last column's
-    Seg g;
-    g.e0 = up[r0 + rr];
-    g.len = up[r0 + rr + 1] - g.e0;
-    g.base = up[r0];
-    g.total = up[r0 + TS] - g.base;
-    g.ltop = up[r0 + TS] - up[r0 + TS - 1];
-    return g;
+  auto seg_of = [&](const Raw &r) {
+    const int base = __builtin_amdgcn_readfirstlane(r.b0);
+    return Seg{r.e0 - base, r.e1 - r.e0, base, __builtin_amdgcn_readfirstlane(r.b1) - base};
   };
-  // entries [c0, c0 + EVC) of the block's segments, this thread's share
-  auto ev_load = [&](const T *src, const Seg &g, int c0, T (&ev)[4]) {
+  // the block's first EVC entries, this thread's share (clamped into the
+  // block and issued unconditionally; a block without entries reads the one
+  // before it, or the array's padding entry)
+  auto ev_load = [&](const T *src, const Seg &g, T (&ev)[EVU]) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = c0 + tid + WG * u;
-      ev[u] = k < g.total ? src[g.base + k] : T(0);
+    for (int u = 0; u < EVU; ++u) ev[u] = src[max(g.base + min(tid + WG * u, g.total - 1), 0)];
+  };
+  // acc -= (segment entries) (finished rows), rows 16w..16w+15.  Row form:
+  // a segment ends at column r0 - 1, so the steps count back from r0; column
+  // form: it starts at row r0 + TS.
+  auto env_part = [&](auto fwd, const T *src, const Seg &g, int r0, d4 &acc) {
+    constexpr bool FWD = decltype(fwd)::value;
+    const int ltop = __builtin_amdgcn_readlane(g.len, FWD ? 0 : 15);
+    const int ns = (ltop + 3) >> 2;
+    const int ib = (FWD ? g.len - 4 * ns : 0) + mq;  // this lane's segment index at step 0
+    const int vb = (FWD ? r0 - 4 * ns : r0 + TS) + mq;
+    if (ns == 0) return;
+    if (g.total <= EVC && ltop <= RING) {
+      // entries and rows from LDS, four steps' reads issued before the four
+      // products before them (the steps past ns read in range and are not used)
+      auto fetch = [&](int s0, double(&a)[4], double(&b)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = ib + 4 * (s0 + u);
+          const bool ok = k >= 0 && k < g.len;
+          const T v = Ev[ok ? g.off + k : 0];
+          a[u] = ok ? -(double)v : 0.0;
+          b[u] = Rg[((vb + 4 * (s0 + u)) & (RING - 1)) * LVR + mi];
+        }
+      };
+      auto mul = [&](int s0, const double(&a)[4], const double(&b)[4]) __attribute__((always_inline)) {
+        acc = mfma16x16x4(a[0], b[0], acc);
+        if (s0 + 1 < ns) acc = mfma16x16x4(a[1], b[1], acc);
+        if (s0 + 2 < ns) {
+          acc = mfma16x16x4(a[2], b[2], acc);
+          acc = mfma16x16x4(a[3], b[3], acc);
+        }
+      };
+      double a0[4], b0[4], a1[4], b1[4];
+      fetch(0, a0, b0);
+      for (int s0 = 0;; s0 += 8) {
+        fetch(s0 + 4, a1, b1);
+        mul(s0, a0, b0);
+        if (s0 + 4 >= ns) break;
+        fetch(s0 + 8, a0, b0);
+        mul(s0 + 4, a1, b1);
+        if (s0 + 8 >= ns) break;
+      }
+    } else {  // long segments or many entries: from global memory
+      for (int s = 0; s < ns; ++s) {
+        const int k = ib + 4 * s;
+        const bool ok = k >= 0 && k < g.len;
+        const T v = src[g.base + (ok ? g.off + k : 0)];
+        const double x = Xi[(size_t)min(max(vb + 4 * s, 0), npad - 1) * EIGP + mi];
+        acc = mfma16x16x4(ok ? -(double)v : 0.0, x, acc);
+      }
     }
   };
-  // acc[j] -= sum_k seg[k] * (finished row v0 + k)[4q + j]
-  auto env_part = [&](const T *src, const Seg &g, int v0, const T (&ev0)[4], double (&acc)[4]) {
-    const bool in_ring = g.ltop <= RING;
-    const int off = g.e0 - g.base;  // this row's first entry within the block's entries
-    for (int c0 = 0; c0 < g.total; c0 += EVC) {
-      T ev[4];
-      if (c0 == 0) {
+  auto rows_load = [&](const double *src, int r0, d4 &x) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) ev[u] = ev0[u];
-      } else {
-        ev_load(src, g, c0, ev);
-      }
-      __syncthreads();  // earlier readers of Ev are done
-#pragma unroll
-      for (int u = 0; u < 4; ++u) Ev[tid + WG * u] = ev[u];
-      __syncthreads();
-      const int kb = max(0, c0 - off), ke = min(g.len, c0 + EVC - off);
-      for (int k = kb; k < ke; ++k) {
-        const double a = (double)Ev[off + k - c0];
-        const int row = v0 + k;
-        const double *wr = in_ring ? Rg + (row & (RING - 1)) * LV + 4 * q
-                                   : Xi + (size_t)row * EIGP + 4 * q;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = fma(-a, wr[j], acc[j]);
-      }
-    }
+    for (int r = 0; r < 4; ++r) x[r] = src[(size_t)(r0 + rb + 4 * r) * EIGP + mi];
   };
-  // y (rows rb + 4r, column mi of the block at row r0) into the ring and X
+  auto acc_write = [&](const d4 &acc) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Acc[(rb + 4 * r) * LVA + mi] = acc[r];
+  };
+  // y into the ring and X
   auto store_block = [&](int r0, const d4 &y) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = r0 + rb + 4 * r;
-      Rg[(row & (RING - 1)) * LV + mi] = y[r];
+      Rg[(row & (RING - 1)) * LVR + mi] = y[r];
       Xi[(size_t)row * EIGP + mi] = y[r];
     }
   };
-  // Each block's global loads (its diagonal tile row, first envelope chunk
-  // and right-hand side) are issued during the block before, each as soon
-  // as its registers are free, so that their latency overlaps that block's
-  // products; segment bounds are loaded two blocks ahead.
-  // forward: Y_I = inv(L_II) (X_I - L[I rows, c < 64I] Y)
-  {
-    T dA[16];
-    T ev0[4];
-    double xin[4];
-    Seg g = seg_row(0);
-    Seg gn = nt > 1 ? seg_row(TS) : g;
-    packed_row16(dA, dpool, 16 * w + mi, 16 * mq);
-    ev_load(erow_i, g, 0, ev0);
+  auto ev_write = [&](const T (&ev)[EVU]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) xin[j] = Xin_i[(size_t)rr * EIGP + 4 * q + j];
-    for (int I = 0; I < nt; ++I) {
-      const int r0 = I * TS;
-      const bool more = I + 1 < nt;
-      Seg gnn = gn;
-      if (I + 2 < nt) gnn = seg_row(r0 + 2 * TS);
-      double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      env_part(erow_i, g, r0 - g.len, ev0, acc);
-      if (more) ev_load(erow_i, gn, 0, ev0);
+    for (int u = 0; u < EVU; ++u) Ev[tid + WG * u] = ev[u];
+  };
+  // One sweep.  Slot I % PF of the buffers holds what block I (in sweep
+  // order) needs from memory, loaded PF blocks ahead, each part as soon as
+  // its registers are free; bounds are loaded 2 PF blocks ahead.
+  auto sweep = [&](auto fwd, const int *ptr, const T *env, const double *in) __attribute__((always_inline)) {
+    constexpr bool FWD = decltype(fwd)::value;
+    struct Buf {
+      T dA[16], ev[EVU];
+      d4 x;
+      Seg g;
+      Raw raw;
+    } b[PF];
+    auto row0 = [&](int I) { return (FWD ? I : nt - 1 - I) * TS; };
+    // forward: row 16w + mi, columns 16g + 4q + u for the groups g <= w;
+    // backward: column 16w + mi, rows 16g + 4q + u for the groups g >= w
+    // (entries outside the triangle lie inside the packed tile and are
+    // dropped where they are used)
+    auto load_d = [&](int I, T (&dA)[16]) {
+      const T *tile = dpool + (size_t)(FWD ? I : nt - 1 - I) * DE;
+      const T *row = FWD ? tile + dpos_row(16 * w + mi) + 4 * mq : tile + 16 * w + mi;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) Acc[rr * LV + 4 * q + j] = xin[j] + acc[j];
-      if (more) {
+      for (int g = 0; g < 4; ++g)
+        if (FWD ? g <= w : g >= w) {
+          const int k4 = 4 * g + mq;  // backward: row / 4
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xin[j] = Xin_i[(size_t)(r0 + TS + rr) * EIGP + 4 * q + j];
-      }
-      __syncthreads();  // Acc complete; all ring reads of this block done
-      d4 y = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < 16; ++s) y = mfma16x16x4((double)dA[s], Acc[(16 * mq + s) * LV + mi], y);
-      if (more) packed_row16(dA, dpool + (size_t)(I + 1) * DE, 16 * w + mi, 16 * mq);
-      store_block(r0, y);
-      __syncthreads();  // Y_I visible in the ring and X; Acc free
-      g = gn;
-      gn = gnn;
-    }
-  }
-  // backward: X_J = inv(L_JJ)^T (Y_J - L[r >= 64(J+1), J cols]^T X)
-  {
-    T dA[16];
-    T ev0[4];
-    double yin[4];
-    auto load_dt = [&](int J) {
-#pragma unroll
-      for (int s = 0; s < 16; ++s)
-        dA[s] = packed_at(dpool + (size_t)J * DE, 16 * mq + s, 16 * w + mi);
+          for (int u = 0; u < 4; ++u)
+            dA[4 * g + u] = FWD ? row[16 * g + u] : row[4 * (k4 + 1) * (2 * k4 + u)];
+        }
     };
-    const int J0 = nt - 1;
-    Seg g = seg_col(J0 * TS);
-    Seg gn = J0 > 0 ? seg_col((J0 - 1) * TS) : g;
-    load_dt(J0);
-    ev_load(ecol_i, g, 0, ev0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) yin[j] = Xi[(size_t)(J0 * TS + rr) * EIGP + 4 * q + j];
-    for (int J = J0; J >= 0; --J) {
-      const int r0 = J * TS, r1 = r0 + TS;
-      const bool more = J > 0;
-      Seg gnn = gn;
-      if (J > 1) gnn = seg_col(r0 - 2 * TS);
-      double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      env_part(ecol_i, g, r1, ev0, acc);
-      if (more) ev_load(ecol_i, gn, 0, ev0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) Acc[rr * LV + 4 * q + j] = yin[j] + acc[j];
-      if (more) {
-        // rows of block J - 1 of Y: final since the forward sweep, and not
-        // written by this sweep before block J - 1's own store
-#pragma unroll
-        for (int j = 0; j < 4; ++j) yin[j] = Xi[(size_t)(r0 - TS + rr) * EIGP + 4 * q + j];
-      }
-      __syncthreads();
-      d4 y = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < 16; ++s) y = mfma16x16x4((double)dA[s], Acc[(16 * mq + s) * LV + mi], y);
-      if (more) load_dt(J - 1);
-      store_block(r0, y);
-      __syncthreads();
-      g = gn;
-      gn = gnn;
+    for (int j = 0; j < PF; ++j) {
+      b[j].g = seg_of(seg_load(ptr, row0(min(j, nt - 1))));
+      b[j].raw = seg_load(ptr, row0(min(j + PF, nt - 1)));
+      ev_load(env, b[j].g, b[j].ev);
+      rows_load(in, row0(min(j, nt - 1)), b[j].x);
+      load_d(min(j, nt - 1), b[j].dA);
     }
-  }
+    for (int I0 = 0; I0 < nt; I0 += PF) {
+#pragma unroll
+      for (int j = 0; j < PF; ++j) {
+        const int I = I0 + j;
+        if (I < nt) {
+          Buf &c = b[j];
+          // the block that takes this slot next (past the last one: the last
+          // one again, unused; nothing here is conditional, so that the waits
+          // are for the oldest loads only)
+          const int In = min(I + PF, nt - 1);
+          const Seg g = c.g;
+          ev_write(c.ev);
+          __syncthreads();  // Ev and the ring complete; the last block's Acc reads done
+          d4 acc = c.x;
+          c.g = seg_of(c.raw);
+          ev_load(env, c.g, c.ev);
+          // (backward: this lane's own stores of the forward sweep)
+          rows_load(in, row0(In), c.x);
+          c.raw = seg_load(ptr, row0(min(I + 2 * PF, nt - 1)));
+          env_part(fwd, env, g, row0(I), acc);
+          acc_write(acc);
+          __syncthreads();  // Acc complete; Ev and the ring free
+          d4 y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            double bd[8];  // two groups' reads, issued (and waited for) together
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              bd[e] = Acc[(32 * h + 16 * (e >> 2) + 4 * mq + (e & 3)) * LVA + mi];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) __asm__ volatile("" : "+v"(bd[e]));
+#pragma unroll
+            for (int gr = 2 * h; gr < 2 * h + 2; ++gr)
+              if (FWD ? gr <= w : gr >= w) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                  const bool in = gr != w || (FWD ? 4 * mq + u <= mi : mi <= 4 * mq + u);
+                  y = mfma16x16x4(in ? (double)c.dA[4 * gr + u] : 0.0, bd[4 * (gr & 1) + u], y);
+                }
+              }
+          }
+          load_d(In, c.dA);
+          store_block(row0(I), y);
+        }
+      }
+    }
+  };
+  // forward: Y_I = inv(L_II) (X_I - L[I rows, c < 64I] Y)
+  sweep(std::true_type{}, ep, erow_i, Xin_i);
+  // backward: X_J = inv(L_JJ)^T (Y_J - L[r >= 64(J+1), J cols]^T X)
+  sweep(std::false_type{}, up, ecol_i, Xi);
 }
 
+// Entries staged per thread: the regions of a plane grid have some 300
+// envelope entries per block (four per thread cover 1024); where blocks
+// average more than 700, as in three dimensions, sixteen.  Blocks in flight:
+// two for a float64 factor (64 regions of 21 blocks: 91 us with one, 87-96
+// with two; 256: 141 / 105; 1024: 335 / 315), one for a float32 factor, whose
+// third and fourth workgroup per unit are worth more (256: 105 / 98; 1024:
+// 220 / 250), and where the staged entries already fill the registers (512
+// regions of 16 blocks in three dimensions: 155 / 170).
 template <typename T>
 void launch_env_solve_block(hipStream_t s, const Plan &p, const T *diag, const T *erow,
                             const T *ecol, const double *X, double *Y, const int *skip) {
-  hipLaunchKernelGGL((k_env_solve_block<T>), dim3(p.N), dim3(WG), 0, s, p, diag, erow, ecol, X, Y,
-                     skip);
+  if (p.env_mean <= 700)
+    hipLaunchKernelGGL((k_env_solve_block<T, 4, sizeof(T) == 8 ? 2 : 1>), dim3(p.N), dim3(WG), 0,
+                       s, p, diag, erow, ecol, X, Y, skip);
+  else
+    hipLaunchKernelGGL((k_env_solve_block<T, 16, 1>), dim3(p.N), dim3(WG), 0, s, p, diag, erow,
+                       ecol, X, Y, skip);
 }
 template void launch_env_solve_block<double>(hipStream_t, const Plan &, const double *,
                                              const double *, const double *, const double *,
