@@ -1085,8 +1085,8 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
       launch_stream_from_tiles(h->stream, p, h->ntilerows, h->fac64, h->fst32, h->bst32);
     } else {
       ALLOC(h->dg64, double, ndiag);
-      ALLOC(h->erow64, double, nenv + 1);
-      ALLOC(h->ecol64, double, nenv + 1);
+      ALLOC(h->erow64, double, nenv + 2);
+      ALLOC(h->ecol64, double, nenv + 2);
       HIP_TRY(hipMemcpyAsync(h->dg64, dsrc, ndiag * sizeof(double), hipMemcpyDeviceToDevice,
                              h->stream));
       launch_env_from_tiles<double>(h->stream, p, h->ntilerows, h->fac64, h->erow64, h->ecol64);
@@ -1302,7 +1302,7 @@ extern "C" amsp_status amsp_setup(const amsp_csr *A, const int32_t *partition, i
   }
   // the local apply keeps a region's vector and envelope segment starts in
   // LDS (160 KB per workgroup, less the kernel's 512 B of static LDS)
-  if ((o.precision == AMSP_FP64 ? local_apply_lds_bytes(h->hp.max_npad, 8)
+  if ((o.precision == AMSP_FP64 ? local_apply_lds_bytes(h->hp.max_npad)
                                  : local_apply_stream_lds_bytes(h->hp.max_npad)) >
       160 * 1024 - 512) {
     g_setup_error = "largest region (" + std::to_string(h->hp.max_npad) +
@@ -1390,10 +1390,8 @@ static amsp_status apply_one(amsp_handle *h, const double *r, double *z, int par
     hipEvent_t e0, e1;
     tk = tpair(h, 1, &e0, &e1);
     if (!mixed)
-      launch_local_apply_t<double, double, double>(h->stream, p, h->hp.max_npad, r, h->dg64,
-                                                   h->erow64, h->ecol64,
-                                                   (const double *)h->phi_nat, t, tpart, h->T0,
-                                                   h->xloc, done, e0, e1);
+      launch_local_apply(h->stream, p, h->hp.max_npad, r, h->dg64, h->erow64, h->ecol64,
+                         (const double *)h->phi_nat, t, tpart, h->T0, h->xloc, done, e0, e1);
     else if (!bf)
       launch_local_apply_stream<float>(h->stream, p, h->hp.max_npad, r, h->fst32, h->bst32,
                                        (const float *)h->phi_nat, t, tpart, h->T0, h->xloc, done,

@@ -123,9 +123,9 @@ void launch_tiles_to_f32(hipStream_t s, const double *src, float *dst, size_t co
 template <typename T>
 void launch_env_from_tiles(hipStream_t s, const Plan &p, int ntilerows, const double *tiles,
                            T *erow, T *ecol);
-// Dynamic LDS of the local apply for regions of up to max_npad padded rows
-// and compute type of csize bytes.
-size_t local_apply_lds_bytes(int max_npad, size_t csize);
+// LDS that the FP64 form's local apply is allowed for regions of up to
+// max_npad padded rows (larger regions are refused).
+size_t local_apply_lds_bytes(int max_npad);
 // Per-sweep streams of an f32 factor: for every region, its 64-row blocks in
 // sweep order (forward: ascending, envelope row form; backward: descending,
 // column form), each block's envelope segments zero-padded to a multiple of
@@ -141,7 +141,7 @@ template <typename TB>
 void launch_restrict(hipStream_t s, const Plan &p, const double *r, const TB *phi, double *cvec,
                      const int *done);
 // The mixed-form local apply on the streams (same operation as
-// launch_local_apply_t with float factors).
+// launch_local_apply with float factors).
 template <typename TB>
 void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const double *r,
                                const float *fst, const float *bst, const TB *phi, const double *t,
@@ -152,16 +152,16 @@ void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const
 // added to each region's output (phi: the copy made by
 // launch_basis_to_natural).  With tpart (else nullptr) the coarse solution
 // is instead summed from the per-tile products of W0^T (launch_trmv with
-// y == nullptr; T0 tiles), as the reduction would sum them.  diag: the packed inverse diagonal tiles
-// (DE entries per tile row), erow/ecol: the envelope.  T factor, C compute,
-// TB basis type.  ev_start / ev_stop (optional, created with timing): bound
-// to the dispatch itself (no extra packets in the stream).
-template <typename T, typename C, typename TB>
-void launch_local_apply_t(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                          const T *diag, const T *erow, const T *ecol, const TB *phi,
-                          const double *t, const double *tpart, int T0, double *xloc,
-                          const int *done, hipEvent_t ev_start = nullptr,
-                          hipEvent_t ev_stop = nullptr);
+// y == nullptr; T0 tiles), as the reduction would sum them.  diag: the packed
+// inverse diagonal tiles (DE entries per tile row), erow/ecol: the envelope
+// (with two entries of padding behind it).  ev_start / ev_stop (optional,
+// created with timing): bound to the dispatch itself (no extra packets in the
+// stream).
+void launch_local_apply(hipStream_t s, const Plan &p, int max_npad, const double *r,
+                        const double *diag, const double *erow, const double *ecol,
+                        const double *phi, const double *t, const double *tpart, int T0,
+                        double *xloc, const int *done, hipEvent_t ev_start = nullptr,
+                        hipEvent_t ev_stop = nullptr);
 void launch_selftest_mfma(hipStream_t s, const double *A, const double *B, double *D);
 // The regions' dofs in ascending order and their local indices (Plan::asc,
 // Plan::lop).

@@ -11,80 +11,6 @@
 
 namespace amsp {
 
-// ------------------------------------------------ local solves (1 rhs) ----
-// What one thread holds of a streamed piece of the factor: 16 entries, and
-// for an envelope chunk the vector index paired with a[0] (entry s pairs with
-// cb + 4s) and the bound kv (entries with 4s >= kv lie past the segment and
-// are zero).
-template <typename T>
-struct Frag {
-  T a[16];
-  int cb, kv;
-};
-
-// Row mapping of a packed diagonal tile: row t>>2, columns 16(t&3) .. +15.
-template <typename T>
-__device__ __forceinline__ void row_frag_load_diag(Frag<T> &f, const T *__restrict__ dtile) {
-  packed_row16(f.a, dtile, threadIdx.x >> 2, 16 * (threadIdx.x & 3));
-}
-
-template <typename T, typename C>
-__device__ __forceinline__ C row_frag_dot(const Frag<T> &f, const C *v) {
-  const C *vv = v + 16 * (threadIdx.x & 3);
-  C s = 0;
-#pragma unroll
-  for (int c = 0; c < 16; ++c) s = fma((C)f.a[c], vv[c], s);
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
-  return s;  // full row sum in all 4 lanes of the row
-}
-
-// Column mapping of a packed diagonal tile: wavefront w owns columns
-// 16w .. 16w+15; lane l covers column 16w + (l & 15) and rows 16(l >> 4) ..
-// +15, so a column's 64 rows sit in four lanes 16 apart.
-template <typename T>
-__device__ __forceinline__ void col_frag_load_diag(Frag<T> &f, const T *__restrict__ dtile) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = 16 * w + (l & 15), r0 = 16 * (l >> 4);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) f.a[r] = packed_at(dtile, r0 + r, col);
-}
-
-// sum_r tile[r][col] x[r] for this lane's column, complete in all four lanes
-// of the column (x: the 64-vector the tile multiplies, in LDS)
-template <typename T, typename C>
-__device__ __forceinline__ C col_frag_dot(const Frag<T> &f, const C *x) {
-  const C *xx = x + 16 * ((threadIdx.x & 63) >> 4);
-  C s = 0;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) s = fma((C)f.a[r], xx[r], s);
-  s += __shfl_xor(s, 16, 64);
-  s += __shfl_xor(s, 32, 64);
-  return s;
-}
-
-// Chunk j of this thread's envelope segment (seg: its first entry, len: its
-// length, v0: the vector index of entry 0): entries k = 64j + (t&3) + 4s.
-template <typename T>
-__device__ __forceinline__ void env_chunk_load(Frag<T> &f, const T *__restrict__ seg, int len,
-                                               int v0, int j) {
-  const int kb = TS * j + (threadIdx.x & 3);
-  f.cb = v0 + kb;
-  f.kv = len - kb;
-#pragma unroll
-  for (int s = 0; s < 16; ++s) f.a[s] = 4 * s < f.kv ? seg[kb + 4 * s] : T(0);
-}
-
-// acc -= sum over the chunk's entries of a[s] x[cb + 4s] (partial: this
-// thread's share of the segment)
-template <typename T, typename C>
-__device__ __forceinline__ C env_chunk_dot(const Frag<T> &f, const C *x, C acc) {
-#pragma unroll
-  for (int s = 0; s < 16; ++s)
-    if (4 * s < f.kv) acc = fma(-(C)f.a[s], x[f.cb + 4 * s], acc);
-  return acc;
-}
-
 // dst[l] = src[l] for l < cnt (LDS from global), each thread's loads all in
 // flight together when cnt <= U * WG: they are clamped into range and
 // issued unconditionally, and the stores of rows past cnt go to
@@ -267,35 +193,187 @@ __device__ __forceinline__ void coarse_partial_finish(const Plan &p, int i, doub
   if (threadIdx.x % TRMV_RG == 0 && q < p.mi[i]) tq[q] = tot;
 }
 
-size_t local_apply_lds_bytes(int max_npad, size_t csize) {
-  return (size_t)(max_npad + TS) * csize + 2 * (size_t)(max_npad + 1) * sizeof(int);
+// ------------------------------------------------ local solves (1 rhs) ----
+// One sweep of the local solves over a region's nt 64-row blocks, the vector
+// v in LDS.  FWD: y_I = inv(L_II) (b_I - sum_{c < 64I} L[., c] y_c), blocks
+// upwards, row form; otherwise x_J = inv(L_JJ)^T (y_J - sum_{r >= 64(J+1)}
+// L[r, .]^T x_r), blocks downwards, column form.
+//
+// A sweep is a chain of blocks: its latency is what counts with few regions,
+// memory with four per compute unit.  Two barriers a block; everything that a
+// block needs from memory is in registers when it begins (loaded during the
+// block before, bounds during the one before that, no load under a condition:
+// the wait before such a load's use would drain the others), as contiguous
+// 16-byte pieces that cost the load path one line each.  (The packed tile
+// loaded straight into the lanes that use it spread each load over 16 to 64
+// lines, and a compute unit's 64 bytes per cycle were the limit.)
+//   - Envelope: four lanes per row (or column) take its entries in turn, from
+//     LDS (EVU staged entries per thread; a block with more reads them from
+//     global memory).
+//   - Diagonal tile: lane (i, q) of wavefront w takes, of row (column) 16w + i,
+//     the entries 16g + 4q .. + 3 of the groups g that the triangle has there
+//     (g <= w, backward g >= w).
+// Deeper prefetch (two and three blocks) measured the same.
+// Measured (blocks of 64 rows, float64, whole kernel): 64 regions of 21 blocks
+// 97 -> 54 us; 1024 regions 222 -> 165 us (0.93 GB, 5.6 TB/s: what a copy
+// reaches); 1331 regions of 12 blocks in three dimensions 231 us.
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+
+template <bool FWD, int EVU, typename T>
+__device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
+                                            const T *__restrict__ env,
+                                            const T *__restrict__ diag, T *v, T *tmp, T *Ev, T *Dt) {
+  constexpr int EVC = EVU * WG;
+  // a lane's envelope entries and groups of the triangle per pass (registers)
+  constexpr int EB = EVU > 4 ? 8 : 4, NG = EVU > 4 ? 4 : 2;
+  const int t = threadIdx.x, rr = t >> 2, q = t & 3, i = (t & 63) >> 2;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  // Segment bounds of a block, as loaded (Raw) and as used: this row's first
+  // entry within the block's entries [base, base + total) and its length.
+  struct Raw {
+    int b0, b1, e0, e1;
+  };
+  struct Seg {
+    int off, len, base, total;
+  };
+  auto row0 = [&](int I) { return (FWD ? I : nt - 1 - I) * TS; };
+  auto seg_load = [&](int I) {
+    const int *b = ptr + row0(min(I, nt - 1));
+    return Raw{b[0], b[TS], b[rr], b[rr + 1]};
+  };
+  auto seg_of = [&](const Raw &r) {
+    const int base = __builtin_amdgcn_readfirstlane(r.b0);
+    return Seg{r.e0 - base, r.e1 - r.e0, base, __builtin_amdgcn_readfirstlane(r.b1) - base};
+  };
+  // two neighbouring entries per load, clamped into the block (a block without
+  // entries reads the one before it or the array's padding)
+  auto ev_load = [&](const Seg &g, T(&ev)[EVU]) {
+#pragma unroll
+    for (int u = 0; u < EVU; u += 2) {
+      const T *e = env + max(g.base + min(2 * t + WG * u, g.total - 1), 0);
+      ev[u] = e[0];
+      ev[u + 1] = e[1];
+    }
+  };
+  // the packed diagonal tile, in 16-byte pieces (the pieces past its end: the
+  // last one again)
+  constexpr int DV = DE * (int)sizeof(T) / 16, DU = (DV + WG - 1) / WG;
+  auto load_d = [&](int I, v4u(&d)[DU]) {
+    const v4u *tile =
+        reinterpret_cast<const v4u *>(diag + (size_t)(row0(min(I, nt - 1)) / TS) * DE);
+#pragma unroll
+    for (int u = 0; u < DU; ++u) d[u] = tile[min(t + WG * u, DV - 1)];
+  };
+  v4u dt[DU];
+  T ev[EVU];
+  Seg g = seg_of(seg_load(0));
+  Raw raw = seg_load(1);
+  ev_load(g, ev);
+  load_d(0, dt);
+  for (int I = 0; I < nt; ++I) {
+    const int r0 = row0(I);
+#pragma unroll
+    for (int u = 0; u < EVU; ++u) Ev[2 * t + WG * (u & ~1) + (u & 1)] = ev[u];
+    __syncthreads();  // Ev and v complete; the last block's reads of tmp and Dt done
+#pragma unroll
+    for (int u = 0; u < DU; ++u) reinterpret_cast<v4u *>(Dt)[min(t + WG * u, DV - 1)] = dt[u];
+    const Seg gn = seg_of(raw);
+    ev_load(gn, ev);
+    load_d(I + 1, dt);
+    raw = seg_load(I + 2);
+    const int v0 = FWD ? r0 - g.len : r0 + TS;
+    const int ltop = __builtin_amdgcn_readlane(g.len, FWD ? 0 : 60);  // the wavefront's longest
+    T s0 = 0, s1 = 0;
+    T br = v[r0 + rr];
+    __asm__ volatile("" : "+v"(br));  // read here, off the path after the sum
+    if (g.total <= EVC) {
+      // reads past the segment (other entries, rows of v and the TS zeros
+      // behind them) are dropped
+      const T *as = Ev + g.off + q, *xs = v + v0 + q;
+      int left = g.len - q;
+      for (int k0 = 0; k0 < ltop; k0 += 4 * EB, as += 4 * EB, xs += 4 * EB, left -= 4 * EB) {
+        T a[EB], x[EB];
+#pragma unroll
+        for (int u = 0; u < EB; ++u) {
+          a[u] = as[4 * u];
+          x[u] = xs[4 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < EB; ++u) __asm__ volatile("" : "+v"(a[u]), "+v"(x[u]));
+#pragma unroll
+        for (int u = 0; u < EB; ++u) {
+          T &sx = u & 1 ? s1 : s0;
+          const T f = fma(-a[u], x[u], sx);
+          sx = 4 * u < left ? f : sx;
+        }
+      }
+    } else {
+      for (int k = q; k < g.len; k += 4) s0 = fma(-env[g.base + g.off + k], v[v0 + k], s0);
+    }
+    T acc = quad_sum(s0 + s1);
+    if (q == 0) tmp[rr] = br + acc;
+    __syncthreads();  // tmp and Dt complete; Ev free
+    // the diagonal group (w), then the up to three whole ones; the reads of NG
+    // groups are issued (and waited for) together, those of groups outside
+    // the triangle stay within the tile and are not used
+    T d[4];  // four chains: columns (rows) 4m + u
+#pragma unroll
+    for (int m0 = 0; m0 < 4; m0 += NG) {
+      T a[4 * NG], x[4 * NG];
+#pragma unroll
+      for (int e = 0; e < 4 * NG; ++e) {
+        const int m = m0 + (e >> 2), u = e & 3;
+        const int k4 = 4 * (m == 0 ? w : FWD ? m - 1 : m) + q;
+        x[e] = tmp[4 * k4 + u];
+        a[e] = FWD ? Dt[dpos_row(16 * w + i) + 4 * k4 + u]
+                   : Dt[4 * (k4 + 1) * (2 * k4 + u) + 16 * w + i];
+      }
+#pragma unroll
+      for (int e = 0; e < 4 * NG; ++e) __asm__ volatile("" : "+v"(x[e]), "+v"(a[e]));
+#pragma unroll
+      for (int m = m0; m < m0 + NG; ++m) {
+        const int e = 4 * (m - m0);
+        if (m == 0) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            d[u] = ((FWD ? 4 * q + u <= i : i <= 4 * q + u) ? a[u] : T(0)) * x[u];
+        } else if (FWD ? m - 1 < w : m > w) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) d[u] = fma(a[e + u], x[e + u], d[u]);
+        }
+      }
+    }
+    acc = quad_sum((d[0] + d[1]) + (d[2] + d[3]));
+    if (q == 0) v[r0 + rr] = acc;
+    g = gn;
+  }
+  __syncthreads();  // v complete
 }
 
-// Fused additive-Schwarz local kernel for one region per workgroup:
-//   gather r on the region, forward/backward substitution with the factor,
-//   store the local correction (plus Phi_i t_i when t is given) into xloc.
-// T: factor storage type, C: compute type, TB: basis storage type.
-template <typename T, typename C, typename TB>
-__global__ void __launch_bounds__(WG) k_local_apply(Plan p, const double *__restrict__ r,
-                                                    const T *__restrict__ diag,
-                                                    const T *__restrict__ erow,
-                                                    const T *__restrict__ ecol,
-                                                    const TB *__restrict__ phi,
-                                                    const double *__restrict__ t,
-                                                    const double *__restrict__ tpart, int T0,
-                                                    double *__restrict__ xloc,
-                                                    const int *__restrict__ done) {
+size_t local_apply_lds_bytes(int max_npad) {
+  return (size_t)(max_npad + TS) * sizeof(double) + 2 * (size_t)(max_npad + 1) * sizeof(int);
+}
+
+// Fused additive-Schwarz local kernel of the FP64 form for one region per
+// workgroup: gather r on the region, forward/backward substitution with the
+// factor, store the local correction (plus Phi_i t_i when t is given) into
+// xloc.
+template <int EVU>
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(EVU <= 4 ? 4 : 2)))
+k_local_apply(Plan p, const double *__restrict__ r, const double *__restrict__ diag,
+              const double *__restrict__ erow, const double *__restrict__ ecol,
+              const double *__restrict__ phi, const double *__restrict__ t,
+              const double *__restrict__ tpart, int T0, double *__restrict__ xloc,
+              const int *__restrict__ done) {
   if (done && *done) return;
-  extern __shared__ char smem_raw[];
-  __shared__ double tq_s[16];  // the region's coarse values (a multiple of 16 bytes)
+  extern __shared__ __align__(16) char smem_raw[];
+  __shared__ double tq_s[16];  // the region's coarse values
+  __shared__ __align__(16) double Ev[EVU * WG], Dt[DE], tmp[TS];
   const int i = blockIdx.x;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
   const int g0 = p.trow_ptr[i], nt = p.trow_ptr[i + 1] - g0;
   const int npad = nt * TS;
-  C *v = reinterpret_cast<C *>(smem_raw);  // whole local vector (padded)
-  C *tmp = v + npad;                         // 64
-  int *er = reinterpret_cast<int *>(tmp + TS);  // npad + 1 row-form segment starts
-  int *eu = er + npad + 1;                       // npad + 1 column-form segment starts
+  double *v = reinterpret_cast<double *>(smem_raw);  // whole local vector (padded), TS zeros
   const double cps = tpart ? coarse_partial_load(p, i, tpart, T0) : 0.0;
   {  // gather, nothing conditional (as in the stream kernel; tmp takes the
      // stores of rows past the padding)
@@ -310,135 +388,17 @@ __global__ void __launch_bounds__(WG) k_local_apply(Plan p, const double *__rest
 #pragma unroll
       for (int u = 0; u < GU; ++u) {
         const int l = l0 + u * WG;
-        v[l < npad ? l : npad + (threadIdx.x & (TS - 1))] = l < ni ? (C)rv[u] : C(0);
+        *(l < npad ? v + l : tmp + (threadIdx.x & (TS - 1))) = l < ni ? rv[u] : 0.0;
       }
     }
   }
-  {
-    const int *ep = p.eptr + p.vp_ptr[i] + i, *up = p.uptr + p.vp_ptr[i] + i;
-    int *junk = reinterpret_cast<int *>(tmp);  // scratch until the sweeps
-    copy_ints_to_lds<8>(er, ep, npad + 1, junk);
-    copy_ints_to_lds<8>(eu, up, npad + 1, junk);
-  }
+  if (threadIdx.x < TS) v[npad + threadIdx.x] = 0.0;
   if (tpart) coarse_partial_finish(p, i, cps, tq_s);
   const double *tq = tpart ? tq_s : (t ? t + p.coff[i] : nullptr);
-  __syncthreads();
-  const int rr = threadIdx.x >> 2, q = threadIdx.x & 3;
-  const T *dpool = diag + (size_t)g0 * DE;
-  const T *erow_i = erow + p.ebase[i];
-  const T *ecol_i = ecol + p.ebase[i];
-  // Each sweep streams, per block of 64 rows, the block's envelope chunks
-  // (64 entries of every row segment each) and then its diagonal tile.  A
-  // load cursor walks that sequence D + 1 pieces ahead of the consuming one;
-  // D + 1 register slots hold the pieces in flight, and the slot loop is
-  // unrolled so each slot is refilled in place right after its piece is used
-  // (no register copies, which would wait for the loads in flight).  Segment
-  // lengths are monotone inside a block (fenv nondecreasing), so the block's
-  // chunk count comes from its first row (row form) or last column (column
-  // form).
-  constexpr int D = sizeof(T) == 4 ? 3 : 1;  // keeps 4 workgroups per CU resident
-  auto nch_row = [&](int I) { return (er[I * TS + 1] - er[I * TS] + TS - 1) / TS; };
-  auto nch_col = [&](int I) { return (eu[I * TS + TS] - eu[I * TS + TS - 1] + TS - 1) / TS; };
-  // forward: y_I = inv(L_II) (b_I - sum_{c < 64I} L[., c] y_c)
-  {
-    Frag<T> f[D + 1];
-    int lI = 0, lj = 0, lnch = nch_row(0);  // load cursor: block lI, chunk lj
-    auto load_next = [&](Frag<T> &fr) {
-      if (lj < lnch) {
-        const int row = lI * TS + rr;
-        const int e0 = er[row], len = er[row + 1] - e0;
-        env_chunk_load(fr, erow_i + e0, len, lI * TS - len, lj);
-        ++lj;
-      } else {
-        row_frag_load_diag(fr, dpool + (size_t)lI * DE);
-        ++lI;
-        lj = 0;
-        if (lI < nt) lnch = nch_row(lI);
-      }
-    };
-#pragma unroll
-    for (int d = 0; d <= D; ++d)
-      if (lI < nt) load_next(f[d]);
-    int I = 0, j = 0, nch = nch_row(0);
-    C acc = 0;
-    for (;;) {
-#pragma unroll
-      for (int sl = 0; sl <= D; ++sl) {
-        if (I < nt) {
-          if (j < nch) {
-            acc = env_chunk_dot<T, C>(f[sl], v, acc);
-            ++j;
-          } else {
-            acc += __shfl_xor(acc, 1, 64);
-            acc += __shfl_xor(acc, 2, 64);
-            if (q == 0) tmp[rr] = v[I * TS + rr] + acc;
-            __syncthreads();
-            const C y = row_frag_dot<T, C>(f[sl], tmp);
-            if (q == 0) v[I * TS + rr] = y;
-            __syncthreads();
-            ++I;
-            j = 0;
-            acc = 0;
-            if (I < nt) nch = nch_row(I);
-          }
-          if (lI < nt) load_next(f[sl]);
-        }
-      }
-      if (I >= nt) break;
-    }
-  }
-  // backward: x_J = inv(L_JJ)^T (y_J - sum_{r >= 64(J+1)} L[r, .]^T x_r),
-  // J = nt-1 .. 0, with the column form (row c of L^T).
-  {
-    Frag<T> f[D + 1];
-    int lI = nt - 1, lj = 0, lnch = nch_col(nt - 1);
-    auto load_next = [&](Frag<T> &fr) {
-      if (lj < lnch) {
-        const int c = lI * TS + rr;
-        const int e0 = eu[c], len = eu[c + 1] - e0;
-        env_chunk_load(fr, ecol_i + e0, len, (lI + 1) * TS, lj);
-        ++lj;
-      } else {
-        col_frag_load_diag(fr, dpool + (size_t)lI * DE);
-        --lI;
-        lj = 0;
-        if (lI >= 0) lnch = nch_col(lI);
-      }
-    };
-#pragma unroll
-    for (int d = 0; d <= D; ++d)
-      if (lI >= 0) load_next(f[d]);
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int col = 16 * w + (l & 15);
-    const bool head = (l >> 4) == 0;  // one lane of the four that share a column
-    int I = nt - 1, j = 0, nch = nch_col(nt - 1);
-    C acc = 0;
-    for (;;) {
-#pragma unroll
-      for (int sl = 0; sl <= D; ++sl) {
-        if (I >= 0) {
-          if (j < nch) {
-            acc = env_chunk_dot<T, C>(f[sl], v, acc);
-            ++j;
-          } else {
-            acc += __shfl_xor(acc, 1, 64);
-            acc += __shfl_xor(acc, 2, 64);
-            if (q == 0) tmp[rr] = v[I * TS + rr] + acc;
-            __syncthreads();  // tmp complete
-            const C x = col_frag_dot<T, C>(f[sl], tmp);
-            if (head) v[I * TS + col] = x;
-            __syncthreads();  // x_I visible; all reads of tmp done
-            --I;
-            j = 0;
-            acc = 0;
-            if (I >= 0) nch = nch_col(I);
-          }
-          if (lI >= 0) load_next(f[sl]);
-        }
-      }
-      if (I < 0) break;
-    }
-  }
+  const int po = p.vp_ptr[i] + i;  // the region's segment starts
+  const double *dpool = diag + (size_t)g0 * DE;
+  local_sweep<true, EVU>(nt, p.eptr + po, erow + p.ebase[i], dpool, v, tmp, Ev, Dt);
+  local_sweep<false, EVU>(nt, p.uptr + po, ecol + p.ebase[i], dpool, v, tmp, Ev, Dt);
   // local correction (+ prolongation) in the region's ascending-global-index
   // layout, so that the scatter reads contiguous runs
   store_local(p, i, r0, ni, v, phi, tq, xloc);
@@ -713,28 +673,34 @@ template void launch_restrict<float>(hipStream_t, const Plan &, const double *, 
 template void launch_restrict<__hip_bfloat16>(hipStream_t, const Plan &, const double *,
                                               const __hip_bfloat16 *, double *, const int *);
 
-template <typename T, typename C, typename TB>
-void launch_local_apply_t(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                          const T *diag, const T *erow, const T *ecol, const TB *phi,
-                          const double *t, const double *tpart, int T0, double *xloc,
-                          const int *done, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  const size_t sm = local_apply_lds_bytes(max_npad, sizeof(C));
-  allow_lds(k_local_apply<T, C, TB>, sm);
+template <int EVU>
+static void local_apply_launch(hipStream_t s, const Plan &p, int max_npad, const double *r,
+                               const double *diag, const double *erow, const double *ecol,
+                               const double *phi, const double *t, const double *tpart, int T0,
+                               double *xloc, const int *done, hipEvent_t ev_start,
+                               hipEvent_t ev_stop) {
+  const size_t sm = (size_t)(max_npad + TS) * sizeof(double);
+  allow_lds(k_local_apply<EVU>, sm);
   if (ev_start || ev_stop)  // events bound to this dispatch: exact kernel duration
-    hipExtLaunchKernelGGL((k_local_apply<T, C, TB>), dim3(p.N), dim3(WG), sm, s, ev_start, ev_stop,
+    hipExtLaunchKernelGGL((k_local_apply<EVU>), dim3(p.N), dim3(WG), sm, s, ev_start, ev_stop,
                           0, p, r, diag, erow, ecol, phi, t, tpart, T0, xloc, done);
   else
-    hipLaunchKernelGGL((k_local_apply<T, C, TB>), dim3(p.N), dim3(WG), sm, s, p, r, diag, erow,
+    hipLaunchKernelGGL(k_local_apply<EVU>, dim3(p.N), dim3(WG), sm, s, p, r, diag, erow,
                        ecol, phi, t, tpart, T0, xloc, done);
 }
 
-#define AMSP_LOCAL_APPLY_INST(T, C, TB)                                                        \
-  template void launch_local_apply_t<T, C, TB>(hipStream_t, const Plan &, int, const double *, \
-                                               const T *, const T *, const T *, const TB *,    \
-                                               const double *, const double *, int, double *,  \
-                                               const int *, hipEvent_t, hipEvent_t);
-AMSP_LOCAL_APPLY_INST(double, double, double)
-#undef AMSP_LOCAL_APPLY_INST
+void launch_local_apply(hipStream_t s, const Plan &p, int max_npad, const double *r,
+                        const double *diag, const double *erow, const double *ecol,
+                        const double *phi, const double *t, const double *tpart, int T0,
+                        double *xloc, const int *done, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  // staged entries per thread: as for the block solve (launch_env_solve_block)
+  if (p.env_mean <= 700)
+    local_apply_launch<4>(s, p, max_npad, r, diag, erow, ecol, phi, t, tpart, T0, xloc, done,
+                          ev_start, ev_stop);
+  else
+    local_apply_launch<16>(s, p, max_npad, r, diag, erow, ecol, phi, t, tpart, T0, xloc, done,
+                           ev_start, ev_stop);
+}
 
 template <typename TB>
 void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const double *r,

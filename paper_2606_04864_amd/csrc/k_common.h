@@ -70,37 +70,6 @@ __device__ __forceinline__ size_t diag_elem(const Plan &p, int g) {
   return (size_t)p.noff * TE + (size_t)g * DE;
 }
 
-// Entries c0 .. c0+15 (c0 a multiple of 16) of row R of a packed diagonal
-// tile; entries above the diagonal are zero.  Each 4-entry group that starts
-// right of the diagonal is not read.
-template <typename T>
-__device__ __forceinline__ void packed_row16(T (&a)[16], const T *__restrict__ dtile, int R,
-                                             int c0) {
-  const T *row = dtile + dpos_row(R) + c0;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if (c0 + 4 * u <= R) {
-      if constexpr (sizeof(T) == 4) {
-        const float4 v = *reinterpret_cast<const float4 *>(row + 4 * u);
-        a[4 * u] = v.x;
-        a[4 * u + 1] = v.y;
-        a[4 * u + 2] = v.z;
-        a[4 * u + 3] = v.w;
-      } else {
-        const double2 v0 = *reinterpret_cast<const double2 *>(row + 4 * u);
-        const double2 v1 = *reinterpret_cast<const double2 *>(row + 4 * u + 2);
-        a[4 * u] = v0.x;
-        a[4 * u + 1] = v0.y;
-        a[4 * u + 2] = v1.x;
-        a[4 * u + 3] = v1.y;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) a[4 * u + j] = T(0);
-    }
-  }
-}
-
 // Entry (R, C) of a packed diagonal tile (zero above the diagonal).
 template <typename T>
 __device__ __forceinline__ T packed_at(const T *__restrict__ dtile, int R, int C) {
@@ -236,6 +205,16 @@ __device__ __forceinline__ double dpp_quad(double v) {
 template <int CTRL>
 __device__ __forceinline__ float dpp_quad_f(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// Sum over the four lanes of a quad, in every lane.
+__device__ __forceinline__ double quad_sum(double v) {
+  v += dpp_quad<0xB1>(v);
+  return v + dpp_quad<0x4E>(v);
+}
+__device__ __forceinline__ float quad_sum(float v) {
+  v += dpp_quad_f<0xB1>(v);
+  return v + dpp_quad_f<0x4E>(v);
 }
 
 // Cholesky factor of a 64x64 SPD tile and the inverse of the factor, in LDS.

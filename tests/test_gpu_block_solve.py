@@ -1,5 +1,5 @@
-"""The block solve of several columns at the edges of its layout, against the
-oracle's local solves column by column: regions of one block, segments longer
+"""The local solves, of several columns (the block solve) and of one, at the
+edges of their layout, against the oracle's local solves column by column: regions of one block, segments longer
 than the rows kept on chip, blocks with more envelope entries than are staged,
 the three-dimensional variant, full triangles.  Bar as for the one-column
 apply: max(1e-10, 10 F) with F the oracle's own floor under a rounding-only
@@ -48,22 +48,22 @@ def problem(name):
     raise KeyError(name)
 
 
-@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("prec,cols", [("fp64", 3), ("fp32", 3), ("fp64", 1)])
 @pytest.mark.parametrize("name", ["one_block", "long_segments", "narrow_and_wide", "cubes",
                                   "full_triangles"])
-def test_block_solve_edges(name, prec):
+def test_local_solve_edges(name, prec, cols):
     A, part, nparts, kw = problem(name)
     M = A.to_scipy()
     st = O.setup(M, part, nparts, 2, 1)
     alt = O.setup(M, part, nparts, 2, 1, local_order="descending")
-    print("block solve", name, prec, file=sys.stderr, flush=True)
+    print("local solve", name, prec, cols, file=sys.stderr, flush=True)
     pc = P.setup(A, part, nparts, 2, overlap=1, precision=prec, **kw)
-    R = np.random.default_rng(6).standard_normal((3, A.n))
+    R = np.random.default_rng(6).standard_normal((cols, A.n))
     Z = pc.apply_columns(torch.tensor(R, device="cuda"), parts=1)
     torch.cuda.synchronize()
     Z = Z.cpu().numpy()
     pc.close()
-    for j in range(3):
+    for j in range(cols):
         ref = O.local_part(st, R[j])
         floor = np.linalg.norm(O.local_part(alt, R[j]) - ref) / np.linalg.norm(ref)
         err = np.linalg.norm(Z[j] - ref) / np.linalg.norm(ref)
