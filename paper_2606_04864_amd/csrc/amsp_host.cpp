@@ -537,8 +537,8 @@ static amsp_status tree_coarse_setup(amsp_handle *h, const HostPlan &P) {
   ALLOC(h->X64, double, (size_t)tp.xtiles * TE);
   ALLOC(dinv, double, (size_t)std::max(tp.dtiles, 1) * TE);
   ALLOC(cstat, int, 1);
-  ALLOC(h->ty, double, std::max(h->nc, 1));
-  ALLOC(h->tv, double, std::max(tp.nvec, 1));
+  ALLOC(h->ty, double, (size_t)std::max(h->nc, 1) * EIGP);  // rows of up to EIGP columns
+  ALLOC(h->tv, double, (size_t)std::max(tp.nvec, 1) * EIGP);
   HIP_TRY(hipMemsetAsync(cstat, 0, sizeof(int), h->stream));
   launch_fill(h->stream, (size_t)tp.ftiles * TE, F, 0.0);
   launch_fill(h->stream, (size_t)tp.xtiles * TE, h->X64, 0.0);
@@ -612,6 +612,18 @@ static void coarse_solve_tree(amsp_handle *h, hipStream_t s, const double *c, do
   else
     launch_tree_solve<double>(s, h->td, tp.lvl_ptr, tp.lvl_maxT, tp.lvl_maxK, tp.max_K, tp.max_T,
                               h->X64, c, h->ty, h->tv, x, done);
+}
+
+// The same for nr columns (rows of EIGP values).
+static void coarse_solve_tree_multi(amsp_handle *h, hipStream_t s, int nr, const double *c,
+                                    double *x) {
+  const TreePlan &tp = h->tp;
+  if (h->X32)
+    launch_tree_solve_multi<float>(s, h->td, tp.lvl_ptr, tp.lvl_maxT, tp.lvl_maxK, nr, h->X32, c,
+                                   h->ty, h->tv, x);
+  else
+    launch_tree_solve_multi<double>(s, h->td, tp.lvl_ptr, tp.lvl_maxT, tp.lvl_maxK, nr, h->X64, c,
+                                    h->ty, h->tv, x);
 }
 
 static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
@@ -1426,7 +1438,7 @@ static amsp_status apply_one(amsp_handle *h, const double *r, double *z, int par
 // z_k = M^{-1} r_k (parts as in apply_one) for nr <= EIGP columns, n apart,
 // with one pass over the local factor: the block solve with the Dirichlet
 // factor (f32-stored in the mixed forms, f64 arithmetic), the restriction of
-// all columns, one coarse solve per column, the prolongation and the scatter.
+// all columns, one coarse solve for all columns, the prolongation and the scatter.
 // Workspace of the block apply: gathered, solved and output blocks (rows x
 // EIGP each), the coarse vectors (ncp x EIGP each) and the coarse products'
 // partial sums (T0^2 x TS x EIGP).
@@ -1491,7 +1503,7 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
   const size_t ncp = (size_t)std::max(1, h->T0 * TS);
   double *const bX = ws.X, *const bY = ws.Y, *const bXN = ws.XN, *const bC = ws.C,
                *const bT = ws.T, *const bC2 = ws.C2, *const bPart = ws.Part;
-  if (do_coarse && ws.clear_c) launch_fill(s, ncp * nr, bC, 0.0);  // padding rows read as zero
+  if (do_coarse && ws.clear_c) launch_fill(s, ncp * EIGP, bC, 0.0);  // padding rows read as zero
   if (mixed && do_local && !h->dg32) {
     const size_t nenv = (size_t)h->hp.nenv;
     ALLOC(h->dg32, float, (size_t)h->ntilerows * DE);
@@ -1509,30 +1521,30 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
   const void *phi = mixed ? h->phi_lo : (const void *)h->phi64;
   if (do_coarse) {
     if (!mixed)
-      launch_restrict_multi<double>(s, p, nr, ncp, (const double *)phi, bX, bC);
+      launch_restrict_multi<double>(s, p, nr, (const double *)phi, bX, bC);
     else if (!bf)
-      launch_restrict_multi<float>(s, p, nr, ncp, (const float *)phi, bX, bC);
+      launch_restrict_multi<float>(s, p, nr, (const float *)phi, bX, bC);
     else
-      launch_restrict_multi<__hip_bfloat16>(s, p, nr, ncp, (const __hip_bfloat16 *)phi, bX, bC);
+      launch_restrict_multi<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)phi, bX, bC);
     // t_k = W0^T (W0 c_k) for all columns, W0's tiles read once per product
     if (h->tree) {
-      for (int k = 0; k < nr; ++k) coarse_solve_tree(h, s, bC + k * ncp, bT + k * ncp, nullptr);
+      coarse_solve_tree_multi(h, s, nr, bC, bT);
     } else if (!mixed) {
-      launch_trmm<double>(s, h->W0, h->T0, bC, ncp, nr, bPart, bC2, 0);
-      launch_trmm<double>(s, h->W0, h->T0, bC2, ncp, nr, bPart, bT, 1);
+      launch_trmm<double>(s, h->W0, h->T0, bC, nr, bPart, bC2, 0);
+      launch_trmm<double>(s, h->W0, h->T0, bC2, nr, bPart, bT, 1);
     } else {
-      launch_trmm<float>(s, h->W0f, h->T0, bC, ncp, nr, bPart, bC2, 0);
-      launch_trmm<float>(s, h->W0f, h->T0, bC2, ncp, nr, bPart, bT, 1);
+      launch_trmm<float>(s, h->W0f, h->T0, bC, nr, bPart, bC2, 0);
+      launch_trmm<float>(s, h->W0f, h->T0, bC2, nr, bPart, bT, 1);
     }
   }
   const double *tcoarse = do_coarse ? bT : nullptr;
   const double *ylocal = do_local ? bY : nullptr;
   if (!mixed)
-    launch_prolong_multi<double>(s, p, nr, ncp, (const double *)phi, tcoarse, ylocal, bXN);
+    launch_prolong_multi<double>(s, p, nr, (const double *)phi, tcoarse, ylocal, bXN);
   else if (!bf)
-    launch_prolong_multi<float>(s, p, nr, ncp, (const float *)phi, tcoarse, ylocal, bXN);
+    launch_prolong_multi<float>(s, p, nr, (const float *)phi, tcoarse, ylocal, bXN);
   else
-    launch_prolong_multi<__hip_bfloat16>(s, p, nr, ncp, (const __hip_bfloat16 *)phi, tcoarse,
+    launch_prolong_multi<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)phi, tcoarse,
                                          ylocal, bXN);
   launch_scatter_multi(s, n, nr, h->inv_ptr, h->inv_x, bXN, z);
   HIP_TRY(hipGetLastError());

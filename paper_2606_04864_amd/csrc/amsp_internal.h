@@ -185,17 +185,17 @@ void launch_scatter_sum_t(hipStream_t s, const Plan &p, int max_ni, int n, const
 // (ascending-global-index layout), scatter into z (columns n apart).
 void launch_gather_multi(hipStream_t s, const Plan &p, int n, int nr, const double *r, double *X);
 template <typename TB>
-void launch_restrict_multi(hipStream_t s, const Plan &p, int nr, size_t ncp, const TB *phi,
+void launch_restrict_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
                            const double *X, double *c);
 template <typename TB>
-void launch_prolong_multi(hipStream_t s, const Plan &p, int nr, size_t ncp, const TB *phi,
+void launch_prolong_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
                           const double *t, const double *Y, double *XN);
 void launch_scatter_multi(hipStream_t s, int n, int nr, const int *inv_ptr, const int *ix,
                           const double *XN, double *z);
 // y_k = W0 x_k (transpose 0) or W0^T x_k (1) for k < nr, vectors ncp apart,
 // reading W0's tiles once; part holds T0 * T0 * 64 * EIGP doubles.
 template <typename T>
-void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, size_t ncp, int nr,
+void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr,
                  double *part, double *y, int transpose);
 // CG on nr columns ld apart, one recurrence per column: Y = A X (entries
 // read once for all columns); out[k] = A_k . B_k (part: 256 * nr doubles);

@@ -112,5 +112,12 @@ void launch_tree_solve(hipStream_t s, const TreeDev &t, const std::vector<int> &
                        const std::vector<int> &lvl_maxT, const std::vector<int> &lvl_maxK,
                        int maxK, int maxT, const TX *X, const double *c, double *y, double *v,
                        double *x, const int *done);
+// The same for nr <= EIGP columns: c, x (rows of the coarse numbering), y and
+// v hold rows of EIGP values; columns nr .. of c are read as zero.
+template <typename TX>
+void launch_tree_solve_multi(hipStream_t s, const TreeDev &t, const std::vector<int> &lvl_ptr,
+                             const std::vector<int> &lvl_maxT, const std::vector<int> &lvl_maxK,
+                             int nr, const TX *X, const double *c, double *y, double *v,
+                             double *x);
 
 }  // namespace amsp

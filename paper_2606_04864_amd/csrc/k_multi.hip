@@ -36,9 +36,9 @@ __global__ void __launch_bounds__(WG) k_gather_multi(Plan p, int n, int nr,
 // Restriction of every column: c_k[coff_i + q] = sum_l phi_i[l][q] X[l][k].
 // Thread (row group g, column k) adds rows g, g + 16, ... for all q (GU rows'
 // loads issued together); the 16 group sums are then added in group order.
-// The coarse vectors are ncp apart (their padding stays zero).
+// The coarse vectors are rows of EIGP values (padding rows stay zero).
 template <typename TB>
-__global__ void __launch_bounds__(WG) k_restrict_multi(Plan p, int nr, size_t ncp,
+__global__ void __launch_bounds__(WG) k_restrict_multi(Plan p, int nr,
                                                        const TB *__restrict__ phi,
                                                        const double *__restrict__ X,
                                                        double *__restrict__ c) {
@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(WG) k_restrict_multi(Plan p, int nr, size_t nc
     const int q = threadIdx.x / EIGP, kk = threadIdx.x % EIGP;
     double s = 0.0;
     for (int gg = 0; gg < RGS; ++gg) s += sh[gg][q][kk];
-    if (kk < nr) c[(size_t)kk * ncp + p.coff[i] + q] = s;
+    if (kk < nr) c[(size_t)(p.coff[i] + q) * EIGP + kk] = s;
   }
 }
 
@@ -85,7 +85,7 @@ __global__ void __launch_bounds__(WG) k_restrict_multi(Plan p, int nr, size_t nc
 // (without the coarse part when t is null; without the local part when Y is).
 // The region's coarse values are staged in LDS; thread per row.
 template <typename TB>
-__global__ void __launch_bounds__(WG) k_prolong_multi(Plan p, int nr, size_t ncp,
+__global__ void __launch_bounds__(WG) k_prolong_multi(Plan p, int nr,
                                                       const TB *__restrict__ phi,
                                                       const double *__restrict__ t,
                                                       const double *__restrict__ Y,
@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(WG) k_prolong_multi(Plan p, int nr, size_t ncp
   const int co = p.coff[i];
   if (t && (int)threadIdx.x < MAXNEV * EIGP) {
     const int q = threadIdx.x / EIGP, k = threadIdx.x % EIGP;
-    tl[q][k] = (q < m && k < nr) ? t[(size_t)k * ncp + co + q] : 0.0;
+    tl[q][k] = (q < m && k < nr) ? t[(size_t)(co + q) * EIGP + k] : 0.0;
   }
   __syncthreads();
   for (int l = threadIdx.x; l < ni; l += WG) {
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(WG) k_scatter_multi(int n, int nr, const int *
 // contribution to output tile O (I, or J transposed).
 template <typename T>
 __global__ void __launch_bounds__(WG) k_trmm_tiles(const T *__restrict__ Wt, int T0,
-                                                   const double *__restrict__ x, size_t ncp, int nr,
+                                                   const double *__restrict__ x, int nr,
                                                    double *__restrict__ part, int transpose) {
   __shared__ double xs[TS][EIGP];
   const int b = blockIdx.x;
@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(WG) k_trmm_tiles(const T *__restrict__ Wt, int
   const int K = transpose ? I : J, O = transpose ? J : I;
   for (int e = threadIdx.x; e < TS * EIGP; e += WG) {
     const int rr = e / EIGP, k = e % EIGP;
-    xs[rr][k] = k < nr ? x[(size_t)k * ncp + K * TS + rr] : 0.0;
+    xs[rr][k] = k < nr ? x[(size_t)(K * TS + rr) * EIGP + k] : 0.0;
   }
   __syncthreads();
   const int o = threadIdx.x % TS, kq = threadIdx.x / TS;  // output row o, columns 4kq..4kq+3
@@ -201,14 +201,14 @@ __global__ void __launch_bounds__(WG) k_trmm_tiles(const T *__restrict__ Wt, int
 
 // y_k[O*64 + r] = sum over input tiles K (in order) of part[(O*T0 + K)][r][k]
 __global__ void __launch_bounds__(TS * EIGP) k_trmm_reduce(int T0, const double *__restrict__ part,
-                                                           double *__restrict__ y, size_t ncp,
-                                                           int nr, int transpose) {
+                                                           double *__restrict__ y, int nr,
+                                                           int transpose) {
   const int O = blockIdx.x, r = threadIdx.x / EIGP, k = threadIdx.x % EIGP;
   const int k0 = transpose ? O : 0, k1 = transpose ? T0 : O + 1;
   double s = 0.0;
 #pragma unroll 4
   for (int K = k0; K < k1; ++K) s += part[(((size_t)O * T0 + K) * TS + r) * EIGP + k];
-  if (k < nr) y[(size_t)k * ncp + O * TS + r] = s;
+  if (k < nr) y[(size_t)(O * TS + r) * EIGP + k] = s;
 }
 
 // The mixed forms keep their f32 factor only as the two per-sweep streams;
@@ -362,15 +362,15 @@ void launch_gather_multi(hipStream_t s, const Plan &p, int n, int nr, const doub
 }
 
 template <typename TB>
-void launch_restrict_multi(hipStream_t s, const Plan &p, int nr, size_t ncp, const TB *phi,
+void launch_restrict_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
                            const double *X, double *c) {
-  hipLaunchKernelGGL((k_restrict_multi<TB>), dim3(p.N), dim3(WG), 0, s, p, nr, ncp, phi, X, c);
+  hipLaunchKernelGGL((k_restrict_multi<TB>), dim3(p.N), dim3(WG), 0, s, p, nr, phi, X, c);
 }
 
 template <typename TB>
-void launch_prolong_multi(hipStream_t s, const Plan &p, int nr, size_t ncp, const TB *phi,
+void launch_prolong_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
                           const double *t, const double *Y, double *XN) {
-  hipLaunchKernelGGL((k_prolong_multi<TB>), dim3(p.N), dim3(WG), 0, s, p, nr, ncp, phi, t, Y, XN);
+  hipLaunchKernelGGL((k_prolong_multi<TB>), dim3(p.N), dim3(WG), 0, s, p, nr, phi, t, Y, XN);
 }
 
 void launch_scatter_multi(hipStream_t s, int n, int nr, const int *inv_ptr, const int *ix,
@@ -381,18 +381,18 @@ void launch_scatter_multi(hipStream_t s, int n, int nr, const int *inv_ptr, cons
 }
 
 template <typename T>
-void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, size_t ncp, int nr,
+void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr,
                  double *part, double *y, int transpose) {
   const int nb = T0 * (T0 + 1) / 2;
   if (nb == 0) return;
-  hipLaunchKernelGGL((k_trmm_tiles<T>), dim3(nb), dim3(WG), 0, s, Wt, T0, x, ncp, nr, part,
+  hipLaunchKernelGGL((k_trmm_tiles<T>), dim3(nb), dim3(WG), 0, s, Wt, T0, x, nr, part,
                      transpose);
-  hipLaunchKernelGGL(k_trmm_reduce, dim3(T0), dim3(TS * EIGP), 0, s, T0, part, y, ncp, nr,
+  hipLaunchKernelGGL(k_trmm_reduce, dim3(T0), dim3(TS * EIGP), 0, s, T0, part, y, nr,
                      transpose);
 }
-template void launch_trmm<double>(hipStream_t, const double *, int, const double *, size_t, int,
+template void launch_trmm<double>(hipStream_t, const double *, int, const double *, int,
                                   double *, double *, int);
-template void launch_trmm<float>(hipStream_t, const float *, int, const double *, size_t, int,
+template void launch_trmm<float>(hipStream_t, const float *, int, const double *, int,
                                  double *, double *, int);
 
 static int col_blocks(int n) {
@@ -491,9 +491,9 @@ void launch_col_direction(hipStream_t s, int n, size_t ld, int nr, const double 
 }
 
 #define AMSP_MULTI_INST(TB)                                                                  \
-  template void launch_restrict_multi<TB>(hipStream_t, const Plan &, int, size_t, const TB *, \
+  template void launch_restrict_multi<TB>(hipStream_t, const Plan &, int, const TB *, \
                                           const double *, double *);                          \
-  template void launch_prolong_multi<TB>(hipStream_t, const Plan &, int, size_t, const TB *,  \
+  template void launch_prolong_multi<TB>(hipStream_t, const Plan &, int, const TB *,  \
                                          const double *, const double *, double *);
 AMSP_MULTI_INST(double)
 AMSP_MULTI_INST(float)

@@ -214,41 +214,141 @@ __global__ void k_x_to_f32(const double *__restrict__ src, float *__restrict__ d
 }
 
 // ----------------------------------------------------------- the solve ---
+// One launch per level and direction.  A level costs its dependent memory
+// round trips (gather, tiles, store), so each is taken once for as much as
+// possible: a thread gathers up to four rows with their loads together, and a
+// wavefront (b, j) of the 4 NJ loads its 16-row quarter b of every NJ-th tile,
+// four tiles at a time, as contiguous 16-byte pieces.
+// Measured (three-dimensional tree of 13824 coarse dofs in 8 levels, float32,
+// both directions): 255 us with each lane walking 64-byte pieces of one tile
+// after the other, 151 us so.
+constexpr int TREE_B = 4;  // tiles per batch
+
+// v[k][e] = entry (16 b + 4k + (l >> 4), 4 (l & 15) + e) of a tile, lane l
+template <typename TX>
+__device__ __forceinline__ void quarter_load(TX (&v)[4][4], const TX *__restrict__ g, int b) {
+  const int l = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[k][e] = g[(16 * b + 4 * k + (l >> 4)) * TS + 4 * (l & 15) + e];
+}
+
+// cs[r] = c + the children's contributions to front row r (in order), r < rows
+__device__ __forceinline__ void tree_gather(const TreeDev &t, int rb, int rows, int nthreads,
+                                            const double *__restrict__ c,
+                                            const double *v, double *cs) {
+  constexpr int U = 4;
+  for (int r0 = threadIdx.x; r0 < rows; r0 += U * nthreads) {
+    int rc[U], g0[U], g1[U];
+    double s[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = rb + min(r0 + u * nthreads, rows - 1);
+      rc[u] = t.row_coarse[r];
+      g0[u] = t.gptr[r];
+      g1[u] = t.gptr[r + 1];
+    }
+    int most = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double x = c[max(rc[u], 0)];
+      s[u] = rc[u] >= 0 ? x : 0.0;
+      most = max(most, g1[u] - g0[u]);
+    }
+    for (int k = 0; k < most; ++k) {
+      int src[U];
+      double x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) src[u] = g0[u] + k < g1[u] ? t.gsrc[g0[u] + k] : -1;
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = src[u] >= 0 ? v[src[u]] : 0.0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) s[u] = src[u] >= 0 ? s[u] + x[u] : s[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r0 + u * nthreads < rows) cs[r0 + u * nthreads] = s[u];
+  }
+}
+
+// z[r] = y (own rows, r < own) or x (update rows) of front row r, a <= r < rows
+__device__ __forceinline__ void tree_rows(const TreeDev &t, int rb, int a, int own, int rows,
+                                          int nthreads, const double *y, const double *x,
+                                          double *z) {
+  constexpr int U = 4;
+  for (int r0 = a + threadIdx.x; r0 < rows; r0 += U * nthreads) {
+    int rc[U];
+    double s[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) rc[u] = t.row_coarse[rb + min(r0 + u * nthreads, rows - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] = (r0 + u * nthreads < own ? y : x)[max(rc[u], 0)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r0 + u * nthreads < rows) z[r0 + u * nthreads] = rc[u] < 0 ? 0.0 : s[u];
+  }
+}
+
 // Forward, one level: workgroup (front f, row tile I) forms the front's own
 // input cs = c + the children's contributions, then rows 64I.. of X cs:
 // own rows give y (by coarse index), update rows give the front's update
 // vector v_f = (X cs) + the children's contributions to those rows.
-template <typename TX>
-__global__ void __launch_bounds__(WG) k_tree_fwd(TreeDev t, int f0, const TX *__restrict__ X,
-                                                 const double *__restrict__ c,
-                                                 double *__restrict__ y, double *__restrict__ v,
-                                                 const int *__restrict__ done) {
+template <typename TX, int NJ, int NB>
+__global__ void __launch_bounds__(64 * NB * NJ) k_tree_fwd(TreeDev t, int f0, const TX *__restrict__ X,
+                                                       const double *__restrict__ c,
+                                                       double *__restrict__ y, double *v,
+                                                       const int *__restrict__ done) {
   if (done && *done) return;
   extern __shared__ double cs[];  // 64 K
-  const int f = f0 + blockIdx.y, I = blockIdx.x;
+  __shared__ double red[NJ][16 * NB];
+  constexpr int NQ = 4 / NB;  // workgroups per row tile
+  const int f = f0 + blockIdx.y, I = blockIdx.x / NQ;
   const int K = t.K[f];
   if (I >= t.T[f]) return;
-  const int rb = t.rbase[f];
-  for (int r = threadIdx.x; r < K * TS; r += WG) {
-    const int rc = t.row_coarse[rb + r];
-    double s = rc >= 0 ? c[rc] : 0.0;
-    for (int g = t.gptr[rb + r]; g < t.gptr[rb + r + 1]; ++g) s += v[t.gsrc[g]];
-    cs[r] = s;
-  }
+  const int rb = t.rbase[f], jn = I < K ? I + 1 : K;  // inv(L11) is lower triangular
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, j = w / NB;
+  const int b0 = NB * (blockIdx.x % NQ), b = b0 + w % NB;
+  tree_gather(t, rb, jn * TS, 64 * NB * NJ, c, v, cs);
   __syncthreads();
-  const int row = threadIdx.x >> 2, q = threadIdx.x & 3;
-  const int jn = I < K ? I + 1 : K;  // inv(L11) is lower triangular
-  double s = 0.0;
-  for (int J = 0; J < jn; ++J) {
-    const TX *x = xtile(X, t, f, I, J) + row * TS + 16 * q;
-    const double *cc = cs + J * TS + 16 * q;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int J0 = j; J0 < jn; J0 += TREE_B * NJ) {
+    TX x[TREE_B][4][4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s = fma((double)x[e], cc[e], s);
+    for (int u = 0; u < TREE_B; ++u)  // (past the last tile: the last one again, unused)
+      quarter_load(x[u], xtile(X, t, f, I, min(J0 + u * NJ, jn - 1)), b);
+#pragma unroll
+    for (int u = 0; u < TREE_B; ++u)
+      if (J0 + u * NJ < jn) {
+        double cc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cc[e] = cs[(J0 + u * NJ) * TS + 4 * (l & 15) + e];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[k] = fma((double)x[u][k][e], cc[e], a[k]);
+      }
   }
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
-  if (q != 0) return;
-  const int R = I * TS + row;
+  // the 16 lanes of a row group add their shares of four rows: two steps halve
+  // the rows a lane carries (lane's row 16b + 4 ((l >> 2) & 3) + (l >> 4)), two
+  // add the last four lanes
+#pragma unroll
+  for (int o = 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      if (k < o) {
+        const bool up = (l & (4 * o)) != 0;
+        const double mine = up ? a[k + o] : a[k], other = up ? a[k] : a[k + o];
+        a[k] = mine + __shfl_xor(other, 4 * o, 64);
+      }
+  const double sum = quad_sum(a[0]);
+  if ((l & 3) == 0) red[j][16 * (b - b0) + 4 * ((l >> 2) & 3) + (l >> 4)] = sum;
+  __syncthreads();
+  if (w != 0 || l >= 16 * NB) return;
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < NJ; ++u) s += red[u][l];
+  const int R = I * TS + 16 * b0 + l;
   if (I < K) {
     const int rc = t.row_coarse[rb + R];
     if (rc >= 0) y[rc] = s;
@@ -264,37 +364,231 @@ __global__ void __launch_bounds__(WG) k_tree_fwd(TreeDev t, int f0, const TX *__
 // Backward, one level: workgroup (front f, column tile J) forms
 // z = [y on the own rows; x on the update rows (ancestors, solved)] and
 // x[own rows 64J..] = (X^T z) restricted to those columns.
-template <typename TX>
-__global__ void __launch_bounds__(WG) k_tree_bwd(TreeDev t, int f0, const TX *__restrict__ X,
-                                                 const double *__restrict__ y,
-                                                 double *__restrict__ x,
-                                                 const int *__restrict__ done) {
+template <typename TX, int NJ>
+__global__ void __launch_bounds__(256 * NJ) k_tree_bwd(TreeDev t, int f0, const TX *__restrict__ X,
+                                                       const double *__restrict__ y, double *x,
+                                                       const int *__restrict__ done) {
   if (done && *done) return;
   extern __shared__ double z[];  // 64 T
-  __shared__ double red[4][TS];
+  __shared__ double red[4 * NJ][TS];
   const int f = f0 + blockIdx.y, J = blockIdx.x;
   const int K = t.K[f], T = t.T[f];
   if (J >= K) return;
   const int rb = t.rbase[f];
-  for (int r = J * TS + threadIdx.x; r < T * TS; r += WG) {
-    const int rc = t.row_coarse[rb + r];
-    z[r] = rc < 0 ? 0.0 : (r < K * TS ? y[rc] : x[rc]);
-  }
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, b = w & 3, j = w >> 2;
+  tree_rows(t, rb, J * TS, K * TS, T * TS, 256 * NJ, y, x, z);
   __syncthreads();
-  const int col = threadIdx.x & 63, g = threadIdx.x >> 6;
-  double s = 0.0;
-  for (int I = J; I < T; ++I) {
-    const TX *xt = xtile(X, t, f, I, J) + (16 * g) * TS + col;
-    const double *zz = z + I * TS + 16 * g;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int I0 = J + j; I0 < T; I0 += TREE_B * NJ) {
+    TX xt[TREE_B][4][4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s = fma((double)xt[r * TS], zz[r], s);
+    for (int u = 0; u < TREE_B; ++u)
+      quarter_load(xt[u], xtile(X, t, f, min(I0 + u * NJ, T - 1), J), b);
+#pragma unroll
+    for (int u = 0; u < TREE_B; ++u)
+      if (I0 + u * NJ < T) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double zz = z[(I0 + u * NJ) * TS + 16 * b + 4 * k + (l >> 4)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[e] = fma((double)xt[u][k][e], zz, a[e]);
+        }
+      }
   }
-  red[g][col] = s;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    a[e] += __shfl_xor(a[e], 16, 64);
+    a[e] += __shfl_xor(a[e], 32, 64);
+    if (l < 16) red[w][4 * l + e] = a[e];
+  }
   __syncthreads();
-  if (g == 0) {
-    const int rc = t.row_coarse[rb + J * TS + col];
-    if (rc >= 0) x[rc] = (red[0][col] + red[1][col]) + (red[2][col] + red[3][col]);
+  if (w != 0) return;
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < 4 * NJ; ++u) s += red[u][l];
+  const int rc = t.row_coarse[rb + J * TS + l];
+  if (rc >= 0) x[rc] = s;
+}
+
+// The same for a quarter of a column tile per workgroup (columns 16b .. of
+// tile J): sixteen wavefronts, each loading 64 rows x 16 columns of every
+// sixteenth tile (64-byte pieces).
+template <typename TX>
+__global__ void __launch_bounds__(1024) k_tree_bwd_quarter(TreeDev t, int f0,
+                                                           const TX *__restrict__ X,
+                                                           const double *__restrict__ y, double *x,
+                                                           const int *__restrict__ done) {
+  if (done && *done) return;
+  extern __shared__ double z[];  // 64 T
+  __shared__ double red[16][16];
+  const int f = f0 + blockIdx.y, J = blockIdx.x >> 2, b = blockIdx.x & 3;
+  const int K = t.K[f], T = t.T[f];
+  if (J >= K) return;
+  const int rb = t.rbase[f];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  tree_rows(t, rb, J * TS, K * TS, T * TS, 1024, y, x, z);
+  __syncthreads();
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int I0 = J + w; I0 < T; I0 += 16 * 2) {
+    TX xt[2][4][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const TX *g = xtile(X, t, f, min(I0 + 16 * u, T - 1), J) + (l >> 2) * TS + 16 * b + 4 * (l & 3);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xt[u][k][e] = g[16 * k * TS + e];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (I0 + 16 * u < T) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double zz = z[(I0 + 16 * u) * TS + 16 * k + (l >> 2)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[e] = fma((double)xt[u][k][e], zz, a[e]);
+        }
+      }
   }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) a[e] += __shfl_xor(a[e], o, 64);
+    if (l < 4) red[w][4 * l + e] = a[e];
+  }
+  __syncthreads();
+  if (threadIdx.x >= 16) return;
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) s += red[u][l];
+  const int rc = t.row_coarse[rb + J * TS + 16 * b + l];
+  if (rc >= 0) x[rc] = s;
+}
+
+// ---- the same for EIGP columns at once -----------------------------------
+// c, y, v and x hold rows of EIGP values (columns nr .. of c read as zero).
+// The products run on the matrix cores: wavefront (b, j) of NW = 4 NJ owns
+// rows (forward; columns backward) 16b .. of the output tile and every NJ-th
+// tile of the sum; MFMA step (g, u), lane quarter q stands for entry
+// 16g + 4q + u of the summed index.  The input rows are staged CH tiles at a
+// time.  (One column after the other, two launches per level each, was 416 us
+// of a batched step of 32 problems and eight columns; so it is
+// 92 us.)
+constexpr int LVM = EIGP + 4;  // staged rows 4 apart fall into different banks
+constexpr int TREE_CH = 4;     // tiles staged per pass
+
+template <typename F>
+__device__ __forceinline__ void tree_stage(double *cs, int rows, int nthreads, F &&value) {
+  for (int e = threadIdx.x; e < rows * EIGP; e += nthreads)
+    cs[(e / EIGP) * LVM + e % EIGP] = value(e / EIGP, e % EIGP);
+}
+
+// acc += A B over one tile: a[4g + u] = entry (., 16g + 4q + u) of the lane's
+// output row, B from the staged rows at cs
+template <typename TX>
+__device__ __forceinline__ void tree_mma(d4 &acc, const TX (&a)[16], const double *cs, int mi,
+                                         int mq) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    acc = mfma16x16x4((double)a[e], cs[(16 * (e >> 2) + 4 * mq + (e & 3)) * LVM + mi], acc);
+}
+
+// The NJ wavefronts' shares of the output tile added in order; out(row, col, s)
+// for every entry.
+template <int NJ, typename F>
+__device__ __forceinline__ void tree_out(const d4 &acc, double *red, int b, int j, int mi, int mq,
+                                         F &&out) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    red[(j * TS + 16 * b + mq + 4 * r) * EIGP + mi] = acc[r];
+  __syncthreads();
+  for (int e = threadIdx.x; e < TS * EIGP; e += 256 * NJ) {
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) s += red[u * TS * EIGP + e];
+    out(e / EIGP, e % EIGP, s);
+  }
+}
+
+template <typename TX, int NJ>
+__global__ void __launch_bounds__(256 * NJ) k_tree_fwd_multi(TreeDev t, int f0, int nr,
+                                                             const TX *__restrict__ X,
+                                                             const double *__restrict__ c,
+                                                             double *__restrict__ y,
+                                                             double *__restrict__ v) {
+  __shared__ double cs[TREE_CH * TS * LVM], red[NJ * TS * EIGP];
+  const int f = f0 + blockIdx.y, I = blockIdx.x;
+  const int K = t.K[f];
+  if (I >= t.T[f]) return;
+  const int rb = t.rbase[f], jn = I < K ? I + 1 : K;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, mi = l & 15, mq = l >> 4;
+  const int b = w & 3, j = w >> 2;
+  auto children = [&](int r, int k) {
+    double s = 0.0;
+    for (int g = t.gptr[r]; g < t.gptr[r + 1]; ++g) s += v[(size_t)t.gsrc[g] * EIGP + k];
+    return s;
+  };
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int c0 = 0; c0 < jn; c0 += TREE_CH) {
+    const int nt = min(TREE_CH, jn - c0);
+    __syncthreads();  // the last pass's reads of cs done
+    tree_stage(cs, nt * TS, 256 * NJ, [&](int r, int k) {
+      const int row = rb + c0 * TS + r, rc = t.row_coarse[row];
+      return (rc >= 0 && k < nr ? c[(size_t)rc * EIGP + k] : 0.0) + children(row, k);
+    });
+    __syncthreads();
+    for (int J = j; J < nt; J += NJ) {
+      const TX *x = xtile(X, t, f, I, c0 + J) + (16 * b + mi) * TS + 4 * mq;
+      TX a[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) a[e] = x[16 * (e >> 2) + (e & 3)];
+      tree_mma(acc, a, cs + J * TS * LVM, mi, mq);
+    }
+  }
+  tree_out<NJ>(acc, red, b, j, mi, mq, [&](int r, int k, double s) {
+    const int R = I * TS + r;
+    if (I < K) {
+      const int rc = t.row_coarse[rb + R];
+      if (rc >= 0) y[(size_t)rc * EIGP + k] = s;
+    } else if (R - K * TS < t.udof[f]) {
+      v[(size_t)(t.vbase[f] + R - K * TS) * EIGP + k] = s + children(rb + R, k);
+    }
+  });
+}
+
+template <typename TX, int NJ>
+__global__ void __launch_bounds__(256 * NJ) k_tree_bwd_multi(TreeDev t, int f0,
+                                                             const TX *__restrict__ X,
+                                                             const double *__restrict__ y,
+                                                             double *__restrict__ x) {
+  __shared__ double zs[TREE_CH * TS * LVM], red[NJ * TS * EIGP];
+  const int f = f0 + blockIdx.y, J = blockIdx.x;
+  const int K = t.K[f], T = t.T[f];
+  if (J >= K) return;
+  const int rb = t.rbase[f];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, mi = l & 15, mq = l >> 4;
+  const int b = w & 3, j = w >> 2;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int c0 = J; c0 < T; c0 += TREE_CH) {
+    const int nt = min(TREE_CH, T - c0);
+    __syncthreads();
+    tree_stage(zs, nt * TS, 256 * NJ, [&](int r, int k) {
+      const int R = c0 * TS + r, rc = t.row_coarse[rb + R];
+      return rc < 0 ? 0.0 : (R < K * TS ? y : x)[(size_t)rc * EIGP + k];
+    });
+    __syncthreads();
+    for (int I = j; I < nt; I += NJ) {
+      const TX *xt = xtile(X, t, f, c0 + I, J) + 4 * mq * TS + 16 * b + mi;
+      TX a[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) a[e] = xt[(16 * (e >> 2) + (e & 3)) * TS];
+      tree_mma(acc, a, zs + I * TS * LVM, mi, mq);
+    }
+  }
+  tree_out<NJ>(acc, red, b, j, mi, mq, [&](int r, int k, double s) {
+    const int rc = t.row_coarse[rb + J * TS + r];
+    if (rc >= 0) x[(size_t)rc * EIGP + k] = s;
+  });
 }
 
 // ------------------------------------------------------------- launchers ---
@@ -352,32 +646,93 @@ void launch_tree_x_to_f32(hipStream_t s, const double *X, float *Xf, long long n
   hipLaunchKernelGGL(k_x_to_f32, dim3((unsigned)b), dim3(WG), 0, s, X, Xf, n);
 }
 
+// Workgroups of a level: a whole tile each, four wavefronts, or sixteen where a
+// front has more than four tiles to sum (a front whose vector leaves no LDS
+// for their sums: four).  Few large fronts (at most 512 such workgroups):
+// sixteen wavefronts per quarter of a tile, so that a row's or column's tiles
+// arrive at more compute units.  Forward that pays from more than sixteen
+// tiles (one front of 34 tiles 17.0 -> 10.4 us; eight of 35 rows by 5 columns
+// 9.1 -> 15.5, their gathers being repeated), backward from more than four
+// (10.2 -> 8.4, 11.2 -> 8.4).
+static bool tree_wide(int sum_tiles) { return sum_tiles > 4 && sum_tiles <= 300; }
+static bool tree_quarter(int out_tiles, int nf, int sum_tiles, int from) {
+  return tree_wide(sum_tiles) && sum_tiles > from && (long long)out_tiles * nf <= 512;
+}
+
 template <typename TX>
 void launch_tree_solve(hipStream_t s, const TreeDev &t, const std::vector<int> &lvl_ptr,
                        const std::vector<int> &lvl_maxT, const std::vector<int> &lvl_maxK,
                        int maxK, int maxT, const TX *X, const double *c, double *y, double *v,
                        double *x, const int *done) {
   const int nl = (int)lvl_ptr.size() - 1;
-  allow_lds(k_tree_fwd<TX>, (size_t)maxK * TS * sizeof(double));
-  allow_lds(k_tree_bwd<TX>, (size_t)maxT * TS * sizeof(double));
+  const size_t smk = (size_t)maxK * TS * sizeof(double), smt = (size_t)maxT * TS * sizeof(double);
+  allow_lds(k_tree_fwd<TX, 1, 4>, smk);
+  allow_lds(k_tree_fwd<TX, 4, 4>, smk);
+  allow_lds(k_tree_fwd<TX, 16, 1>, smk);
+  allow_lds(k_tree_bwd<TX, 1>, smt);
+  allow_lds(k_tree_bwd<TX, 4>, smt);
+  allow_lds(k_tree_bwd_quarter<TX>, smt);
   for (int h = 0; h < nl; ++h) {
-    const int f0 = lvl_ptr[h], nf = lvl_ptr[h + 1] - f0;
-    hipLaunchKernelGGL((k_tree_fwd<TX>), dim3(lvl_maxT[h], nf), dim3(WG),
-                       (size_t)lvl_maxK[h] * TS * sizeof(double), s, t, f0, X, c, y, v, done);
+    const int f0 = lvl_ptr[h], nf = lvl_ptr[h + 1] - f0, nt = lvl_maxT[h], nk = lvl_maxK[h];
+    const size_t sm = (size_t)nk * TS * sizeof(double);
+    if (tree_quarter(nt, nf, nk, 16))
+      hipLaunchKernelGGL((k_tree_fwd<TX, 16, 1>), dim3(4 * nt, nf), dim3(1024), sm, s, t, f0, X, c,
+                         y, v, done);
+    else if (tree_wide(nk))
+      hipLaunchKernelGGL((k_tree_fwd<TX, 4, 4>), dim3(nt, nf), dim3(1024), sm, s, t, f0, X, c, y,
+                         v, done);
+    else
+      hipLaunchKernelGGL((k_tree_fwd<TX, 1, 4>), dim3(nt, nf), dim3(256), sm, s, t, f0, X, c, y, v,
+                         done);
   }
   for (int h = nl - 1; h >= 0; --h) {
-    const int f0 = lvl_ptr[h], nf = lvl_ptr[h + 1] - f0;
-    hipLaunchKernelGGL((k_tree_bwd<TX>), dim3(lvl_maxK[h], nf), dim3(WG),
-                       (size_t)lvl_maxT[h] * TS * sizeof(double), s, t, f0, X, y, x, done);
+    const int f0 = lvl_ptr[h], nf = lvl_ptr[h + 1] - f0, nt = lvl_maxT[h], nk = lvl_maxK[h];
+    const size_t sm = (size_t)nt * TS * sizeof(double);
+    if (tree_quarter(nk, nf, nt, 4))
+      hipLaunchKernelGGL((k_tree_bwd_quarter<TX>), dim3(4 * nk, nf), dim3(1024), sm, s, t, f0, X, y,
+                         x, done);
+    else if (tree_wide(nt))
+      hipLaunchKernelGGL((k_tree_bwd<TX, 4>), dim3(nk, nf), dim3(1024), sm, s, t, f0, X, y, x, done);
+    else
+      hipLaunchKernelGGL((k_tree_bwd<TX, 1>), dim3(nk, nf), dim3(256), sm, s, t, f0, X, y, x, done);
   }
 }
-template void launch_tree_solve<double>(hipStream_t, const TreeDev &, const std::vector<int> &,
-                                        const std::vector<int> &, const std::vector<int> &, int,
-                                        int, const double *, const double *, double *, double *,
-                                        double *, const int *);
-template void launch_tree_solve<float>(hipStream_t, const TreeDev &, const std::vector<int> &,
-                                       const std::vector<int> &, const std::vector<int> &, int, int,
-                                       const float *, const double *, double *, double *, double *,
-                                       const int *);
+
+template <typename TX>
+void launch_tree_solve_multi(hipStream_t s, const TreeDev &t, const std::vector<int> &lvl_ptr,
+                             const std::vector<int> &lvl_maxT, const std::vector<int> &lvl_maxK,
+                             int nr, const TX *X, const double *c, double *y, double *v,
+                             double *x) {
+  const int nl = (int)lvl_ptr.size() - 1;
+  for (int h = 0; h < nl; ++h) {
+    const int f0 = lvl_ptr[h];
+    const dim3 grid(lvl_maxT[h], lvl_ptr[h + 1] - f0);
+    if (lvl_maxK[h] > 1)
+      hipLaunchKernelGGL((k_tree_fwd_multi<TX, 4>), grid, dim3(1024), 0, s, t, f0, nr, X, c, y, v);
+    else
+      hipLaunchKernelGGL((k_tree_fwd_multi<TX, 1>), grid, dim3(256), 0, s, t, f0, nr, X, c, y, v);
+  }
+  for (int h = nl - 1; h >= 0; --h) {
+    const int f0 = lvl_ptr[h];
+    const dim3 grid(lvl_maxK[h], lvl_ptr[h + 1] - f0);
+    if (lvl_maxT[h] > 1)
+      hipLaunchKernelGGL((k_tree_bwd_multi<TX, 4>), grid, dim3(1024), 0, s, t, f0, X, y, x);
+    else
+      hipLaunchKernelGGL((k_tree_bwd_multi<TX, 1>), grid, dim3(256), 0, s, t, f0, X, y, x);
+  }
+}
+
+#define AMSP_TREE_INST(TX)                                                                      \
+  template void launch_tree_solve<TX>(hipStream_t, const TreeDev &, const std::vector<int> &,   \
+                                      const std::vector<int> &, const std::vector<int> &, int,  \
+                                      int, const TX *, const double *, double *, double *,      \
+                                      double *, const int *);                                   \
+  template void launch_tree_solve_multi<TX>(hipStream_t, const TreeDev &,                       \
+                                            const std::vector<int> &, const std::vector<int> &, \
+                                            const std::vector<int> &, int, const TX *,          \
+                                            const double *, double *, double *, double *);
+AMSP_TREE_INST(double)
+AMSP_TREE_INST(float)
+#undef AMSP_TREE_INST
 
 }  // namespace amsp
