@@ -1511,21 +1511,15 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
     ALLOC(h->ec32, float, nenv + 1);
     launch_streams_to_env(s, p, h->ntilerows, h->fst32, h->bst32, h->dg32, h->er32, h->ec32);
   }
-  launch_gather_multi(s, p, n, nr, r, bX);
-  if (do_local) {
-    if (mixed)
-      launch_env_solve_block<float>(s, p, h->dg32, h->er32, h->ec32, bX, bY, nullptr);
-    else
-      launch_env_solve_block<double>(s, p, h->dg64, h->erow64, h->ecol64, bX, bY, nullptr);
-  }
+  launch_cols_to_rows(s, n, (size_t)n, nr, r, bX);
   const void *phi = mixed ? h->phi_lo : (const void *)h->phi64;
   if (do_coarse) {
     if (!mixed)
-      launch_restrict_multi<double>(s, p, nr, (const double *)phi, bX, bC);
+      launch_restrict_rows<double>(s, p, nr, (const double *)h->phi_nat, bX, bC);
     else if (!bf)
-      launch_restrict_multi<float>(s, p, nr, (const float *)phi, bX, bC);
+      launch_restrict_rows<float>(s, p, nr, (const float *)h->phi_nat, bX, bC);
     else
-      launch_restrict_multi<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)phi, bX, bC);
+      launch_restrict_rows<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)h->phi_nat, bX, bC);
     // t_k = W0^T (W0 c_k) for all columns, W0's tiles read once per product
     if (h->tree) {
       coarse_solve_tree_multi(h, s, nr, bC, bT);
@@ -1537,16 +1531,31 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
       launch_trmm<float>(s, h->W0f, h->T0, bC2, nr, bPart, bT, 1);
     }
   }
-  const double *tcoarse = do_coarse ? bT : nullptr;
-  const double *ylocal = do_local ? bY : nullptr;
-  if (!mixed)
-    launch_prolong_multi<double>(s, p, nr, (const double *)phi, tcoarse, ylocal, bXN);
-  else if (!bf)
-    launch_prolong_multi<float>(s, p, nr, (const float *)phi, tcoarse, ylocal, bXN);
-  else
-    launch_prolong_multi<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)phi, tcoarse,
-                                         ylocal, bXN);
-  launch_scatter_multi(s, n, nr, h->inv_ptr, h->inv_x, bXN, z);
+  // the local solves add the prolongation of the coarse part as they store
+  const double *t = do_coarse ? bT : nullptr;
+  if (do_local) {
+    if (!mixed)
+      launch_solve_rows<double, double>(s, p, nr, h->dg64, h->erow64, h->ecol64, bX,
+                                        (const double *)phi, t, bY, bXN);
+    else if (!bf)
+      launch_solve_rows<float, float>(s, p, nr, h->dg32, h->er32, h->ec32, bX, (const float *)phi,
+                                      t, bY, bXN);
+    else
+      launch_solve_rows<float, __hip_bfloat16>(s, p, nr, h->dg32, h->er32, h->ec32, bX,
+                                               (const __hip_bfloat16 *)phi, t, bY, bXN);
+  } else if (do_coarse) {
+    if (!mixed)
+      launch_prolong_rows<double>(s, p, nr, (const double *)phi, t, bXN);
+    else if (!bf)
+      launch_prolong_rows<float>(s, p, nr, (const float *)phi, t, bXN);
+    else
+      launch_prolong_rows<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)phi, t, bXN);
+  } else {  // coarse part asked for, but no coarse space
+    launch_fill(s, (size_t)n * nr, z, 0.0);
+    HIP_TRY(hipGetLastError());
+    return AMSP_OK;
+  }
+  launch_scatter_cols(s, n, nr, h->inv_ptr, h->inv_x, bXN, z);
   HIP_TRY(hipGetLastError());
   return AMSP_OK;
 }

@@ -179,24 +179,32 @@ void launch_scatter_sum_t(hipStream_t s, const Plan &p, int max_ni, int n, const
                           const int *done);
 
 // ------------------------------------------------------- several columns ---
-// Up to EIGP right-hand sides per pass (k_multi.hip): gather into X (per
-// region npad_i rows of EIGP doubles, local order), restriction of every
-// column into c (columns ncp apart), prolongation + local solution into XN
-// (ascending-global-index layout), scatter into z (columns n apart).
-void launch_gather_multi(hipStream_t s, const Plan &p, int n, int nr, const double *r, double *X);
+// Up to EIGP right-hand sides per pass (k_multi.hip).  Vectors are rows of
+// W = row_width(nr) values, coarse vectors rows of EIGP; see k_multi.hip.
+int row_width(int nr);
+void launch_cols_to_rows(hipStream_t s, int n, size_t ld, int nr, const double *A, double *R);
+// c = R0 R (phi: the copy made by launch_basis_to_natural)
 template <typename TB>
-void launch_restrict_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
-                           const double *X, double *c);
+void launch_restrict_rows(hipStream_t s, const Plan &p, int nr, const TB *phi, const double *R,
+                          double *c);
+// XN = local solves of the gathered rows + Phi_i t_i (t null: without; phi in
+// local order); Y: padded rows of W, scratch
+template <typename T, typename TB>
+void launch_solve_rows(hipStream_t s, const Plan &p, int nr, const T *diag, const T *erow,
+                       const T *ecol, const double *R, const TB *phi, const double *t, double *Y,
+                       double *XN);
+// XN = Phi_i t_i alone
 template <typename TB>
-void launch_prolong_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
-                          const double *t, const double *Y, double *XN);
-void launch_scatter_multi(hipStream_t s, int n, int nr, const int *inv_ptr, const int *ix,
-                          const double *XN, double *z);
-// y_k = W0 x_k (transpose 0) or W0^T x_k (1) for k < nr, vectors ncp apart,
-// reading W0's tiles once; part holds T0 * T0 * 64 * EIGP doubles.
+void launch_prolong_rows(hipStream_t s, const Plan &p, int nr, const TB *phi, const double *t,
+                         double *XN);
+// z (columns n apart) = sum of every dof's copies in XN
+void launch_scatter_cols(hipStream_t s, int n, int nr, const int *inv_ptr, const int *ix,
+                         const double *XN, double *z);
+// y = W0 x (transpose 0) or W0^T x (1), reading W0's tiles once; part holds
+// T0 * T0 * 64 * W doubles.
 template <typename T>
-void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr,
-                 double *part, double *y, int transpose);
+void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr, double *part,
+                 double *y, int transpose);
 // CG on nr columns ld apart, one recurrence per column: Y = A X (entries
 // read once for all columns); out[k] = A_k . B_k (part: 256 * nr doubles);
 // x_k += alpha_k p_k, r_k -= alpha_k q_k with rr[k] = r_k . r_k; p_k = z_k +

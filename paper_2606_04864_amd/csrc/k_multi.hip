@@ -1,214 +1,352 @@
 // Several right-hand sides at once: z_k = M^{-1} r_k for up to EIGP columns
 // with one pass over the local factors.  With many columns the local solves
-// become triangular solves with a block of right-hand sides, whose diagonal
-// products run on the matrix cores: the same block solve the eigensolver
-// uses (k_env_solve_block), here with the Dirichlet factor of the apply.
+// become triangular solves with a block of right-hand sides, whose products
+// run on the matrix cores: the block solve that the eigensolver uses
+// (env_solve), here with the Dirichlet factor of the apply.
 //
-// Layouts: the columns of r and z are n apart (column-major n x nr); the
-// gathered block X and the solved block Y hold, per region, npad_i rows of
-// EIGP doubles in the local (RCM) order at row vp_ptr[i]; XN holds the
-// region outputs (local solve plus coarse prolongation) in the region's
-// ascending-global-index layout, the layout the scatter reads.  Columns nr ..
-// EIGP-1 and padding rows are zero.
+// Layout: inside, vectors are rows of W values, W = 8 for up to eight columns
+// and EIGP otherwise (columns nr .. W-1 zero), so that whatever reads a row
+// through an index (the regions' gathers, the matrix product's neighbours)
+// reads one 64- or 128-byte piece of memory; as columns n apart, the gather of
+// 16 columns by region took 144 us on the 1024^2 workload against 55 for one
+// transposing pass.  The coarse vectors are rows of EIGP values.  XN holds the
+// region outputs (local solve plus coarse prolongation), rows of W in the
+// region's ascending-global-index layout, which the scatter reads.
 #include "k_common.h"
+#include "k_solve.h"
 
 namespace amsp {
 
-// X[vp_i + l][k] = r_k[dof(l)] for real rows and k < nr, zero otherwise;
-// thread per row (its EIGP entries are one contiguous 128-byte row of X).
-__global__ void __launch_bounds__(WG) k_gather_multi(Plan p, int n, int nr,
-                                                     const double *__restrict__ r,
-                                                     double *__restrict__ X) {
-  const int i = blockIdx.x;
-  const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
-  const int v0 = p.vp_ptr[i], npad = p.vp_ptr[i + 1] - v0;
-  for (int l = threadIdx.x; l < npad; l += WG) {
-    const int dof = l < ni ? p.sd_dofs[r0 + l] : -1;
-    double v[EIGP];
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// f(std::integral_constant<int, W>) for the row width of nr columns
+template <typename F>
+static void with_width(int nr, F &&f) {
+  if (nr <= 8)
+    f(std::integral_constant<int, 8>{});
+  else
+    f(std::integral_constant<int, EIGP>{});
+}
+int row_width(int nr) { return nr <= 8 ? 8 : EIGP; }
+
+// Rows of W <-> columns ld apart, WG rows per workgroup through LDS (rows a
+// padded LDS row apart, so that both sides are contiguous in memory).
+template <int W>
+__global__ void __launch_bounds__(WG) k_cols_to_rows(int n, size_t ld, int nr,
+                                                     const double *__restrict__ A,
+                                                     double *__restrict__ R) {
+  __shared__ double sh[WG][W + 1];
+  const int i0 = blockIdx.x * WG, i = i0 + threadIdx.x;
+  const int ic = min(i, n - 1);
 #pragma unroll
-    for (int k = 0; k < EIGP; ++k) v[k] = (dof >= 0 && k < nr) ? r[(size_t)k * n + dof] : 0.0;
-    double2 *dst = reinterpret_cast<double2 *>(X + (size_t)(v0 + l) * EIGP);
+  for (int k = 0; k < W; ++k) {
+    const double x = A[(size_t)min(k, nr - 1) * ld + ic];
+    sh[threadIdx.x][k] = k < nr ? x : 0.0;
+  }
+  __syncthreads();
 #pragma unroll
-    for (int k = 0; k < EIGP / 2; ++k) dst[k] = make_double2(v[2 * k], v[2 * k + 1]);
+  for (int u = 0; u < W / 2; ++u) {
+    const int e = u * WG + threadIdx.x, r = e / (W / 2), c = 2 * (e % (W / 2));
+    if (i0 + r < n)
+      *reinterpret_cast<d2 *>(R + (size_t)(i0 + r) * W + c) = d2{sh[r][c], sh[r][c + 1]};
   }
 }
 
-// Restriction of every column: c_k[coff_i + q] = sum_l phi_i[l][q] X[l][k].
-// Thread (row group g, column k) adds rows g, g + 16, ... for all q (GU rows'
-// loads issued together); the 16 group sums are then added in group order.
-// The coarse vectors are rows of EIGP values (padding rows stay zero).
-template <typename TB>
-__global__ void __launch_bounds__(WG) k_restrict_multi(Plan p, int nr,
-                                                       const TB *__restrict__ phi,
-                                                       const double *__restrict__ X,
-                                                       double *__restrict__ c) {
-  constexpr int RGS = WG / EIGP;  // row groups
-  __shared__ double sh[RGS][MAXNEV][EIGP];
+// Restriction of every column: c[coff_i + q][k] = sum_l phi_i[l][q] R[dof(l)][k]
+// over the region's rows in ascending global order (phi: the copy made by
+// launch_basis_to_natural), on the matrix cores: one step takes four rows,
+// operand A the basis coefficients (lane's coefficient l & 15), B the rows.
+// The wavefronts take interleaved four-row steps, NS at a time with all loads
+// issued together, and are added in order.  Columns nr .. are stored as zero.
+template <int W, typename TB>
+__global__ void __launch_bounds__(WG) k_restrict_rows(Plan p, int nr, const TB *__restrict__ phi,
+                                                      const double *__restrict__ R,
+                                                      double *__restrict__ c) {
+  __shared__ double red[WG / 64][EIGP][EIGP];
   const int i = blockIdx.x;
-  const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0, m = p.mi[i], nev = p.nev;
-  const int k = threadIdx.x % EIGP, g = threadIdx.x / EIGP;
-  const double *Xi = X + (size_t)p.vp_ptr[i] * EIGP;
-  if (m > 0)
-    with_km(nev, [&](auto km) __attribute__((always_inline)) {
-      constexpr int KM = decltype(km)::value, GU = 4;
-      double acc[KM];
+  const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0, m = p.mi[i];
+  if (m == 0) return;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, a = l & 15, q = l >> 4;
+  const TB *ph = phi + (size_t)r0 * p.nev + (size_t)min(a, m - 1) * ni;
+  constexpr int NS = 6;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int s0 = 4 * w + q; s0 - q < ni; s0 += 16 * NS) {
+    int dof[NS];
+    TB raw[NS];
+    double x[NS];
 #pragma unroll
-      for (int q = 0; q < KM; ++q) acc[q] = 0.0;
-      for (int l0 = g; l0 < ni; l0 += GU * RGS) {
-        double x[GU];
-        TB raw[GU][KM];
+    for (int u = 0; u < NS; ++u) {
+      const int pos = min(s0 + 16 * u, ni - 1);
+      dof[u] = p.asc[r0 + pos];
+      raw[u] = ph[pos];
+    }
 #pragma unroll
-        for (int u = 0; u < GU; ++u) {
-          const int l = l0 + u * RGS, lc = min(l, ni - 1);
-          x[u] = l < ni ? Xi[(size_t)lc * EIGP + k] : 0.0;
-          basis_row_load<KM>(phi + (size_t)(r0 + lc) * nev, 1, m, raw[u]);
-        }
+    for (int u = 0; u < NS; ++u) x[u] = R[(size_t)dof[u] * W + (a & (W - 1))];
 #pragma unroll
-        for (int u = 0; u < GU; ++u)
+    for (int u = 0; u < NS; ++u) {
+      const bool in = s0 + 16 * u < ni;
+      acc = mfma16x16x4(in && a < m ? to_d(raw[u]) : 0.0, in ? x[u] : 0.0, acc);
+    }
+  }
 #pragma unroll
-          for (int q = 0; q < KM; ++q) acc[q] = fma(basis_coef<KM>(raw[u], q, m), x[u], acc[q]);
+  for (int r = 0; r < 4; ++r) red[w][q + 4 * r][a] = acc[r];
+  __syncthreads();
+  const int cq = threadIdx.x / EIGP, k = threadIdx.x % EIGP;
+  if (cq < m) {
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < WG / 64; ++u) s += red[u][cq][k];
+    c[(size_t)(p.coff[i] + cq) * EIGP + k] = k < nr ? s : 0.0;
+  }
+}
+
+// The rows of env_solve for the apply: gathered from R by the region's dofs
+// (padding rows zero), the forward result kept in Y (rows of W), the output
+// with the prolongation Phi_i t_i added (KS matrix-core steps of four
+// coefficients) written to XN in the ascending-global-index layout.  For
+// W < EIGP the lanes' columns W .. repeat columns 0 .. and are not stored.
+template <int W, int KS, typename TB>
+struct ApplyIO {
+  struct Idx {
+    int v[4];
+  };
+  struct Aux {
+    int nat[4];
+    TB phi[KS];
+  };
+  const double *R;      // [n][W]
+  double *Y, *XN;       // the region's padded rows
+  const int *dofs, *nat;
+  const TB *phi;        // [ni][nev], local order
+  int ni, nev, m, col, rb, arow, q;
+  bool keep, has_t;     // keep: the backward rows are read back (row())
+  double t[KS];         // coarse values 4s + q, column col
+  template <typename F>
+  __device__ __forceinline__ Idx idx(F, int r0) const {
+    Idx x;
+    if constexpr (F::value) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x.v[r] = dofs[min(r0 + rb + 4 * r, ni - 1)];
+    }
+    return x;
+  }
+  template <typename F>
+  __device__ __forceinline__ Aux aux(F, int r0) const {
+    Aux x;
+    if constexpr (!F::value) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x.nat[r] = nat[min(r0 + rb + 4 * r, ni - 1)];
+      const TB *ph = phi + (size_t)min(r0 + arow, ni - 1) * nev;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) x.phi[s] = ph[min(4 * s + q, nev - 1)];
+    }
+    return x;
+  }
+  template <typename F>
+  __device__ __forceinline__ void load(F, int r0, const Idx &id, d4 &x) const {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = r0 + rb + 4 * r;
+      if constexpr (F::value) {
+        const double v = R[(size_t)id.v[r] * W + (col & (W - 1))];
+        x[r] = row < ni ? v : 0.0;
+      } else {  // this lane's own stores (lanes of repeated columns: their pair's)
+        x[r] = Y[(size_t)row * W + (col & (W - 1))];
+      }
+    }
+  }
+  template <typename F>
+  __device__ __forceinline__ void store(F, int r0, const d4 &y, const Aux &a) const {
+    if (F::value || keep) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (col < W) Y[(size_t)(r0 + rb + 4 * r) * W + col] = y[r];
+    }
+    if constexpr (!F::value) {
+      d4 z = y;
+      if (has_t) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) z = mfma16x16x4(4 * s + q < m ? to_d(a.phi[s]) : 0.0, t[s], z);
       }
 #pragma unroll
-      for (int q = 0; q < KM; ++q)
-        if (q < m) sh[g][q][k] = acc[q];
-    });
-  __syncthreads();
-  if ((int)threadIdx.x < m * EIGP) {
-    const int q = threadIdx.x / EIGP, kk = threadIdx.x % EIGP;
-    double s = 0.0;
-    for (int gg = 0; gg < RGS; ++gg) s += sh[gg][q][kk];
-    if (kk < nr) c[(size_t)(p.coff[i] + q) * EIGP + kk] = s;
+      for (int r = 0; r < 4; ++r)
+        if (col < W && r0 + rb + 4 * r < ni) XN[(size_t)a.nat[r] * W + col] = z[r];
+    }
   }
+  __device__ __forceinline__ double row(int r) const { return Y[(size_t)r * W + (col & (W - 1))]; }
+};
+
+template <int W, int KS, typename T, typename TB, int EVU, int PF>
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(EVU <= 4 && PF == 1 ? 3 : 2)))
+k_solve_rows(Plan p, const T *__restrict__ diag, const T *__restrict__ erow,
+             const T *__restrict__ ecol, const double *__restrict__ R, const TB *__restrict__ phi,
+             const double *__restrict__ t, double *Y, double *XN) {
+  const int i = blockIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0, npad = p.vp_ptr[i + 1] - p.vp_ptr[i];
+  const size_t v0 = p.vp_ptr[i];
+  ApplyIO<W, KS, TB> io;
+  io.R = R;
+  io.Y = Y + v0 * W;
+  io.XN = XN + v0 * W;
+  io.dofs = p.sd_dofs + r0;
+  io.nat = p.nat + r0;
+  io.phi = phi + (size_t)r0 * p.nev;
+  io.ni = ni;
+  io.nev = max(p.nev, 1);
+  io.m = t ? p.mi[i] : 0;
+  io.has_t = io.m > 0;
+  if (!io.has_t) io.phi = phi;  // never null where the basis is empty (see the launcher)
+  io.col = l & 15;
+  io.q = l >> 4;
+  io.rb = 16 * w + io.q;
+  io.arow = 16 * w + (l & 15);
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const int k = 4 * s + io.q;
+    io.t[s] = k < io.m ? t[(size_t)(p.coff[i] + k) * EIGP + io.col] : 0.0;
+  }
+  // blocks whose segments reach beyond the ring (a block's longest column
+  // segment is its last) or hold more entries than are staged read finished
+  // rows from memory: the backward rows are then kept in Y as well
+  const int *up = p.uptr + v0 + i;
+  int far = 0;
+  for (int r = TS * ((int)threadIdx.x + 1) - 1; r < npad; r += TS * WG)
+    far |= up[r + 1] - up[r] > SOLVE_RING || up[r + 1] - up[r + 1 - TS] > EVU * WG;
+  io.keep = __syncthreads_or(far) != 0;
+  env_solve<EVU, PF>(p, i, diag, erow, ecol, io);
 }
 
-// XN[vp_i + nat(l)][k] = Y[vp_i + l][k] + sum_q phi_i[l][q] t_k[coff_i + q]
-// (without the coarse part when t is null; without the local part when Y is).
-// The region's coarse values are staged in LDS; thread per row.
-template <typename TB>
-__global__ void __launch_bounds__(WG) k_prolong_multi(Plan p, int nr,
-                                                      const TB *__restrict__ phi,
-                                                      const double *__restrict__ t,
-                                                      const double *__restrict__ Y,
-                                                      double *__restrict__ XN) {
-  __shared__ double tl[MAXNEV][EIGP];
+// XN = Phi_i t_i alone (the coarse part without the local solves); thread per
+// row, the region's coarse values in LDS.
+template <int W, typename TB>
+__global__ void __launch_bounds__(WG) k_prolong_rows(Plan p, const TB *__restrict__ phi,
+                                                     const double *__restrict__ t,
+                                                     double *__restrict__ XN) {
+  __shared__ double tl[MAXNEV][W];
   const int i = blockIdx.x;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0, m = p.mi[i], nev = p.nev;
   const size_t v0 = p.vp_ptr[i];
-  const int co = p.coff[i];
-  if (t && (int)threadIdx.x < MAXNEV * EIGP) {
-    const int q = threadIdx.x / EIGP, k = threadIdx.x % EIGP;
-    tl[q][k] = (q < m && k < nr) ? t[(size_t)(co + q) * EIGP + k] : 0.0;
-  }
+  for (int e = threadIdx.x; e < m * W; e += WG)
+    tl[e / W][e % W] = t[(size_t)(p.coff[i] + e / W) * EIGP + e % W];
   __syncthreads();
   for (int l = threadIdx.x; l < ni; l += WG) {
-    double v[EIGP];
-    if (Y) {
-      const double2 *src = reinterpret_cast<const double2 *>(Y + (v0 + l) * EIGP);
+    double v[W];
 #pragma unroll
-      for (int k = 0; k < EIGP / 2; ++k) {
-        const double2 y = src[k];
-        v[2 * k] = y.x;
-        v[2 * k + 1] = y.y;
-      }
-    } else {
+    for (int k = 0; k < W; ++k) v[k] = 0.0;
+    for (int q = 0; q < m; ++q) {
+      const double a = to_d(phi[(size_t)(r0 + l) * nev + q]);
 #pragma unroll
-      for (int k = 0; k < EIGP; ++k) v[k] = 0.0;
+      for (int k = 0; k < W; ++k) v[k] = fma(a, tl[q][k], v[k]);
     }
-    if (t && m > 0)
-      with_km(nev, [&](auto km) __attribute__((always_inline)) {
-        constexpr int KM = decltype(km)::value;
-        TB raw[KM];
-        basis_row_load<KM>(phi + (size_t)(r0 + l) * nev, 1, m, raw);
+    d2 *dst = reinterpret_cast<d2 *>(XN + (v0 + p.nat[r0 + l]) * W);
 #pragma unroll
-        for (int q = 0; q < KM; ++q)
-          if (q < m) {  // the loads above are already in flight
-            const double a = basis_coef<KM>(raw, q, m);
-#pragma unroll
-            for (int k = 0; k < EIGP; ++k) v[k] = fma(a, tl[q][k], v[k]);
-          }
-      });
-#pragma unroll
-    for (int k = 0; k < EIGP; ++k)
-      if (k >= nr) v[k] = 0.0;
-    double2 *dst = reinterpret_cast<double2 *>(XN + (v0 + p.nat[r0 + l]) * EIGP);
-#pragma unroll
-    for (int k = 0; k < EIGP / 2; ++k) dst[k] = make_double2(v[2 * k], v[2 * k + 1]);
+    for (int k = 0; k < W / 2; ++k) dst[k] = d2{v[2 * k], v[2 * k + 1]};
   }
 }
 
-// z_k[j] = sum over the copies of dof j (fixed map order) of XN[copy][k];
-// thread per dof, the copies' rows read whole, each column written coalesced.
-__global__ void __launch_bounds__(WG) k_scatter_multi(int n, int nr, const int *__restrict__ inv_ptr,
-                                                      const int *__restrict__ ix,
-                                                      const double *__restrict__ XN,
-                                                      double *__restrict__ z) {
-  const int j = blockIdx.x * WG + threadIdx.x;
-  if (j >= n) return;
-  double s[EIGP];
+// Sum over the copies of row i (fixed map order) of the columns c, c + 1 of XN;
+// the first CU copies' index and value loads are issued together.
+template <int W>
+__device__ __forceinline__ d2 sum_copies(int i, int c, const int *__restrict__ inv_ptr,
+                                         const int *__restrict__ ix,
+                                         const double *__restrict__ XN) {
+  constexpr int CU = 4;
+  const int e0 = inv_ptr[i], e1 = inv_ptr[i + 1];
+  int src[CU];
+  d2 x[CU];
 #pragma unroll
-  for (int k = 0; k < EIGP; ++k) s[k] = 0.0;
-  for (int e = inv_ptr[j]; e < inv_ptr[j + 1]; ++e) {
-    const double2 *row = reinterpret_cast<const double2 *>(XN + (size_t)ix[e] * EIGP);
+  for (int u = 0; u < CU; ++u) src[u] = ix[min(e0 + u, e1 - 1)];
 #pragma unroll
-    for (int k = 0; k < EIGP / 2; ++k) {
-      const double2 x = row[k];
-      s[2 * k] += x.x;
-      s[2 * k + 1] += x.y;
-    }
+  for (int u = 0; u < CU; ++u) x[u] = *reinterpret_cast<const d2 *>(XN + (size_t)src[u] * W + c);
+  d2 s = {0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < CU; ++u) {
+    const d2 a = s + x[u];
+    s = e0 + u < e1 ? a : s;
   }
+  for (int e = e0 + CU; e < e1; ++e) s += *reinterpret_cast<const d2 *>(XN + (size_t)ix[e] * W + c);
+  return s;
+}
+
+// z_k[j] = sum over the copies of dof j of XN[copy][k], columns n apart:
+// W / 2 lanes per row, WG rows per workgroup, through LDS.
+template <int W>
+__global__ void __launch_bounds__(WG) k_scatter_cols(int n, int nr, const int *__restrict__ inv_ptr,
+                                                     const int *__restrict__ ix,
+                                                     const double *__restrict__ XN,
+                                                     double *__restrict__ z) {
+  __shared__ double sh[WG][W + 1];
+  const int i0 = blockIdx.x * WG;
 #pragma unroll
-  for (int k = 0; k < EIGP; ++k)
-    if (k < nr) z[(size_t)k * n + j] = s[k];
+  for (int u = 0; u < W / 2; ++u) {
+    const int e = u * WG + threadIdx.x, r = e / (W / 2), c = 2 * (e % (W / 2));
+    const d2 s = sum_copies<W>(min(i0 + r, n - 1), c, inv_ptr, ix, XN);
+    sh[r][c] = s[0];
+    sh[r][c + 1] = s[1];
+  }
+  __syncthreads();
+  const int i = i0 + threadIdx.x;
+  if (i >= n) return;
+#pragma unroll
+  for (int k = 0; k < W; ++k)
+    if (k < nr) z[(size_t)k * n + i] = sh[threadIdx.x][k];
 }
 
 // Coarse solve of every column: the product with the tiles of W0 (or W0^T)
-// for all columns at once, so W0 is read once.  Workgroup per lower tile
-// (I, J); the input block (64 rows x EIGP columns of tile K = J, or I
-// transposed) is staged in LDS; part[(O * T0 + K)][row][k] holds the tile's
-// contribution to output tile O (I, or J transposed).
-template <typename T>
+// for all columns at once, so W0 is read once, on the matrix cores.  Workgroup
+// per lower tile (I, J), wavefront w rows 16w .. of the product; MFMA step
+// (g, u), lane quarter q stands for entry 16g + 4q + u of the summed index, so
+// a lane reads four neighbouring entries of W0 per group.
+// part[(O * T0 + K)][row][k] (rows of W) holds the tile's contribution to
+// output tile O (I, or J transposed) from input tile K (J, or I transposed).
+template <int W, typename T>
 __global__ void __launch_bounds__(WG) k_trmm_tiles(const T *__restrict__ Wt, int T0,
-                                                   const double *__restrict__ x, int nr,
+                                                   const double *__restrict__ x,
                                                    double *__restrict__ part, int transpose) {
-  __shared__ double xs[TS][EIGP];
   const int b = blockIdx.x;
   int I = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
   while ((I + 1) * (I + 2) / 2 <= b) ++I;
   while (I * (I + 1) / 2 > b) --I;
   const int J = b - I * (I + 1) / 2;  // J <= I
-  const T *w = Wt + ((size_t)I * T0 + J) * TE;
+  const T *t = Wt + ((size_t)I * T0 + J) * TE;
   const int K = transpose ? I : J, O = transpose ? J : I;
-  for (int e = threadIdx.x; e < TS * EIGP; e += WG) {
-    const int rr = e / EIGP, k = e % EIGP;
-    xs[rr][k] = k < nr ? x[(size_t)(K * TS + rr) * EIGP + k] : 0.0;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, mi = l & 15, mq = l >> 4;
+  const T *row = transpose ? t + 4 * mq * TS + 16 * w + mi : t + (16 * w + mi) * TS + 4 * mq;
+  const int step = transpose ? TS : 1;
+  const double *xr = x + ((size_t)K * TS + 4 * mq) * EIGP + mi;
+  T a[16];
+  double v[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int k = 16 * (e >> 2) + (e & 3);
+    a[e] = row[k * step];
+    v[e] = xr[k * EIGP];
   }
-  __syncthreads();
-  const int o = threadIdx.x % TS, kq = threadIdx.x / TS;  // output row o, columns 4kq..4kq+3
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  for (int c = 0; c < TS; ++c) {
-    const double wv = transpose ? (double)w[c * TS + o] : (double)w[o * TS + c];
-    a0 = fma(wv, xs[c][4 * kq], a0);
-    a1 = fma(wv, xs[c][4 * kq + 1], a1);
-    a2 = fma(wv, xs[c][4 * kq + 2], a2);
-    a3 = fma(wv, xs[c][4 * kq + 3], a3);
-  }
-  double *dst = part + (((size_t)O * T0 + K) * TS + o) * EIGP + 4 * kq;
-  dst[0] = a0;
-  dst[1] = a1;
-  dst[2] = a2;
-  dst[3] = a3;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc = mfma16x16x4((double)a[e], v[e], acc);
+  double *dst = part + (((size_t)O * T0 + K) * TS + 16 * w + mq) * W + mi;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (mi < W) dst[4 * r * W] = acc[r];
 }
 
-// y_k[O*64 + r] = sum over input tiles K (in order) of part[(O*T0 + K)][r][k]
-__global__ void __launch_bounds__(TS * EIGP) k_trmm_reduce(int T0, const double *__restrict__ part,
-                                                           double *__restrict__ y, int nr,
-                                                           int transpose) {
-  const int O = blockIdx.x, r = threadIdx.x / EIGP, k = threadIdx.x % EIGP;
+// y[O*64 + r][k] = sum over input tiles K (in order) of part[(O*T0 + K)][r][k];
+// columns W .. of y are stored as zero.
+template <int W>
+__global__ void __launch_bounds__(WG) k_trmm_reduce(int T0, const double *__restrict__ part,
+                                                    double *__restrict__ y, int transpose) {
+  constexpr int RW = WG / EIGP;  // rows per workgroup
+  const int O = blockIdx.x / (TS / RW), r = RW * (blockIdx.x % (TS / RW)) + threadIdx.x / EIGP;
+  const int k = threadIdx.x % EIGP;
   const int k0 = transpose ? O : 0, k1 = transpose ? T0 : O + 1;
   double s = 0.0;
-#pragma unroll 4
-  for (int K = k0; K < k1; ++K) s += part[(((size_t)O * T0 + K) * TS + r) * EIGP + k];
-  if (k < nr) y[(size_t)(O * TS + r) * EIGP + k] = s;
+  if (k < W) {
+#pragma unroll 8
+    for (int K = k0; K < k1; ++K) s += part[(((size_t)O * T0 + K) * TS + r) * W + k];
+  }
+  y[(size_t)(O * TS + r) * EIGP + k] = s;
 }
 
 // The mixed forms keep their f32 factor only as the two per-sweep streams;
@@ -357,43 +495,80 @@ void launch_streams_to_env(hipStream_t s, const Plan &p, int ntilerows, const fl
   hipLaunchKernelGGL(k_streams_to_env, dim3(ntilerows), dim3(WG), 0, s, p, fst, bst, dg, er, ec);
 }
 
-void launch_gather_multi(hipStream_t s, const Plan &p, int n, int nr, const double *r, double *X) {
-  hipLaunchKernelGGL(k_gather_multi, dim3(p.N), dim3(WG), 0, s, p, n, nr, r, X);
+void launch_cols_to_rows(hipStream_t s, int n, size_t ld, int nr, const double *A, double *R) {
+  with_width(nr, [&](auto w) {
+    hipLaunchKernelGGL((k_cols_to_rows<decltype(w)::value>), dim3((n + WG - 1) / WG), dim3(WG), 0,
+                       s, n, ld, nr, A, R);
+  });
 }
 
 template <typename TB>
-void launch_restrict_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
-                           const double *X, double *c) {
-  hipLaunchKernelGGL((k_restrict_multi<TB>), dim3(p.N), dim3(WG), 0, s, p, nr, phi, X, c);
+void launch_restrict_rows(hipStream_t s, const Plan &p, int nr, const TB *phi, const double *R,
+                          double *c) {
+  with_width(nr, [&](auto w) {
+    hipLaunchKernelGGL((k_restrict_rows<decltype(w)::value, TB>), dim3(p.N), dim3(WG), 0, s, p, nr,
+                       phi, R, c);
+  });
+}
+
+// Staged entries and blocks in flight as for launch_env_solve_block; KS: the
+// matrix-core steps of four coefficients that hold nev.
+template <typename T, typename TB>
+void launch_solve_rows(hipStream_t s, const Plan &p, int nr, const T *diag, const T *erow,
+                       const T *ecol, const double *R, const TB *phi, const double *t, double *Y,
+                       double *XN) {
+  // without a basis the kernel's (unused) coefficient loads read the factor
+  if (!phi) phi = reinterpret_cast<const TB *>(diag);
+  auto go = [&](auto w, auto ks) {
+    constexpr int W = decltype(w)::value, KS = decltype(ks)::value, PF = sizeof(T) == 8 ? 2 : 1;
+    if (p.env_mean <= 700)
+      hipLaunchKernelGGL((k_solve_rows<W, KS, T, TB, 4, PF>), dim3(p.N), dim3(WG), 0, s, p, diag,
+                         erow, ecol, R, phi, t, Y, XN);
+    else
+      hipLaunchKernelGGL((k_solve_rows<W, KS, T, TB, 16, 1>), dim3(p.N), dim3(WG), 0, s, p, diag,
+                         erow, ecol, R, phi, t, Y, XN);
+  };
+  with_width(nr, [&](auto w) {
+    if (p.nev <= 8)
+      go(w, std::integral_constant<int, 2>{});
+    else
+      go(w, std::integral_constant<int, 4>{});
+  });
 }
 
 template <typename TB>
-void launch_prolong_multi(hipStream_t s, const Plan &p, int nr, const TB *phi,
-                          const double *t, const double *Y, double *XN) {
-  hipLaunchKernelGGL((k_prolong_multi<TB>), dim3(p.N), dim3(WG), 0, s, p, nr, phi, t, Y, XN);
+void launch_prolong_rows(hipStream_t s, const Plan &p, int nr, const TB *phi, const double *t,
+                         double *XN) {
+  with_width(nr, [&](auto w) {
+    hipLaunchKernelGGL((k_prolong_rows<decltype(w)::value, TB>), dim3(p.N), dim3(WG), 0, s, p, phi,
+                       t, XN);
+  });
 }
 
-void launch_scatter_multi(hipStream_t s, int n, int nr, const int *inv_ptr, const int *ix,
-                          const double *XN, double *z) {
-  const unsigned b = (unsigned)(((long long)n + WG - 1) / WG);
-  if (b == 0) return;
-  hipLaunchKernelGGL(k_scatter_multi, dim3(b), dim3(WG), 0, s, n, nr, inv_ptr, ix, XN, z);
+void launch_scatter_cols(hipStream_t s, int n, int nr, const int *inv_ptr, const int *ix,
+                         const double *XN, double *z) {
+  with_width(nr, [&](auto w) {
+    hipLaunchKernelGGL((k_scatter_cols<decltype(w)::value>), dim3((n + WG - 1) / WG), dim3(WG), 0,
+                       s, n, nr, inv_ptr, ix, XN, z);
+  });
 }
 
 template <typename T>
-void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr,
-                 double *part, double *y, int transpose) {
+void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr, double *part,
+                 double *y, int transpose) {
   const int nb = T0 * (T0 + 1) / 2;
   if (nb == 0) return;
-  hipLaunchKernelGGL((k_trmm_tiles<T>), dim3(nb), dim3(WG), 0, s, Wt, T0, x, nr, part,
-                     transpose);
-  hipLaunchKernelGGL(k_trmm_reduce, dim3(T0), dim3(TS * EIGP), 0, s, T0, part, y, nr,
-                     transpose);
+  with_width(nr, [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    hipLaunchKernelGGL((k_trmm_tiles<W, T>), dim3(nb), dim3(WG), 0, s, Wt, T0, x, part, transpose);
+    hipLaunchKernelGGL((k_trmm_reduce<W>), dim3(T0 * (TS * EIGP / WG)), dim3(WG), 0, s, T0, part, y,
+                       transpose);
+  });
 }
-template void launch_trmm<double>(hipStream_t, const double *, int, const double *, int,
-                                  double *, double *, int);
-template void launch_trmm<float>(hipStream_t, const float *, int, const double *, int,
-                                 double *, double *, int);
+template void launch_trmm<double>(hipStream_t, const double *, int, const double *, int, double *,
+                                  double *, int);
+template void launch_trmm<float>(hipStream_t, const float *, int, const double *, int, double *,
+                                 double *, int);
 
 static int col_blocks(int n) {
   int b = (n + WG - 1) / WG;
@@ -490,14 +665,17 @@ void launch_col_direction(hipStream_t s, int n, size_t ld, int nr, const double 
   hipLaunchKernelGGL(k_col_direction, dim3(col_blocks(n), nr), dim3(WG), 0, s, n, ld, nr, beta, Z, P);
 }
 
-#define AMSP_MULTI_INST(TB)                                                                  \
-  template void launch_restrict_multi<TB>(hipStream_t, const Plan &, int, const TB *, \
-                                          const double *, double *);                          \
-  template void launch_prolong_multi<TB>(hipStream_t, const Plan &, int, const TB *,  \
-                                         const double *, const double *, double *);
-AMSP_MULTI_INST(double)
-AMSP_MULTI_INST(float)
-AMSP_MULTI_INST(__hip_bfloat16)
+#define AMSP_MULTI_INST(T, TB)                                                                \
+  template void launch_restrict_rows<TB>(hipStream_t, const Plan &, int, const TB *,           \
+                                         const double *, double *);                           \
+  template void launch_prolong_rows<TB>(hipStream_t, const Plan &, int, const TB *,            \
+                                        const double *, double *);                            \
+  template void launch_solve_rows<T, TB>(hipStream_t, const Plan &, int, const T *, const T *, \
+                                         const T *, const double *, const TB *,               \
+                                         const double *, double *, double *);
+AMSP_MULTI_INST(double, double)
+AMSP_MULTI_INST(float, float)
+AMSP_MULTI_INST(float, __hip_bfloat16)
 #undef AMSP_MULTI_INST
 
 }  // namespace amsp

@@ -72,3 +72,22 @@ def test_local_solve_edges(name, prec, cols):
         bar = max(1e-10, 10 * floor) if prec == "fp64" else max(1e-5, 10 * floor * 6e-8 / 1.1e-16)
         print("  err", err, "bar", bar, file=sys.stderr, flush=True)
         assert err <= bar, (j, err, bar)
+
+
+@pytest.mark.parametrize("cols", [2, 9])
+def test_columns_without_coarse_space(cols):
+    """nev = 0 (one-level Schwarz): no basis to read, the coarse part alone is zero."""
+    A, part, nparts, _ = problem("one_block")
+    st = O.setup(A.to_scipy(), part, nparts, 2, 1)
+    pc = P.setup(A, part, nparts, 0, overlap=1)
+    print("columns without coarse space", cols, file=sys.stderr, flush=True)
+    R = np.random.default_rng(7).standard_normal((cols, A.n))
+    Z = pc.apply_columns(torch.tensor(R, device="cuda"))
+    Z2 = pc.apply_columns(torch.tensor(R, device="cuda"), parts=2)
+    torch.cuda.synchronize()
+    Z, Z2 = Z.cpu().numpy(), Z2.cpu().numpy()
+    pc.close()
+    for j in range(cols):
+        ref = O.local_part(st, R[j])
+        assert np.linalg.norm(Z[j] - ref) <= 1e-10 * np.linalg.norm(ref)
+    assert not Z2.any()
