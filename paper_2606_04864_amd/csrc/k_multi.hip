@@ -176,8 +176,8 @@ struct ApplyIO {
   __device__ __forceinline__ double row(int r) const { return Y[(size_t)r * W + (col & (W - 1))]; }
 };
 
-template <int W, int KS, typename T, typename TB, int EVU, int PF>
-__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(EVU <= 4 && PF == 1 ? 3 : 2)))
+template <int W, int KS, typename T, typename TB, int EVU, int PF, int OCC>
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(OCC)))
 k_solve_rows(Plan p, const T *__restrict__ diag, const T *__restrict__ erow,
              const T *__restrict__ ecol, const double *__restrict__ R, const TB *__restrict__ phi,
              const double *__restrict__ t, double *Y, double *XN) {
@@ -512,27 +512,42 @@ void launch_restrict_rows(hipStream_t s, const Plan &p, int nr, const TB *phi, c
 }
 
 // Staged entries and blocks in flight as for launch_env_solve_block; KS: the
-// matrix-core steps of four coefficients that hold nev.
+// matrix-core steps of four coefficients that hold nev.  Workgroups per unit
+// with a float32 factor: four (128 registers, some spilled) where there are
+// regions for more than two (1024 regions, W = 8: 226 -> 199 us; the 2133
+// regions of 32 problems 446 -> 397), three otherwise (64 regions: 85 / 94).
 template <typename T, typename TB>
 void launch_solve_rows(hipStream_t s, const Plan &p, int nr, const T *diag, const T *erow,
                        const T *ecol, const double *R, const TB *phi, const double *t, double *Y,
                        double *XN) {
   // without a basis the kernel's (unused) coefficient loads read the factor
   if (!phi) phi = reinterpret_cast<const TB *>(diag);
-  auto go = [&](auto w, auto ks) {
-    constexpr int W = decltype(w)::value, KS = decltype(ks)::value, PF = sizeof(T) == 8 ? 2 : 1;
-    if (p.env_mean <= 700)
-      hipLaunchKernelGGL((k_solve_rows<W, KS, T, TB, 4, PF>), dim3(p.N), dim3(WG), 0, s, p, diag,
-                         erow, ecol, R, phi, t, Y, XN);
+  auto go = [&](auto w, auto ks, auto evu, auto pf, auto occ) {
+    hipLaunchKernelGGL((k_solve_rows<decltype(w)::value, decltype(ks)::value, T, TB,
+                                     decltype(evu)::value, decltype(pf)::value,
+                                     decltype(occ)::value>),
+                       dim3(p.N), dim3(WG), 0, s, p, diag, erow, ecol, R, phi, t, Y, XN);
+  };
+  constexpr std::integral_constant<int, 1> i1{};
+  constexpr std::integral_constant<int, 2> i2{};
+  constexpr std::integral_constant<int, 3> i3{};
+  constexpr std::integral_constant<int, 4> i4{};
+  constexpr std::integral_constant<int, 16> i16{};
+  auto variant = [&](auto w, auto ks) {
+    if (p.env_mean > 700)
+      go(w, ks, i16, i1, i2);
+    else if constexpr (sizeof(T) == 8)
+      go(w, ks, i4, i2, i2);
+    else if (p.N > 512)
+      go(w, ks, i4, i1, i4);
     else
-      hipLaunchKernelGGL((k_solve_rows<W, KS, T, TB, 16, 1>), dim3(p.N), dim3(WG), 0, s, p, diag,
-                         erow, ecol, R, phi, t, Y, XN);
+      go(w, ks, i4, i1, i3);
   };
   with_width(nr, [&](auto w) {
     if (p.nev <= 8)
-      go(w, std::integral_constant<int, 2>{});
+      variant(w, i2);
     else
-      go(w, std::integral_constant<int, 4>{});
+      variant(w, i4);
   });
 }
 

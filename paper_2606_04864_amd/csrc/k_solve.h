@@ -42,11 +42,14 @@ namespace amsp {
 //   store(fwd, r0, y, aux)
 //   row(r)               column l & 15 of finished row r of the current sweep,
 //                        for segments that reach beyond the ring
-// Measured (21 blocks of 64 rows per region, float64 / float32 factor): 64
-// regions 200 -> 91 / 84 us (1.4 us a block of products, 0.6 of waiting),
-// 1024 regions 430 -> 315 / 357 -> 220 us (5 TB/s of factor and rows); in
-// three dimensions (1728 regions of 16 blocks) 1320 -> 352 us with a float32
-// factor, whose segments of ~100 entries were a serial loop before.
+// With several workgroups per unit the instructions between the products count
+// (320 vector instructions a block): addresses are one base and constants,
+// masks are taken where a step needs one.
+// Measured in the eigensolver's sweeps (21 blocks of 64 rows per region, float64
+// / float32 factor): 64 regions 200 -> 75 / 67 us, 1024 regions 430 -> 305 /
+// 357 -> 204 us (5 TB/s of factor and rows); in three dimensions (1728 regions
+// of 16 blocks) 1320 -> 320 us with a float32 factor, whose segments of ~100
+// entries were a serial loop before.
 constexpr int SOLVE_RING = 2 * TS;  // finished rows kept in LDS
 
 template <int EVU, int PF, typename T, typename IO>
@@ -57,9 +60,14 @@ __device__ __forceinline__ void env_solve(const Plan &p, int i, const T *__restr
   constexpr int LVR = EIGP;      // neighbouring rows (ring) fall into different banks
   constexpr int RING = SOLVE_RING;
   constexpr int EVC = EVU * WG;  // envelope entries staged per block
-  __shared__ double Rg[RING * LVR];
-  __shared__ double Acc[TS * LVA];
-  __shared__ T Ev[EVC];
+  // one block, so that reads a little before or past a part (dropped by a
+  // select) stay inside it
+  __shared__ struct {
+    double Acc[TS * LVA], Rg[RING * LVR];
+    T Ev[EVC + TS];
+  } sh;
+  double *const Acc = sh.Acc, *const Rg = sh.Rg;
+  T *const Ev = sh.Ev;
   const int g0 = p.trow_ptr[i], nt = p.trow_ptr[i + 1] - g0;
   const int *ep = p.eptr + p.vp_ptr[i] + i, *up = p.uptr + p.vp_ptr[i] + i;
   const T *erow_i = erow + p.ebase[i], *ecol_i = ecol + p.ebase[i];
@@ -97,60 +105,65 @@ __device__ __forceinline__ void env_solve(const Plan &p, int i, const T *__restr
 #pragma unroll
     for (int u = 0; u < EVU; ++u) ev[u] = src[max(g.base + min(tid + WG * u, g.total - 1), 0)];
   };
-  // acc -= (segment entries) (finished rows), rows 16w..16w+15.  Row form:
-  // a segment ends at column r0 - 1, so the steps count back from r0; column
-  // form: it starts at row r0 + TS.
+  // acc = (segment entries) (finished rows) for rows 16w..16w+15, ns steps of
+  // four.  Row form: a segment ends at row r0 - 1; column form: it starts at
+  // row r0 + TS.  The steps end with the longest segment's last entry (row
+  // form) or are shifted by pad (column form), so that only the first step
+  // holds rows outside that segment; those count as zero (a zero coefficient
+  // would turn their infinities into NaN).
   auto env_part = [&](auto fwd, const T *src, const Seg &g, int r0, d4 &acc) {
     constexpr bool FWD = decltype(fwd)::value;
     const int ltop = __builtin_amdgcn_readlane(g.len, FWD ? 0 : 15);
     const int ns = (ltop + 3) >> 2;
-    const int ib = (FWD ? g.len - 4 * ns : 0) + mq;  // this lane's segment index at step 0
-    const int vb = (FWD ? r0 - 4 * ns : r0 + TS) + mq;
     if (ns == 0) return;
-    if (g.total <= EVC && ltop <= RING) {
-      // entries and rows from LDS, four steps' reads issued before the four
-      // products before them (the steps past ns read in range and are not used)
-      auto fetch = [&](int s0, double(&a)[4], double(&b)[4]) __attribute__((always_inline)) {
+    const int pad = 4 * ns - ltop;
+    const int kb = (FWD ? g.len - ltop : 0) - pad + mq;  // this lane's segment index at step 0
+    const int vb = (FWD ? r0 - ltop : r0 + TS) - pad + mq;
+    if (g.total <= EVC && ltop <= TS) {
+      // entries and rows from LDS; the rows are the last block's half of the
+      // ring, so that every address is one base and a constant
+      const T *ea = Ev + g.off + kb;
+      const double *rp =
+          Rg + (((FWD ? r0 - TS : r0 + TS) & (RING - 1)) + (FWD ? TS - 4 * ns : -pad) + mq) * LVR +
+          mi;
+      for (int s0 = 0; s0 < ns; s0 += 4) {
+        T a[4];
+        double b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int k = ib + 4 * (s0 + u);
-          const bool ok = k >= 0 && k < g.len;
-          const T v = Ev[ok ? g.off + k : 0];
-          a[u] = ok ? -(double)v : 0.0;
-          // rows outside the wavefront's longest segment count as zero (a zero
-          // coefficient would turn their infinities into NaN)
-          const int d = 4 * (s0 + u) + mq;
-          const double x = Rg[((vb + 4 * (s0 + u)) & (RING - 1)) * LVR + mi];
-          b[u] = (FWD ? d >= 4 * ns - ltop : d < ltop) ? x : 0.0;
+          a[u] = ea[4 * (s0 + u)];
+          b[u] = rp[4 * (s0 + u) * LVR];
         }
-      };
-      auto mul = [&](int s0, const double(&a)[4], const double(&b)[4]) __attribute__((always_inline)) {
-        acc = mfma16x16x4(a[0], b[0], acc);
-        if (s0 + 1 < ns) acc = mfma16x16x4(a[1], b[1], acc);
+        if (s0 == 0 && mq < pad) b[0] = 0.0;
+        auto step = [&](int u) __attribute__((always_inline)) {
+          const T v = (unsigned)(kb + 4 * (s0 + u)) < (unsigned)g.len ? a[u] : T(0);
+          acc = mfma16x16x4((double)v, b[u], acc);
+        };
+        step(0);
+        if (s0 + 1 < ns) step(1);
         if (s0 + 2 < ns) {
-          acc = mfma16x16x4(a[2], b[2], acc);
-          acc = mfma16x16x4(a[3], b[3], acc);
+          step(2);
+          step(3);
         }
-      };
-      double a0[4], b0[4], a1[4], b1[4];
-      fetch(0, a0, b0);
-      for (int s0 = 0;; s0 += 8) {
-        fetch(s0 + 4, a1, b1);
-        mul(s0, a0, b0);
-        if (s0 + 4 >= ns) break;
-        fetch(s0 + 8, a0, b0);
-        mul(s0 + 4, a1, b1);
-        if (s0 + 8 >= ns) break;
       }
-    } else {  // long segments or many entries: from global memory
+    } else {
+      // longer segments: rows from the whole ring or from memory; many
+      // entries: those from memory
+      const bool staged = g.total <= EVC, in_ring = ltop <= RING;
       for (int s = 0; s < ns; ++s) {
-        const int k = ib + 4 * s;
+        const int k = kb + 4 * s, row = vb + 4 * s;
         const bool ok = k >= 0 && k < g.len;
-        const T v = src[g.base + (ok ? g.off + k : 0)];
-        const int d = 4 * s + mq;
-        double x = io.row(min(max(vb + 4 * s, 0), npad - 1));
-        x = (FWD ? d >= 4 * ns - ltop : d < ltop) ? x : 0.0;
-        acc = mfma16x16x4(ok ? -(double)v : 0.0, x, acc);
+        T v;
+        if (staged)
+          v = Ev[ok ? g.off + k : 0];
+        else
+          v = src[g.base + (ok ? g.off + k : 0)];
+        double x;
+        if (in_ring)
+          x = Rg[(row & (RING - 1)) * LVR + mi];
+        else
+          x = io.row(min(max(row, 0), npad - 1));
+        acc = mfma16x16x4(ok ? (double)v : 0.0, s == 0 && mq < pad ? 0.0 : x, acc);
       }
     }
   };
@@ -180,20 +193,23 @@ __device__ __forceinline__ void env_solve(const Plan &p, int i, const T *__restr
       typename IO::Aux aux;
     } b[PF];
     auto row0 = [&](int I) { return (FWD ? I : nt - 1 - I) * TS; };
-    // forward: row 16w + mi, columns 16g + 4q + u for the groups g <= w;
-    // backward: column 16w + mi, rows 16g + 4q + u for the groups g >= w
-    // (entries outside the triangle lie inside the packed tile and are
-    // dropped where they are used)
+    // forward: row 16w + mi, columns 16g + 4q + u; backward: column 16w + mi,
+    // rows 16g + 4q + u.  Part m = 0: the diagonal group g = w (entries outside
+    // the triangle lie inside the packed tile and are dropped where they are
+    // used); parts 1 .. 3: the whole groups, g = m - 1 < w forward, g = m > w
+    // backward.
+    auto group = [&](int m) { return m == 0 ? w : FWD ? m - 1 : m; };
+    auto whole = [&](int m) { return FWD ? m - 1 < w : m > w; };
     auto load_d = [&](int I, T (&dA)[16]) {
       const T *tile = dpool + (size_t)(FWD ? I : nt - 1 - I) * DE;
       const T *row = FWD ? tile + dpos_row(16 * w + mi) + 4 * mq : tile + 16 * w + mi;
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        if (FWD ? g <= w : g >= w) {
-          const int k4 = 4 * g + mq;  // backward: row / 4
+      for (int m = 0; m < 4; ++m)
+        if (m == 0 || whole(m)) {
+          const int g = group(m), k4 = 4 * g + mq;  // backward: row / 4
 #pragma unroll
           for (int u = 0; u < 4; ++u)
-            dA[4 * g + u] = FWD ? row[16 * g + u] : row[4 * (k4 + 1) * (2 * k4 + u)];
+            dA[4 * m + u] = FWD ? row[16 * g + u] : row[4 * (k4 + 1) * (2 * k4 + u)];
         }
     };
 #pragma unroll
@@ -219,14 +235,15 @@ __device__ __forceinline__ void env_solve(const Plan &p, int i, const T *__restr
           const Seg g = c.g;
           ev_write(c.ev);
           __syncthreads();  // Ev and the ring complete; the last block's Acc reads done
-          d4 acc = c.x;
+          const d4 x = c.x;
           c.g = seg_of(c.raw);
           ev_load(env, c.g, c.ev);
           io.load(fwd, row0(In), c.idx, c.x);
           c.raw = seg_load(ptr, row0(min(I + 2 * PF, nt - 1)));
           c.idx = io.idx(fwd, row0(min(I + 2 * PF, nt - 1)));
+          d4 acc = {0.0, 0.0, 0.0, 0.0};
           env_part(fwd, env, g, row0(I), acc);
-          acc_write(acc);
+          acc_write(x - acc);
           __syncthreads();  // Acc complete; Ev and the ring free
           d4 y = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -234,16 +251,17 @@ __device__ __forceinline__ void env_solve(const Plan &p, int i, const T *__restr
             double bd[8];  // two groups' reads, issued (and waited for) together
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-              bd[e] = Acc[(32 * h + 16 * (e >> 2) + 4 * mq + (e & 3)) * LVA + mi];
+              bd[e] = Acc[(16 * group(2 * h + (e >> 2)) + 4 * mq + (e & 3)) * LVA + mi];
 #pragma unroll
             for (int e = 0; e < 8; ++e) __asm__ volatile("" : "+v"(bd[e]));
 #pragma unroll
-            for (int gr = 2 * h; gr < 2 * h + 2; ++gr)
-              if (FWD ? gr <= w : gr >= w) {
+            for (int m = 2 * h; m < 2 * h + 2; ++m)
+              if (m == 0 || whole(m)) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                  const bool in = gr != w || (FWD ? 4 * mq + u <= mi : mi <= 4 * mq + u);
-                  y = mfma16x16x4(in ? (double)c.dA[4 * gr + u] : 0.0, bd[4 * (gr & 1) + u], y);
+                  T a = c.dA[4 * m + u];
+                  if (m == 0) a = (FWD ? 4 * mq + u <= mi : mi <= 4 * mq + u) ? a : T(0);
+                  y = mfma16x16x4((double)a, bd[4 * (m & 1) + u], y);
                 }
               }
           }
