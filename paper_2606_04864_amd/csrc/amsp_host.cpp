@@ -1470,10 +1470,8 @@ static BlockWs block_ws_from(const amsp_handle *h, double *base) {
   return w;
 }
 
-static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, int nr, int parts,
-                                  const BlockWs &ws);
-
-static amsp_status apply_block(amsp_handle *h, const double *r, double *z, int nr, int parts) {
+// The handle's own workspace, for up to EIGP columns.
+static amsp_status block_ws(amsp_handle *h, BlockWs &ws) {
   const size_t rows = (size_t)h->hp.vp_ptr.back();
   const size_t ncp = (size_t)std::max(1, h->T0 * TS);
   if (!h->bX) {
@@ -1487,14 +1485,23 @@ static amsp_status apply_block(amsp_handle *h, const double *r, double *z, int n
           h->tree ? 1 : std::max<size_t>((size_t)h->T0 * h->T0, 1) * TS * EIGP);
     launch_fill(h->stream, ncp * EIGP, h->bC, 0.0);  // coarse padding stays zero
   }
-  const BlockWs ws{h->bX, h->bY, h->bXN, h->bC, h->bT, h->bC2, h->bPart, false};
-  return apply_block_ws(h, r, z, nr, parts, ws);
+  ws = BlockWs{h->bX, h->bY, h->bXN, h->bC, h->bT, h->bC2, h->bPart, false};
+  return AMSP_OK;
 }
 
 static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, int nr, int parts,
-                                  const BlockWs &ws) {
+                                  const BlockWs &ws);
+
+static amsp_status apply_block(amsp_handle *h, const double *r, double *z, int nr, int parts) {
+  BlockWs ws;
+  const amsp_status st = block_ws(h, ws);
+  return st != AMSP_OK ? st : apply_block_ws(h, r, z, nr, parts, ws);
+}
+
+// The regions' outputs ws.XN (local solves and prolongation, as parts asks) for
+// the rows in ws.X; parts must ask for something that exists.
+static amsp_status apply_rows(amsp_handle *h, int nr, int parts, const BlockWs &ws) {
   const Plan &p = h->plan;
-  const int n = h->n;
   hipStream_t s = h->stream;
   const bool mixed = h->opt.precision != AMSP_FP64;
   const bool bf = h->opt.precision == AMSP_MIXED_BF16;
@@ -1511,7 +1518,6 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
     ALLOC(h->ec32, float, nenv + 1);
     launch_streams_to_env(s, p, h->ntilerows, h->fst32, h->bst32, h->dg32, h->er32, h->ec32);
   }
-  launch_cols_to_rows(s, n, (size_t)n, nr, r, bX);
   const void *phi = mixed ? h->phi_lo : (const void *)h->phi64;
   if (do_coarse) {
     if (!mixed)
@@ -1550,12 +1556,24 @@ static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, in
       launch_prolong_rows<float>(s, p, nr, (const float *)phi, t, bXN);
     else
       launch_prolong_rows<__hip_bfloat16>(s, p, nr, (const __hip_bfloat16 *)phi, t, bXN);
-  } else {  // coarse part asked for, but no coarse space
+  }
+  HIP_TRY(hipGetLastError());
+  return AMSP_OK;
+}
+
+static amsp_status apply_block_ws(amsp_handle *h, const double *r, double *z, int nr, int parts,
+                                  const BlockWs &ws) {
+  const int n = h->n;
+  hipStream_t s = h->stream;
+  if (!(parts & 1) && h->nc == 0) {  // coarse part asked for, but no coarse space
     launch_fill(s, (size_t)n * nr, z, 0.0);
     HIP_TRY(hipGetLastError());
     return AMSP_OK;
   }
-  launch_scatter_cols(s, n, nr, h->inv_ptr, h->inv_x, bXN, z);
+  launch_cols_to_rows(s, n, (size_t)n, nr, r, ws.X);
+  const amsp_status st = apply_rows(h, nr, parts, ws);
+  if (st != AMSP_OK) return st;
+  launch_scatter_cols(s, n, nr, h->inv_ptr, h->inv_x, ws.XN, z);
   HIP_TRY(hipGetLastError());
   return AMSP_OK;
 }
@@ -1714,189 +1732,233 @@ static int64_t bytes_per_iter(const amsp_handle *h) {
   return b;
 }
 
-// PCG on nr <= EIGP columns at once: one CG recurrence per column (the same
-// steps and stopping rule as amsp_pcg), all sharing each SpMV (entries read
-// once) and each preconditioner application (the block path of amsp_apply).
-// Scalars go through the host twice per step.  Converged columns keep
-// alpha = beta = 0.  Adds to the totals in *inf; the history of the last
-// column is kept for amsp_get_pcg_history.
-static amsp_status pcg_columns(amsp_handle *h, const double *F, double *U, int nr, double rtol,
-                               int maxit, amsp_info &inf) {
-  const int n = h->n;
-  const size_t ld = (size_t)n, tot = ld * nr;
+// One CG recurrence per (problem, column) for nr <= EIGP columns of the
+// problems on rows [ptr[s], ptr[s+1]), all sharing each matrix product and each
+// preconditioner application (k_batch.hip).  As in amsp_pcg: stop on the
+// recursive residuals, recompute f - A u, and restart the recurrences whose
+// true residual is above max(rtol, floor) from it (at most 3 times).  Scalars
+// stay on the device: behind every step the count of active recurrences is
+// copied to a pinned slot and read while the next step runs; once none is
+// active the step already enqueued changes nothing (all its coefficients are
+// zero).  A recurrence that breaks down stops; the others run to their end.
+struct RowsResult {  // per recurrence s * nr + k
+  std::vector<double> f2, rec, rt, fl;  // |f|^2, recursive and true residuals, floors
+  std::vector<int> its, broken;
+  int steps = 0;
+};
+
+// all_floors: the floors of every recurrence, not only where the true residual
+// is above rtol; hist: receives the last recurrence's r.r after every step.
+static amsp_status pcg_rows(amsp_handle *h, const std::vector<long long> &ptr, const double *F,
+                            double *U, int nr, double rtol, int maxit, bool all_floors,
+                            double *hist, int hist_cap, RowsResult &o) {
+  const int n = h->n, nseg = (int)ptr.size() - 1, W = row_width(nr), nrec = nseg * W;
+  const size_t ld = (size_t)n, tot = ld * W;
   hipStream_t s = h->stream;
-  double *R = nullptr, *Z = nullptr, *Pd = nullptr, *Q = nullptr, *part = nullptr, *sc = nullptr;
-  ALLOC(R, double, tot);
-  ALLOC(Z, double, tot);
-  ALLOC(Pd, double, tot);
-  ALLOC(Q, double, tot);
-  ALLOC(part, double, (size_t)256 * EIGP);
-  ALLOC(sc, double, 4 * EIGP);  // [0,16) alpha/beta, [16,32) dots, [32,48) rr
-  auto release = [&]() {
-    for (double *b : {R, Z, Pd, Q, part, sc}) h->mem.free_one(b);
-  };
-  auto to_host = [&](const double *src, double *dst) -> hipError_t {
-    hipError_t e = hipMemcpyAsync(dst, src, nr * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    return e;
-  };
-  std::vector<double> f2(nr), rr(nr);
-  std::vector<int> active(nr), its(nr, 0);
-  std::vector<double> hist;
-  launch_fill(s, tot, U, 0.0);
-  HIP_TRY(hipMemcpyAsync(R, F, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
-  launch_col_dots(s, n, ld, nr, F, F, part, sc + 16);
-  HIP_TRY(to_host(sc + 16, f2.data()));
-  for (int k = 0; k < nr; ++k) {
-    if (!std::isfinite(f2[k])) {
-      release();
-      h->err = "right-hand side not finite";
-      return AMSP_ERR_BREAKDOWN;
+  // row blocks of at most CH rows inside each problem
+  constexpr long long CH = 512;
+  std::vector<long long> brow{0};
+  std::vector<int> bseg, sblk{0};
+  for (int q = 0; q < nseg; ++q) {
+    for (long long r = ptr[q]; r < ptr[q + 1]; r += CH) {
+      bseg.push_back(q);
+      brow.push_back(std::min<long long>(r + CH, ptr[q + 1]));
     }
-    rr[k] = f2[k];
-    active[k] = f2[k] > 0.0;
+    sblk.push_back((int)bseg.size());
   }
-  hist.push_back(f2[nr - 1]);
-  int broken = 0;  // bit k: column k broke down
-  int it = 0;
-  auto any_active = [&]() {
-    for (int v : active)
-      if (v) return true;
-    return false;
+  const int nblk = (int)bseg.size();
+  BlockWs ws;
+  amsp_status st = block_ws(h, ws);
+  if (st != AMSP_OK) return st;
+  bool ok = true;
+  RowBlocks rb{nblk, nseg, upload(h, brow, ok), upload(h, bseg, ok), upload(h, sblk, ok)};
+  double *Z = h->mem.alloc<double>(tot), *P0 = h->mem.alloc<double>(tot),
+         *P1 = h->mem.alloc<double>(tot), *Q = h->mem.alloc<double>(tot);
+  double *part = h->mem.alloc<double>((size_t)2 * nblk * W), *part_rr = part + (size_t)nblk * W;
+  double *sc = h->mem.alloc<double>((size_t)5 * nrec);  // alpha or beta, sums; rz, f2, rr
+  int *si = h->mem.alloc<int>((size_t)3 * nrec + 1);
+  auto release = [&]() {
+    for (const void *b : {(const void *)rb.brow, (const void *)rb.bseg, (const void *)rb.sblk,
+                          (const void *)Z, (const void *)P0, (const void *)P1, (const void *)Q,
+                          (const void *)part, (const void *)sc, (const void *)si})
+      if (b) h->mem.free_one(const_cast<void *>(b));
   };
-  std::vector<double> rt(nr, 0.0), fl(nr, 0.0), rec(nr, 0.0);
-  const int nb = reduce_blocks(n);
-  amsp_status st = AMSP_OK;
-  // as in amsp_pcg: stop on the recursive residuals, recompute f - A u, and
-  // restart the columns whose true residual is above max(rtol, floor) from
-  // it (at most 3 times)
-  // The per-column scalars stay on the device (ColCgState).  Behind every
-  // step the state is copied to a pinned slot, and the host reads step t's
-  // copy while step t + 1 runs; once no column is active the step already
-  // enqueued changes nothing (all its coefficients are zero).
-  ColCgState *cs = nullptr, *cs_host = nullptr;
-  ALLOC(cs, ColCgState, 1);
-  HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&cs_host), 2 * sizeof(ColCgState),
-                        hipHostMallocDefault));
-  hipEvent_t cev[2] = {nullptr, nullptr};
+  if (!ok || !Z || !P0 || !P1 || !Q || !part || !sc || !si) {
+    release();
+    h->err = "device allocation failed (several-column CG)";
+    return AMSP_ERR_OOM;
+  }
+  double *const R = ws.X;  // the residual is the preconditioner's input
+  double *const coef = sc, *const sums = sc + nrec;
+  const RowCgState cg{sc + 2 * nrec, sc + 3 * nrec, sc + 4 * nrec, si, si + nrec, si + 2 * nrec,
+                      si + 3 * nrec, hist, hist_cap};
+  std::vector<double> hd(nrec);
+  std::vector<int> hi(nrec);
+  auto dev_to_host = [&](const double *src) -> hipError_t {  // nrec values into hd
+    hipError_t e = hipMemcpyAsync(hd.data(), src, nrec * sizeof(double), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  };
+  // f(index s * nr + k, index s * W + k) for every recurrence
+  auto each = [&](auto &&f) {
+    for (int q = 0; q < nseg; ++q)
+      for (int k = 0; k < nr; ++k) f(q * nr + k, q * W + k);
+  };
+  const int cnt = nseg * nr;
+  o.f2.assign(cnt, 0.0);
+  o.rec.assign(cnt, 0.0);
+  o.rt.assign(cnt, 0.0);
+  o.fl.assign(cnt, 0.0);
+  o.its.assign(cnt, 0);
+  o.broken.assign(cnt, 0);
+  std::vector<double> rr(nrec, 0.0);
+  std::vector<int> active(nrec, 0);
+  launch_fill(s, ld * nr, U, 0.0);
+  launch_cols_to_rows(s, n, ld, nr, F, R);
+  launch_rows_norm(s, rb, nr, R, part);
+  launch_rows_sum(s, rb, nr, part, sums);
+  HIP_TRY(dev_to_host(sums));
+  stage_release(h);
+  bool finite = true;
+  each([&](int r, int d) {
+    o.f2[r] = rr[d] = hd[d];
+    finite = finite && std::isfinite(hd[d]);
+    active[d] = hd[d] > 0.0;
+  });
+  if (!finite) {
+    release();
+    h->err = "right-hand side not finite";
+    return AMSP_ERR_BREAKDOWN;
+  }
+  if (hist) HIP_TRY(hipMemcpyAsync(hist, &o.f2[cnt - 1], sizeof(double), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemcpyAsync(cg.f2, hd.data(), nrec * sizeof(double), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemsetAsync(cg.its, 0, (2 * (size_t)nrec + 1) * sizeof(int), s));  // its, broken
+  HIP_TRY(hipStreamSynchronize(s));
+  int *n_host = nullptr;
+  HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&n_host), 2 * sizeof(int), hipHostMallocDefault));
+  hipEvent_t ev[2] = {nullptr, nullptr};
   struct Guard {
-    ColCgState *p;
+    int *p;
     hipEvent_t *e;
     ~Guard() {
       for (int k = 0; k < 2; ++k)
         if (e[k]) (void)hipEventDestroy(e[k]);
       if (p) (void)hipHostFree(p);
     }
-  } guard{cs_host, cev};
-  for (hipEvent_t &e : cev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  {
-    ColCgState init{};
-    for (int k = 0; k < nr; ++k) {
-      init.f2[k] = f2[k];
-      init.rr[k] = rr[k];
-    }
-    HIP_TRY(hipMemcpyAsync(cs, &init, sizeof(ColCgState), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
-  }
+  } guard{n_host, ev};
+  for (hipEvent_t &e : ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   const double rtol2 = rtol * rtol;
+  int it = 0;
+  // Z = M^{-1} R with the partials of r.z
+  auto precondition = [&]() -> amsp_status {
+    const amsp_status ps = apply_rows(h, nr, 3, ws);
+    if (ps == AMSP_OK)
+      launch_rows_scatter(s, rb, nr, h->inv_ptr, h->inv_x, ws.XN, R, Z, part);
+    return ps;
+  };
   for (int restarts = 0;; ++restarts) {
-    if ((st = apply_block(h, R, Z, nr, 3)) != AMSP_OK) return st;
-    launch_col_dots(s, n, ld, nr, R, Z, part, sc + 16);
-    HIP_TRY(hipMemcpyAsync(cs->rz, sc + 16, nr * sizeof(double), hipMemcpyDeviceToDevice, s));
-    {
-      int act[EIGP] = {0};
-      for (int k = 0; k < nr; ++k) act[k] = active[k];
-      HIP_TRY(hipMemcpyAsync(cs->active, act, sizeof(act), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(cg.active, active.data(), nrec * sizeof(int), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(cg.rr, rr.data(), nrec * sizeof(double), hipMemcpyHostToDevice, s));
+    if ((st = precondition()) != AMSP_OK) {
+      release();
+      return st;
     }
-    HIP_TRY(hipMemcpyAsync(Pd, Z, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
-    int pend = -1;  // slot of the state copy in flight
-    bool live = any_active();
+    launch_rows_sum(s, rb, nr, part, cg.rz);
+    bool live = false;
+    for (int v : active) live = live || v;
+    int pend = -1;  // slot of the count in flight
+    bool first = true;
     while (live && it < maxit) {
-      launch_spmm_sell(s, n, h->sptr, h->scol, h->sval, ld, nr, Pd, Q);
-      launch_col_dots(s, n, ld, nr, Pd, Q, part, sc + 16);
-      launch_col_alpha(s, nr, cs, sc + 16, sc);
-      launch_col_update(s, n, ld, nr, sc, Pd, Q, U, R, part, sc + 32);
-      if ((st = apply_block(h, R, Z, nr, 3)) != AMSP_OK) return st;
-      launch_col_dots(s, n, ld, nr, R, Z, part, sc + 16);
-      launch_col_beta(s, nr, cs, sc + 32, sc + 16, rtol2, sc);
-      launch_col_direction(s, n, ld, nr, sc, Z, Pd);
+      launch_rows_dir(s, rb, nr, h->sptr, h->scol, h->sval, coef, first ? 1 : 0, Z, P0, P1, Q, part);
+      launch_rows_alpha(s, rb, nr, cg, part, coef);
+      launch_rows_update(s, rb, nr, ld, coef, P1, Q, U, R, part_rr);
+      if ((st = precondition()) != AMSP_OK) {
+        release();
+        return st;
+      }
+      launch_rows_beta(s, rb, nr, cg, part_rr, part, rtol2, it + 1, coef);
+      std::swap(P0, P1);
+      first = false;
       const int slot = pend == 0 ? 1 : 0;
-      HIP_TRY(hipMemcpyAsync(cs_host + slot, cs, sizeof(ColCgState), hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipEventRecord(cev[slot], s));
+      HIP_TRY(hipMemcpyAsync(n_host + slot, cg.nactive, sizeof(int), hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipEventRecord(ev[slot], s));
       HIP_TRY(hipGetLastError());
       ++it;
-      if (pend >= 0) {  // the previous step's state, read while this step runs
-        HIP_TRY(hipEventSynchronize(cev[pend]));
-        hist.push_back(cs_host[pend].rr[nr - 1]);
-        if (cs_host[pend].nact == 0) {
-          --it;  // this step found no active column
-          pend = -1;
+      if (pend >= 0) {  // the previous step's count, read while this step runs
+        HIP_TRY(hipEventSynchronize(ev[pend]));
+        if (n_host[pend] == 0) {
+          --it;  // this step found no active recurrence
           break;
         }
       }
       pend = slot;
     }
-    if (pend >= 0) {  // the last step's state
-      HIP_TRY(hipEventSynchronize(cev[pend]));
-      hist.push_back(cs_host[pend].rr[nr - 1]);
-    }
     HIP_TRY(hipStreamSynchronize(s));
-    {
-      ColCgState fin{};
-      HIP_TRY(hipMemcpy(&fin, cs, sizeof(ColCgState), hipMemcpyDeviceToHost));
-      for (int k = 0; k < nr; ++k) {
-        rr[k] = fin.rr[k];
-        its[k] = fin.its[k];
-        active[k] = fin.active[k];
-      }
-      broken |= fin.breakdown;
+    HIP_TRY(dev_to_host(cg.rr));
+    each([&](int r, int d) { o.rec[r] = o.f2[r] > 0.0 ? std::sqrt(hd[d] / o.f2[r]) : 0.0; });
+    HIP_TRY(hipMemcpy(hi.data(), cg.its, nrec * sizeof(int), hipMemcpyDeviceToHost));
+    each([&](int r, int d) { o.its[r] = hi[d]; });
+    HIP_TRY(hipMemcpy(hi.data(), cg.broken, nrec * sizeof(int), hipMemcpyDeviceToHost));
+    each([&](int r, int d) { o.broken[r] = hi[d]; });
+    // true residuals (left in R) and their attainable floors
+    launch_cols_to_rows(s, n, ld, nr, U, Z);
+    launch_rows_dir(s, rb, nr, h->sptr, h->scol, h->sval, coef, 1, Z, Z, P1, Q, part);
+    launch_rows_residual(s, rb, nr, ld, F, Q, R, part);
+    launch_rows_sum(s, rb, nr, part, sums);
+    HIP_TRY(dev_to_host(sums));
+    bool floors = all_floors;
+    each([&](int r, int d) {
+      const double fk = std::sqrt(o.f2[r]);
+      rr[d] = hd[d];
+      o.rt[r] = fk > 0.0 ? std::sqrt(hd[d]) / fk : 0.0;
+      floors = floors || (o.rt[r] > rtol && o.fl[r] == 0.0);
+    });
+    if (floors) {
+      launch_rows_floor(s, rb, nr, h->rowptr, h->col, h->val, Z, part);
+      launch_rows_sum(s, rb, nr, part, sums);
+      HIP_TRY(dev_to_host(sums));
     }
-    for (int k = 0; k < nr; ++k) rec[k] = f2[k] > 0.0 ? std::sqrt(rr[k] / f2[k]) : 0.0;
-    // true residuals (left in R) and, where needed, the attainable floors
-    launch_spmm_sell(s, n, h->sptr, h->scol, h->sval, ld, nr, U, Q);
     bool again = false;
-    for (int k = 0; k < nr; ++k) {
-      const double fk = std::sqrt(f2[k]);
-      rt[k] = 0.0;
-      if (!(fk > 0.0)) continue;
-      launch_residual(s, n, F + k * ld, Q + k * ld, R + k * ld, part);
-      launch_sum_partials(s, part, nb, sc + 47);
-      double r2 = 0.0;
-      HIP_TRY(hipMemcpyAsync(&r2, sc + 47, sizeof(double), hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
-      rt[k] = std::sqrt(r2) / fk;
-      if (rt[k] > rtol && fl[k] == 0.0) {
-        launch_abs_spmv_sq(s, n, h->rowptr, h->col, h->val, U + k * ld, part);
-        launch_sum_partials(s, part, nb, sc + 47);
-        double a2 = 0.0;
-        HIP_TRY(hipMemcpyAsync(&a2, sc + 47, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        fl[k] = DBL_EPSILON * std::sqrt(a2) / fk;
-      }
-      rr[k] = r2;
-      const bool ok = rt[k] <= std::max(rtol, fl[k]);
-      // a column that broke down stops; the others restart as usual
-      active[k] = !ok && std::isfinite(rt[k]) && restarts < 3 && it < maxit && !(broken >> k & 1);
-      again = again || active[k];
-    }
+    each([&](int r, int d) {
+      const double fk = std::sqrt(o.f2[r]);
+      if (all_floors || (o.rt[r] > rtol && o.fl[r] == 0.0))
+        o.fl[r] = fk > 0.0 ? DBL_EPSILON * std::sqrt(hd[d]) / fk : 0.0;
+      const bool okr = !(fk > 0.0) || o.rt[r] <= std::max(rtol, o.fl[r]);
+      active[d] = !okr && std::isfinite(o.rt[r]) && restarts < 3 && it < maxit && !o.broken[r];
+      again = again || active[d];
+    });
     if (!again) break;
   }
-  for (int k = 0; k < nr; ++k) {
-    const bool conv = rt[k] <= std::max(rtol, fl[k]) && std::isfinite(rt[k]);
-    if (!conv) inf.converged = 0;
-    inf.iterations += its[k];
-    inf.first_segment += its[k];  // the block path does not split its segments
-    inf.relres_true = std::max(inf.relres_true, rt[k]);
-    inf.relres_recursive = std::max(inf.relres_recursive, rec[k]);
-    inf.relres_floor = std::max(inf.relres_floor, fl[k]);
-  }
-  h->hist_len = std::min((int)hist.size(), h->hist_cap);
-  h->hist_f2 = f2[nr - 1];
-  HIP_TRY(hipMemcpyAsync(h->hist, hist.data(), h->hist_len * sizeof(double), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  o.steps = it;
   release();
-  h->mem.free_one(cs);
-  if (broken) {
+  return AMSP_OK;
+}
+
+// Adds a several-column solve's totals to inf; true if a recurrence broke down.
+static bool add_rows_result(const RowsResult &o, double rtol, amsp_info &inf) {
+  bool broke = false;
+  for (size_t r = 0; r < o.rt.size(); ++r) {
+    if (!(o.rt[r] <= std::max(rtol, o.fl[r]) && std::isfinite(o.rt[r]))) inf.converged = 0;
+    inf.iterations += o.its[r];
+    inf.first_segment += o.its[r];  // the block path does not split its segments
+    inf.relres_true = std::max(inf.relres_true, o.rt[r]);
+    inf.relres_recursive = std::max(inf.relres_recursive, o.rec[r]);
+    inf.relres_floor = std::max(inf.relres_floor, o.fl[r]);
+    broke = broke || o.broken[r];
+  }
+  return broke;
+}
+
+// PCG on nr <= EIGP columns at once (one problem).  Adds to the totals in *inf;
+// the history of the last column is kept for amsp_get_pcg_history.
+static amsp_status pcg_columns(amsp_handle *h, const double *F, double *U, int nr, double rtol,
+                               int maxit, amsp_info &inf) {
+  RowsResult o;
+  const amsp_status st =
+      pcg_rows(h, {0, h->n}, F, U, nr, rtol, maxit, false, h->hist, h->hist_cap, o);
+  if (st != AMSP_OK) return st;
+  h->hist_len = std::min(o.steps + 1, h->hist_cap);
+  h->hist_f2 = o.f2[nr - 1];
+  if (add_rows_result(o, rtol, inf)) {
     h->err = "CG breakdown in a column (p.Ap <= 0 or a non-finite value)";
     return AMSP_ERR_BREAKDOWN;
   }
@@ -2154,195 +2216,44 @@ extern "C" amsp_status amsp_pcg_batched(amsp_handle *h, int32_t nprob, const int
       return AMSP_ERR_ARG;
     }
   const double t0 = now_ms();
-  const int n = h->n, nseg = nprob, nr = nrhs, nrec = nseg * nr;
-  const size_t ld = (size_t)n, tot = ld * nr;
-  hipStream_t s = h->stream;
-  // row blocks of at most CH rows inside each problem
-  constexpr long long CH = 2048;
-  std::vector<long long> brow{0};
-  std::vector<int> bseg, sblk{0};
-  for (int q = 0; q < nseg; ++q) {
-    for (long long r = prob_ptr[q]; r < prob_ptr[q + 1]; r += CH) {
-      bseg.push_back(q);
-      brow.push_back(std::min<long long>(r + CH, prob_ptr[q + 1]));
-    }
-    sblk.push_back((int)bseg.size());
-  }
-  const int nblk = (int)bseg.size();
-  bool ok = true;
-  const long long *d_brow = upload(h, brow, ok);
-  const int *d_bseg = upload(h, bseg, ok);
-  const int *d_sblk = upload(h, sblk, ok);
-  std::vector<long long> sp(prob_ptr, prob_ptr + nprob + 1);
-  const long long *d_sptr = upload(h, sp, ok);
-  double *R = h->mem.alloc<double>(tot), *Z = h->mem.alloc<double>(tot),
-         *Pd = h->mem.alloc<double>(tot), *Q = h->mem.alloc<double>(tot);
-  double *part = h->mem.alloc<double>((size_t)nblk * nr);
-  double *sc = h->mem.alloc<double>((size_t)5 * nrec);  // alpha/beta, dots, rr, r2, a2
-  double *st_rz = h->mem.alloc<double>(nrec), *st_f2 = h->mem.alloc<double>(nrec),
-         *st_rr = h->mem.alloc<double>(nrec);
-  int *st_act = h->mem.alloc<int>(nrec), *st_its = h->mem.alloc<int>((size_t)2 * nrec),
-      *flags = h->mem.alloc<int>(2);
-  auto release = [&]() {
-    for (const void *b : {(const void *)d_brow, (const void *)d_bseg, (const void *)d_sblk,
-                          (const void *)d_sptr, (const void *)R, (const void *)Z,
-                          (const void *)Pd, (const void *)Q, (const void *)part, (const void *)sc,
-                          (const void *)st_rz, (const void *)st_f2, (const void *)st_rr,
-                          (const void *)st_act, (const void *)st_its, (const void *)flags})
-      if (b) h->mem.free_one(const_cast<void *>(b));
-  };
-  if (!ok || !R || !Z || !Pd || !Q || !part || !sc || !st_rz || !st_f2 || !st_rr || !st_act ||
-      !st_its || !flags) {
-    release();
-    h->err = "amsp_pcg_batched: device allocation failed";
-    return AMSP_ERR_OOM;
-  }
-  double *alpha = sc, *dots = sc + nrec, *rrn = sc + 2 * nrec, *r2d = sc + 3 * nrec,
-         *a2d = sc + 4 * nrec;
-  // the problems must not be coupled
-  {
-    HIP_TRY(hipMemsetAsync(flags, 0, 2 * sizeof(int), s));
-    launch_check_blocks(s, n, h->rowptr, h->col, nseg, d_sptr, flags);
-    int fl = 0;
-    HIP_TRY(hipMemcpyAsync(&fl, flags, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (fl) {
+  const std::vector<long long> ptr(prob_ptr, prob_ptr + nprob + 1);
+  {  // the problems must not be coupled
+    bool ok = true;
+    const long long *d_ptr = upload(h, ptr, ok);
+    int *flag = h->mem.alloc<int>(1);
+    auto release = [&]() {
+      for (const void *b : {(const void *)d_ptr, (const void *)flag})
+        if (b) h->mem.free_one(const_cast<void *>(b));
+    };
+    if (!ok || !d_ptr || !flag) {
       release();
+      h->err = "amsp_pcg_batched: device allocation failed";
+      return AMSP_ERR_OOM;
+    }
+    int fl = 0;
+    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int), h->stream));
+    launch_check_blocks(h->stream, h->n, h->rowptr, h->col, nprob, d_ptr, flag);
+    HIP_TRY(hipMemcpyAsync(&fl, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    release();
+    if (fl) {
       h->err = "amsp_pcg_batched: a stored entry couples two problems";
       return AMSP_ERR_ARG;
     }
   }
-  auto rec_to_host = [&](const double *src, std::vector<double> &dst) -> hipError_t {
-    dst.resize(nrec);
-    hipError_t e = hipMemcpyAsync(dst.data(), src, nrec * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    return e;
-  };
-  std::vector<double> f2, rr(nrec), rt(nrec, 0.0), fl(nrec, 0.0), rec(nrec, 0.0);
-  std::vector<int> active(nrec), its(nrec, 0), broken(nrec, 0);
-  launch_fill(s, tot, u_dev, 0.0);
-  HIP_TRY(hipMemcpyAsync(R, f_dev, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
-  launch_seg_dots(s, nblk, nseg, d_brow, d_sblk, ld, nr, f_dev, f_dev, part, dots);
-  HIP_TRY(rec_to_host(dots, f2));
-  for (int r = 0; r < nrec; ++r) {
-    if (!std::isfinite(f2[r])) {
-      release();
-      h->err = "right-hand side not finite";
-      return AMSP_ERR_BREAKDOWN;
-    }
-    rr[r] = f2[r];
-    active[r] = f2[r] > 0.0;
-  }
-  HIP_TRY(hipMemcpyAsync(st_f2, f2.data(), nrec * sizeof(double), hipMemcpyHostToDevice, s));
-  int *st_brk = st_its + nrec;  // per recurrence: broke down
-  HIP_TRY(hipMemsetAsync(st_its, 0, 2 * nrec * sizeof(int), s));
-  HIP_TRY(hipMemsetAsync(flags, 0, 2 * sizeof(int), s));
-  int *fl_host = nullptr;
-  HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&fl_host), 4 * sizeof(int), hipHostMallocDefault));
-  hipEvent_t fev[2] = {nullptr, nullptr};
-  struct Guard {
-    int *p;
-    hipEvent_t *e;
-    ~Guard() {
-      for (int k = 0; k < 2; ++k)
-        if (e[k]) (void)hipEventDestroy(e[k]);
-      if (p) (void)hipHostFree(p);
-    }
-  } guard{fl_host, fev};
-  for (hipEvent_t &e : fev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  const double rtol2 = rtol * rtol;
-  int it = 0;
-  bool breakdown = false;
-  amsp_status st = AMSP_OK;
-  for (int restarts = 0;; ++restarts) {
-    HIP_TRY(hipMemcpyAsync(st_act, active.data(), nrec * sizeof(int), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(st_rr, rr.data(), nrec * sizeof(double), hipMemcpyHostToDevice, s));
-    if ((st = apply_block(h, R, Z, nr, 3)) != AMSP_OK) {
-      release();
-      return st;
-    }
-    launch_seg_dots(s, nblk, nseg, d_brow, d_sblk, ld, nr, R, Z, part, st_rz);
-    HIP_TRY(hipMemcpyAsync(Pd, Z, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
-    bool live = false;
-    for (int v : active) live = live || v;
-    int pend = -1;
-    while (live && it < maxit) {
-      launch_spmm_sell(s, n, h->sptr, h->scol, h->sval, ld, nr, Pd, Q);
-      launch_seg_dots(s, nblk, nseg, d_brow, d_sblk, ld, nr, Pd, Q, part, dots);
-      launch_seg_alpha(s, nrec, st_rz, st_f2, st_rr, st_act, st_its, st_brk, flags, dots, alpha);
-      launch_seg_update(s, nblk, nseg, d_brow, d_bseg, d_sblk, ld, nr, alpha, Pd, Q, u_dev, R,
-                        part, rrn);
-      if ((st = apply_block(h, R, Z, nr, 3)) != AMSP_OK) {
-        release();
-        return st;
-      }
-      launch_seg_dots(s, nblk, nseg, d_brow, d_sblk, ld, nr, R, Z, part, dots);
-      launch_seg_beta(s, nrec, st_rz, st_f2, st_rr, st_act, st_its, st_brk, flags, rrn, dots, rtol2,
-                      alpha);
-      launch_seg_direction(s, nblk, nseg, d_brow, d_bseg, ld, nr, alpha, Z, Pd);
-      const int slot = pend == 0 ? 1 : 0;
-      HIP_TRY(hipMemcpyAsync(fl_host + 2 * slot, flags, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipEventRecord(fev[slot], s));
-      HIP_TRY(hipGetLastError());
-      ++it;
-      if (pend >= 0) {  // the previous step's flags, read while this step runs
-        HIP_TRY(hipEventSynchronize(fev[pend]));
-        if (fl_host[2 * pend + 1] == 0) {
-          --it;  // this step found no active recurrence (its coefficients are zero)
-          pend = -1;
-          break;
-        }
-      }
-      pend = slot;
-    }
-    HIP_TRY(hipStreamSynchronize(s));
-    std::vector<double> rrv;
-    HIP_TRY(rec_to_host(st_rr, rrv));
-    HIP_TRY(hipMemcpy(its.data(), st_its, nrec * sizeof(int), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(broken.data(), st_brk, nrec * sizeof(int), hipMemcpyDeviceToHost));
-    for (int v : broken) breakdown = breakdown || v != 0;
-    for (int r = 0; r < nrec; ++r) rec[r] = f2[r] > 0.0 ? std::sqrt(rrv[r] / f2[r]) : 0.0;
-    // true residuals R = F - A U and their attainable floors, per recurrence
-    launch_spmm_sell(s, n, h->sptr, h->scol, h->sval, ld, nr, u_dev, Q);
-    launch_sub_columns(s, tot, f_dev, Q, R);
-    launch_seg_dots(s, nblk, nseg, d_brow, d_sblk, ld, nr, R, R, part, r2d);
-    for (int k = 0; k < nr; ++k)
-      launch_abs_spmv_rows(s, n, h->rowptr, h->col, h->val, u_dev + k * ld, Q + k * ld);
-    launch_seg_dots(s, nblk, nseg, d_brow, d_sblk, ld, nr, Q, Q, part, a2d);
-    std::vector<double> r2, a2;
-    HIP_TRY(rec_to_host(r2d, r2));
-    HIP_TRY(rec_to_host(a2d, a2));
-    bool again = false;
-    for (int r = 0; r < nrec; ++r) {
-      const double fk = std::sqrt(f2[r]);
-      rt[r] = fk > 0.0 ? std::sqrt(r2[r]) / fk : 0.0;
-      fl[r] = fk > 0.0 ? DBL_EPSILON * std::sqrt(a2[r]) / fk : 0.0;
-      rr[r] = r2[r];
-      const bool okr = !(fk > 0.0) || rt[r] <= std::max(rtol, fl[r]);
-      // a broken recurrence stops; the others restart as usual
-      active[r] = !okr && std::isfinite(rt[r]) && restarts < 3 && it < maxit && !broken[r];
-      again = again || active[r];
-    }
-    if (!again) break;
-  }
+  RowsResult o;
+  const amsp_status st =
+      pcg_rows(h, ptr, f_dev, u_dev, nrhs, rtol, maxit, true, nullptr, 0, o);
+  if (st != AMSP_OK) return st;
   amsp_info inf{};
   inf.converged = 1;
-  for (int r = 0; r < nrec; ++r) {
-    const bool conv = (rt[r] <= std::max(rtol, fl[r]) || f2[r] == 0.0) && std::isfinite(rt[r]);
-    if (!conv) inf.converged = 0;
-    inf.iterations += its[r];
-    inf.first_segment += its[r];
-    inf.relres_true = std::max(inf.relres_true, rt[r]);
-    inf.relres_recursive = std::max(inf.relres_recursive, rec[r]);
-    inf.relres_floor = std::max(inf.relres_floor, fl[r]);
-    if (iterations) iterations[(size_t)(r % nseg) * nr + r / nseg] = its[r];
-    if (relres) relres[(size_t)(r % nseg) * nr + r / nseg] = rt[r];
+  const bool breakdown = add_rows_result(o, rtol, inf);
+  for (size_t r = 0; r < o.rt.size(); ++r) {
+    if (iterations) iterations[r] = o.its[r];
+    if (relres) relres[r] = o.rt[r];
   }
-  inf.restarts = 0;
   inf.solve_ms = now_ms() - t0;
-  inf.bytes_per_iter = 0;
   if (info) *info = inf;
-  release();
   if (breakdown) {
     h->err = "CG breakdown in a recurrence (p.Ap <= 0 or a non-finite value)";
     return AMSP_ERR_BREAKDOWN;

@@ -205,34 +205,6 @@ void launch_scatter_cols(hipStream_t s, int n, int nr, const int *inv_ptr, const
 template <typename T>
 void launch_trmm(hipStream_t s, const T *Wt, int T0, const double *x, int nr, double *part,
                  double *y, int transpose);
-// CG on nr columns ld apart, one recurrence per column: Y = A X (entries
-// read once for all columns); out[k] = A_k . B_k (part: 256 * nr doubles);
-// x_k += alpha_k p_k, r_k -= alpha_k q_k with rr[k] = r_k . r_k; p_k = z_k +
-// beta_k p_k.  alpha, beta, out and rr are device arrays of nr doubles.
-void launch_spmm_sell(hipStream_t s, int n, const long long *sptr, const int *scol,
-                      const double *sval, size_t ld, int nr, const double *X, double *Y);
-void launch_col_dots(hipStream_t s, int n, size_t ld, int nr, const double *A, const double *B,
-                     double *part, double *out);
-void launch_col_update(hipStream_t s, int n, size_t ld, int nr, const double *alpha,
-                       const double *P, const double *Q, double *X, double *R, double *part,
-                       double *rr);
-void launch_col_direction(hipStream_t s, int n, size_t ld, int nr, const double *beta,
-                          const double *Z, double *P);
-// Scalars of the per-column CG recurrences, kept on the device (nr <= EIGP).
-struct ColCgState {
-  double rz[EIGP], f2[EIGP], rr[EIGP];  // r.z, f.f and r.r (after the last update) per column
-  int active[EIGP], its[EIGP];
-  int breakdown, nact;  // bit k: column k broke down; columns still active
-};
-// alpha_k = (r.z)_k / (p.Ap)_k for active columns (0 otherwise); a column with
-// p.Ap <= 0 or a non-finite ratio stops and sets its breakdown bit.
-void launch_col_alpha(hipStream_t s, int nr, ColCgState *cs, const double *pq, double *alpha);
-// After the update: an active column with r.r <= rtol2 f.f stops (a
-// non-finite r.r stops it with breakdown); the others take beta_k =
-// (r.z)'_k / (r.z)_k and keep (r.z)'.  Copies rr into the state, counts the
-// active columns.
-void launch_col_beta(hipStream_t s, int nr, ColCgState *cs, const double *rr, const double *rz,
-                     double rtol2, double *beta);
 // f32 factor of the mixed forms from its streams back into packed diagonal
 // tiles + envelope (the layout of launch_env_solve_block)
 void launch_streams_to_env(hipStream_t s, const Plan &p, int ntilerows, const float *fst,
@@ -326,27 +298,40 @@ template <typename T>
 void launch_trmv(hipStream_t s, const T *Wt, int T0, const double *x, double *part, double *y,
                  int transpose, const int *done);
 
-// ------------------------------------ independent problems (k_batch.hip) ---
-// Recurrence r = k * nseg + s (column k, problem s); row blocks never cross
-// a problem boundary (rows of block b: [brow[b], brow[b+1]), problem bseg[b];
-// problem s owns blocks [sblk[s], sblk[s+1])).
-void launch_seg_dots(hipStream_t s, int nblk, int nseg, const long long *brow, const int *sblk,
-                     size_t ld, int nr, const double *A, const double *B, double *part,
-                     double *out);
-void launch_seg_update(hipStream_t s, int nblk, int nseg, const long long *brow, const int *bseg,
-                       const int *sblk, size_t ld, int nr, const double *alpha, const double *P,
-                       const double *Q, double *X, double *R, double *part, double *rr);
-void launch_seg_direction(hipStream_t s, int nblk, int nseg, const long long *brow,
-                          const int *bseg, size_t ld, int nr, const double *beta, const double *Z,
-                          double *P);
-void launch_seg_alpha(hipStream_t s, int nrec, double *rz, double *f2, double *rr, int *active,
-                      int *its, int *broken, int *flags, const double *pq, double *alpha);
-void launch_seg_beta(hipStream_t s, int nrec, double *rz, double *f2, double *rr, int *active,
-                     int *its, int *broken, int *flags, const double *rrn, const double *rzn,
-                     double rtol2, double *beta);
-void launch_abs_spmv_rows(hipStream_t s, int n, const int *rp, const int *col, const double *val,
-                          const double *u, double *w);
-void launch_sub_columns(hipStream_t s, size_t tot, const double *F, const double *Q, double *R);
+// ------------------- CG on several columns and problems (k_batch.hip) ---
+// Row blocks (never across a problem boundary) and the recurrences' scalars,
+// W = row_width(nr) per problem; part: nblk * W doubles.  See k_batch.hip.
+struct RowBlocks {
+  int nblk, nseg;
+  const long long *brow;    // [nblk + 1]
+  const int *bseg, *sblk;   // [nblk], [nseg + 1]
+};
+struct RowCgState {
+  double *rz, *f2, *rr;      // nseg * W each
+  int *active, *its, *broken;
+  int *nactive;              // active recurrences after the step
+  double *hist;              // r.r of the last recurrence per step; may be null
+  int hist_cap;
+};
+void launch_rows_norm(hipStream_t s, const RowBlocks &b, int nr, const double *R, double *part);
+void launch_rows_dir(hipStream_t s, const RowBlocks &b, int nr, const long long *sptr,
+                     const int *scol, const double *sval, const double *beta, int first,
+                     const double *z, const double *pold, double *pnew, double *q, double *part);
+void launch_rows_update(hipStream_t s, const RowBlocks &b, int nr, size_t ld, const double *alpha,
+                        const double *P, const double *Q, double *X, double *R, double *part);
+void launch_rows_scatter(hipStream_t s, const RowBlocks &b, int nr, const int *inv_ptr,
+                         const int *ix, const double *XN, const double *R, double *Z,
+                         double *part);
+void launch_rows_residual(hipStream_t s, const RowBlocks &b, int nr, size_t ld, const double *F,
+                          const double *Q, double *R, double *part);
+void launch_rows_floor(hipStream_t s, const RowBlocks &b, int nr, const int *rp, const int *col,
+                       const double *val, const double *U, double *part);
+void launch_rows_sum(hipStream_t s, const RowBlocks &b, int nr, const double *part, double *out);
+void launch_rows_alpha(hipStream_t s, const RowBlocks &b, int nr, const RowCgState &st,
+                       const double *part, double *alpha);
+void launch_rows_beta(hipStream_t s, const RowBlocks &b, int nr, const RowCgState &st,
+                      const double *part_rr, const double *part_rz, double rtol2, int it,
+                      double *beta);
 void launch_check_blocks(hipStream_t s, int n, const int *rp, const int *col, int nseg,
                          const long long *sptr, int *flag);
 

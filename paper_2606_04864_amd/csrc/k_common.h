@@ -436,4 +436,30 @@ __device__ __forceinline__ void acc_mma_ab(Acc4 &c, const double *X, int ldx, co
   }
 }
 
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+// Sum over the copies of row i (fixed map order) of the columns c, c + 1 of XN;
+// the first CU copies' index and value loads are issued together.
+template <int W>
+__device__ __forceinline__ d2 sum_copies(int i, int c, const int *__restrict__ inv_ptr,
+                                         const int *__restrict__ ix,
+                                         const double *__restrict__ XN) {
+  constexpr int CU = 4;
+  const int e0 = inv_ptr[i], e1 = inv_ptr[i + 1];
+  int src[CU];
+  d2 x[CU];
+#pragma unroll
+  for (int u = 0; u < CU; ++u) src[u] = ix[min(e0 + u, e1 - 1)];
+#pragma unroll
+  for (int u = 0; u < CU; ++u) x[u] = *reinterpret_cast<const d2 *>(XN + (size_t)src[u] * W + c);
+  d2 s = {0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < CU; ++u) {
+    const d2 a = s + x[u];
+    s = e0 + u < e1 ? a : s;
+  }
+  for (int e = e0 + CU; e < e1; ++e) s += *reinterpret_cast<const d2 *>(XN + (size_t)ix[e] * W + c);
+  return s;
+}
+
 }  // namespace amsp

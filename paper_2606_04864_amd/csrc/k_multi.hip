@@ -17,8 +17,6 @@
 
 namespace amsp {
 
-typedef double d2 __attribute__((ext_vector_type(2)));
-
 // f(std::integral_constant<int, W>) for the row width of nr columns
 template <typename F>
 static void with_width(int nr, F &&f) {
@@ -245,30 +243,6 @@ __global__ void __launch_bounds__(WG) k_prolong_rows(Plan p, const TB *__restric
   }
 }
 
-// Sum over the copies of row i (fixed map order) of the columns c, c + 1 of XN;
-// the first CU copies' index and value loads are issued together.
-template <int W>
-__device__ __forceinline__ d2 sum_copies(int i, int c, const int *__restrict__ inv_ptr,
-                                         const int *__restrict__ ix,
-                                         const double *__restrict__ XN) {
-  constexpr int CU = 4;
-  const int e0 = inv_ptr[i], e1 = inv_ptr[i + 1];
-  int src[CU];
-  d2 x[CU];
-#pragma unroll
-  for (int u = 0; u < CU; ++u) src[u] = ix[min(e0 + u, e1 - 1)];
-#pragma unroll
-  for (int u = 0; u < CU; ++u) x[u] = *reinterpret_cast<const d2 *>(XN + (size_t)src[u] * W + c);
-  d2 s = {0.0, 0.0};
-#pragma unroll
-  for (int u = 0; u < CU; ++u) {
-    const d2 a = s + x[u];
-    s = e0 + u < e1 ? a : s;
-  }
-  for (int e = e0 + CU; e < e1; ++e) s += *reinterpret_cast<const d2 *>(XN + (size_t)ix[e] * W + c);
-  return s;
-}
-
 // z_k[j] = sum over the copies of dof j of XN[copy][k], columns n apart:
 // W / 2 lanes per row, WG rows per workgroup, through LDS.
 template <int W>
@@ -377,117 +351,6 @@ __global__ void __launch_bounds__(WG) k_streams_to_env(Plan p, const float *__re
   }
 }
 
-// ------------------------------------------ CG on several columns at once ---
-// Independent CG recurrences, one per column, that share every operator
-// application.  Columns are ld apart; per-column scalars come from device
-// arrays (alpha, beta); converged columns carry alpha = beta = 0.
-
-// Y_k = A X_k for k < nr on the sliced copy of A: a row's entries are
-// loaded once and used for every column.
-__global__ void __launch_bounds__(WG) k_spmm_sell(int n, const long long *__restrict__ sptr,
-                                                  const int *__restrict__ scol,
-                                                  const double *__restrict__ sval, size_t ld,
-                                                  int nr, const double *__restrict__ X,
-                                                  double *__restrict__ Y) {
-  constexpr int JU = 8;
-  const int i = blockIdx.x * WG + threadIdx.x;
-  if (i >= n) return;
-  const int sl = i >> 6, lane = i & 63;
-  const long long base = sptr[sl];
-  const int wd = (int)((sptr[sl + 1] - base) >> 6);
-  int c[JU];
-  double v[JU];
-#pragma unroll
-  for (int j = 0; j < JU; ++j) {
-    const bool in = j < wd;
-    const long long e = base + (long long)j * 64 + lane;
-    c[j] = in ? scol[e] : i;
-    v[j] = in ? sval[e] : 0.0;
-  }
-  for (int k = 0; k < nr; ++k) {
-    const double *x = X + (size_t)k * ld;
-    // every slot's x is loaded (c[j] is a valid row for the slots past the
-    // slice width), and those slots are dropped by a select, so that the
-    // loads are in flight together
-    double xv[JU];
-#pragma unroll
-    for (int j = 0; j < JU; ++j) xv[j] = x[c[j]];
-    double s = 0.0;
-#pragma unroll
-    for (int j = 0; j < JU; ++j) {
-      const double t = fma(v[j], xv[j], s);
-      s = j < wd ? t : s;
-    }
-    for (int j = JU; j < wd; ++j) {
-      const long long e = base + (long long)j * 64 + lane;
-      s = fma(sval[e], x[scol[e]], s);
-    }
-    Y[(size_t)k * ld + i] = s;
-  }
-}
-
-// part[k * gridDim.x + b] = sum over rows of block-stride b of A_k . B_k
-__global__ void __launch_bounds__(WG) k_col_dots(int n, size_t ld, int nr,
-                                                 const double *__restrict__ A,
-                                                 const double *__restrict__ B,
-                                                 double *__restrict__ part) {
-  __shared__ double sh[WG / 64];
-  const int k = blockIdx.y;
-  if (k >= nr) return;  // uniform over the workgroup
-  const double *a = A + (size_t)k * ld, *b = B + (size_t)k * ld;
-  double acc = 0.0;
-  for (int i = blockIdx.x * WG + threadIdx.x; i < n; i += gridDim.x * WG) acc = fma(a[i], b[i], acc);
-  const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[(size_t)k * gridDim.x + blockIdx.x] = t;
-}
-
-// x_k += alpha_k p_k, r_k -= alpha_k q_k, partial sums of r_k . r_k
-__global__ void __launch_bounds__(WG) k_col_update(int n, size_t ld, int nr,
-                                                   const double *__restrict__ alpha,
-                                                   const double *__restrict__ P,
-                                                   const double *__restrict__ Q,
-                                                   double *__restrict__ X,
-                                                   double *__restrict__ R,
-                                                   double *__restrict__ part) {
-  __shared__ double sh[WG / 64];
-  const int k = blockIdx.y;
-  if (k >= nr) return;
-  const double a = alpha[k];
-  const size_t o = (size_t)k * ld;
-  double acc = 0.0;
-  for (int i = blockIdx.x * WG + threadIdx.x; i < n; i += gridDim.x * WG) {
-    X[o + i] = fma(a, P[o + i], X[o + i]);
-    const double ri = fma(-a, Q[o + i], R[o + i]);
-    R[o + i] = ri;
-    acc = fma(ri, ri, acc);
-  }
-  const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[(size_t)k * gridDim.x + blockIdx.x] = t;
-}
-
-// p_k = z_k + beta_k p_k
-__global__ void __launch_bounds__(WG) k_col_direction(int n, size_t ld, int nr,
-                                                      const double *__restrict__ beta,
-                                                      const double *__restrict__ Z,
-                                                      double *__restrict__ P) {
-  const int k = blockIdx.y;
-  if (k >= nr) return;
-  const double b = beta[k];
-  const size_t o = (size_t)k * ld;
-  for (int i = blockIdx.x * WG + threadIdx.x; i < n; i += gridDim.x * WG)
-    P[o + i] = fma(b, P[o + i], Z[o + i]);
-}
-
-// out[k] = sum of part[k * nb .. k * nb + nb) in a fixed order
-__global__ void __launch_bounds__(WG) k_col_reduce(int nb, const double *__restrict__ part,
-                                                   double *__restrict__ out) {
-  __shared__ double sh[WG / 64];
-  double acc = 0.0;
-  for (int b = threadIdx.x; b < nb; b += WG) acc += part[(size_t)blockIdx.x * nb + b];
-  const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) out[blockIdx.x] = t;
-}
-
 // ------------------------------------------------------------- launchers ---
 void launch_streams_to_env(hipStream_t s, const Plan &p, int ntilerows, const float *fst,
                            const float *bst, float *dg, float *er, float *ec) {
@@ -584,101 +447,6 @@ template void launch_trmm<double>(hipStream_t, const double *, int, const double
                                   double *, int);
 template void launch_trmm<float>(hipStream_t, const float *, int, const double *, int, double *,
                                  double *, int);
-
-static int col_blocks(int n) {
-  int b = (n + WG - 1) / WG;
-  return b > 256 ? 256 : (b < 1 ? 1 : b);
-}
-
-void launch_spmm_sell(hipStream_t s, int n, const long long *sptr, const int *scol,
-                      const double *sval, size_t ld, int nr, const double *X, double *Y) {
-  const unsigned b = (unsigned)(((long long)n + WG - 1) / WG);
-  if (b == 0 || nr <= 0) return;
-  hipLaunchKernelGGL(k_spmm_sell, dim3(b), dim3(WG), 0, s, n, sptr, scol, sval, ld, nr, X, Y);
-}
-
-void launch_col_dots(hipStream_t s, int n, size_t ld, int nr, const double *A, const double *B,
-                     double *part, double *out) {
-  const int nb = col_blocks(n);
-  hipLaunchKernelGGL(k_col_dots, dim3(nb, nr), dim3(WG), 0, s, n, ld, nr, A, B, part);
-  hipLaunchKernelGGL(k_col_reduce, dim3(nr), dim3(WG), 0, s, nb, part, out);
-}
-
-void launch_col_update(hipStream_t s, int n, size_t ld, int nr, const double *alpha,
-                       const double *P, const double *Q, double *X, double *R, double *part,
-                       double *rr) {
-  const int nb = col_blocks(n);
-  hipLaunchKernelGGL(k_col_update, dim3(nb, nr), dim3(WG), 0, s, n, ld, nr, alpha, P, Q, X, R,
-                     part);
-  hipLaunchKernelGGL(k_col_reduce, dim3(nr), dim3(WG), 0, s, nb, part, rr);
-}
-
-__global__ void __launch_bounds__(64) k_col_alpha(int nr, ColCgState *cs,
-                                                  const double *__restrict__ pq,
-                                                  double *__restrict__ alpha) {
-  const int k = threadIdx.x;
-  if (k >= nr) return;
-  double c = 0.0;
-  bool brk = false;
-  if (cs->active[k]) {
-    const double q = cs->rz[k] / pq[k];
-    if (!(pq[k] > 0.0) || !isfinite(q)) {
-      brk = true;
-      cs->active[k] = 0;
-    } else {
-      c = q;
-    }
-  }
-  alpha[k] = c;
-  const unsigned long long m = __ballot(brk);
-  if (k == 0 && m) cs->breakdown |= (int)m;
-}
-
-__global__ void __launch_bounds__(64) k_col_beta(int nr, ColCgState *cs,
-                                                 const double *__restrict__ rr,
-                                                 const double *__restrict__ rz, double rtol2,
-                                                 double *__restrict__ beta) {
-  const int k = threadIdx.x;
-  int act = 0;
-  bool brk = false;
-  if (k < nr) {
-    double c = 0.0;
-    cs->rr[k] = rr[k];
-    if (cs->active[k]) {
-      cs->its[k] += 1;
-      if (!isfinite(rr[k])) {
-        brk = true;
-        cs->active[k] = 0;
-      } else if (rr[k] <= rtol2 * cs->f2[k]) {
-        cs->active[k] = 0;
-      } else {
-        c = rz[k] / cs->rz[k];
-        cs->rz[k] = rz[k];
-      }
-    }
-    beta[k] = c;
-    act = cs->active[k];
-  }
-  const unsigned long long m = __ballot(act != 0), bm = __ballot(brk);
-  if (k == 0) {
-    cs->nact = __popcll(m);
-    if (bm) cs->breakdown |= (int)bm;
-  }
-}
-
-void launch_col_alpha(hipStream_t s, int nr, ColCgState *cs, const double *pq, double *alpha) {
-  hipLaunchKernelGGL(k_col_alpha, dim3(1), dim3(64), 0, s, nr, cs, pq, alpha);
-}
-
-void launch_col_beta(hipStream_t s, int nr, ColCgState *cs, const double *rr, const double *rz,
-                     double rtol2, double *beta) {
-  hipLaunchKernelGGL(k_col_beta, dim3(1), dim3(64), 0, s, nr, cs, rr, rz, rtol2, beta);
-}
-
-void launch_col_direction(hipStream_t s, int n, size_t ld, int nr, const double *beta,
-                          const double *Z, double *P) {
-  hipLaunchKernelGGL(k_col_direction, dim3(col_blocks(n), nr), dim3(WG), 0, s, n, ld, nr, beta, Z, P);
-}
 
 #define AMSP_MULTI_INST(T, TB)                                                                \
   template void launch_restrict_rows<TB>(hipStream_t, const Plan &, int, const TB *,           \
