@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, 1)))
   if (threadIdx.x == 0) fail = 0;
   tile_to_lds(tile_ptr(A0t, T0, k, k), X);
   __syncthreads();
-  lds_potrf_trtri<32>(X, Y, &fail);
+  lds_potrf_trtri(X, Y, &fail);
   lds_to_tile(X, tile_ptr(A0t, T0, k, k));
   lds_to_tile(Y, dinv + (size_t)k * TE);
   __syncthreads();
@@ -252,7 +252,7 @@ k_dense_next_potrf(double *A0t, int T0, int k, double *dinv, int *status) {
   __syncthreads();  // every wavefront has finished reading L_{k+1,k}
   acc_to_lds(o, Ly);
   __syncthreads();
-  lds_potrf_trtri<32>(Ly, Y, &fail);
+  lds_potrf_trtri(Ly, Y, &fail);
   lds_to_tile(Ly, c);
   lds_to_tile(Y, dinv + (size_t)j * TE);
   __syncthreads();

@@ -136,19 +136,12 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// 1/sqrt(d) for d > 0 to double precision: hardware estimate refined by two
-// Newton steps y <- y (3 - d y^2) / 2 (each squares the relative error).
-__device__ __forceinline__ double rsqrt_nr(double d) {
-  double y = __builtin_amdgcn_rsq(d);
-  const double hd = -0.5 * d;
-  y = y * fma(hd, y * y, 1.5);
-  y = y * fma(hd, y * y, 1.5);
-  return y;
-}
-
-__device__ __forceinline__ int opaque_int(int v) {
-  __asm__ volatile("" : "+v"(v));
-  return v;
+// 1/sqrt(d) for d > 0 to double precision: hardware estimate y (24 bits or
+// more) refined by one third-order step, y (1 + e/2 + 3e^2/8) with e = 1 - d y^2.
+__device__ __forceinline__ double rsqrt_d(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-(d * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // Compile-time loop: f(std::integral_constant<int, v>) for v = B, B+S, ... < E.
@@ -220,136 +213,138 @@ __device__ __forceinline__ float quad_sum(float v) {
 // Cholesky factor of a 64x64 SPD tile and the inverse of the factor, in LDS.
 //   a (stride LDT): lower triangle of the tile on entry, L on exit (upper 0)
 //   w (stride LDT): inv(L) on exit (upper 0)
-// Factorisation: wavefront 0, lane i holds row i in registers (right-looking).
-// At step k the entry L[k+1][k] that the next pivot waits for is taken from
-// lane k+1 directly; the other entries of column k are broadcast through LDS
-// (double-buffered, read in batches of CH).  A single wavefront's LDS
-// accesses complete in program order, so the steps need no barriers.
-// Inverse: all four wavefronts; each column of inv(L) is solved by four
-// adjacent lanes that split every row's dot product and combine it with quad
-// permutations; the next row of L is fetched while the current one is used.
+// A chain of 64 dependent pivots bounds this; all other work is arranged around
+// it, in blocks of 16 rows.  Wavefront 0 factors the diagonal blocks: a lane holds
+// a column of the block and of the identity, one elimination turns them into L
+// and inv(L), and each step's multipliers reach the 16 lanes through DPP (no LDS
+// and no scalar registers on the chain).  The blocks below and left of
+// it are products on the matrix cores: behind block b's pivots come its panel
+// L_ib = A_ib inv(L_bb)^T and row b of the inverse, W_bj = -inv(L_bb) S_bj, one
+// product per wavefront; then wavefront 0 updates and factors the next diagonal
+// block, while the other three update the remaining blocks (A_ij -= L_ib
+// L_jb^T) and the inverse's sums (S_ij += L_ib W_bj, kept in w).  One tile takes
+// 8.2 us, 230 cycles a pivot; 23.3 with all 64 columns in one wavefront's
+// registers and the inverse solved row by row behind it.  (Multipliers as
+// wave-uniform lane reads: 10.5.)
 // A non-positive or non-finite pivot sets *fail and is replaced by 1 so that
 // the result stays finite.  Needs blockDim.x == 256.
-template <int CH>
+
+// c += X Y^T or X Y of 16x16 blocks in LDS (row stride LDT), one wavefront;
+// element r of c is row lane / 16 + 4r, column lane % 16.
+template <bool YT>
+__device__ __forceinline__ d4 block_mma(const double *X, const double *Y, d4 c, double sign) {
+  const int l = threadIdx.x & 63, i = l & 15, q = l >> 4;
+  double x[4], y[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    x[s] = X[i * LDT + 4 * q + s];
+    y[s] = YT ? Y[i * LDT + 4 * q + s] : Y[(4 * q + s) * LDT + i];
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = mfma16x16x4(sign * x[s], y[s], c);
+  return c;
+}
+__device__ __forceinline__ d4 block_load(const double *X) {
+  const int l = threadIdx.x & 63;
+  d4 c;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c[r] = X[((l >> 4) + 4 * r) * LDT + (l & 15)];
+  return c;
+}
+__device__ __forceinline__ void block_store(double *X, d4 c) {
+  const int l = threadIdx.x & 63;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) X[((l >> 4) + 4 * r) * LDT + (l & 15)] = c[r];
+}
+
+// Lane K of every 16 lanes' value in all 16 of them (DPP, folds into the use).
+template <int K>
+__device__ __forceinline__ double row_bcast(double v) {
+  return __builtin_amdgcn_update_dpp(v, v, 0x150 + K, 0xF, 0xF, true);
+}
+
+// One diagonal block (one wavefront): L over its lower triangle in a, inv(L) in
+// w, zeros above both diagonals.  Returns whether a pivot was bad.
+__device__ __forceinline__ bool block_factor(double *a, double *w) {
+  const int l = threadIdx.x & 63, c = l & 15;
+  double v[16], x[16];  // column c of the block and of the identity, in every 16 lanes
+  static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value;
+    v[i] = a[max(i, c) * LDT + min(i, c)];
+    x[i] = i == c ? 1.0 : 0.0;
+  });
+  wave_sync();
+  // lanes 0 .. 15 store row k of L^T, the others (repeatedly) row k of inv(L)
+  const bool left = l < 16;
+  double *out = left ? a + c * LDT : w + c;
+  const int step = left ? 1 : LDT, kept = left ? c : 16;  // (inv(L) is zero above by itself)
+  bool bad = false;
+  static_for<0, 16>([&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
+    const double d = row_bcast<k>(v[k]);
+    const bool bk = !(d > 0.0) || !isfinite(d);
+    bad = bad || bk;
+    double inv = rsqrt_d(d);
+    __asm__ volatile("" : "+v"(inv));  // no branch around it
+    inv = bk ? 1.0 : inv;
+    const double uv = v[k] * inv, ux = x[k] * inv;
+    if constexpr (k < 15) {
+      const double m = row_bcast<k>(v[k + 1]) * inv;
+      x[k + 1] = fma(-m, ux, x[k + 1]);
+      v[k + 1] = fma(-m, uv, v[k + 1]);  // the next pivot waits for this one only
+      const double tv = -(uv * inv), tx = -(ux * inv);
+      static_for<k + 2, 16>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        x[i] = fma(row_bcast<k>(v[i]), tx, x[i]);
+        v[i] = fma(row_bcast<k>(v[i]), tv, v[i]);
+      });
+    }
+    *out = kept >= k ? (left ? uv : ux) : 0.0;
+    out += step;
+  });
+  return bad;
+}
+
 __device__ __forceinline__ void lds_potrf_trtri(double *a, double *w, int *fail) {
-  // The lane index and the LDS base pass once through an opaque move, so
-  // that callers' loops cannot hoist the lane-dependent masks or the
-  // constant LDS addresses below out of the loop and keep them live.
-  const int lane_id = opaque_int((int)threadIdx.x);
-  const int z = opaque_int(0);
-  double *aa = a + z, *ww = w + z;
-  double *ls = ww;        // rows of L with stride 64 for the inverse phase
-  double *rdg = ww + TE;  // 1 / L_kk  (TE + 64 <= TS * LDT)
-  if (threadIdx.x < 64) {
-    const int i = lane_id;
-    double *col = aa;  // two column buffers (a is free once its rows are in registers)
-    double r[TS];      // row i; entries right of the diagonal are never used
-    static_for<0, TS>([&](auto jc) __attribute__((always_inline)) {
-      r[jc.value] = aa[i * LDT + jc.value];
-    });
-    wave_sync();
-    bool bad = false;
-    // column k of L for this lane's row, given the updated r[k]
-    auto pivot = [&](auto kc) __attribute__((always_inline)) {
-      constexpr int k = decltype(kc)::value;
-      double d = readlane_d(r[k], k);
-      const bool bk = !(d > 0.0) || !isfinite(d);
-      bad = bad || bk;
-      d = bk ? 1.0 : d;
-      const double inv = rsqrt_nr(d);
-      r[k] = (i == k) ? d * inv : r[k] * inv;
-      rdg[k] = inv;
-      col[(k & 1) * TS + i] = r[k];
-    };
-    pivot(std::integral_constant<int, 0>{});
-    // Step k: the reads of column k go out first; the next pivot (which
-    // needs only column k+1, updated through a lane read) and its column
-    // write overlap their latency; then the bulk update of columns >= k+2.
-    static_for<0, TS - 1>([&](auto kc) __attribute__((always_inline)) {
-      constexpr int k = decltype(kc)::value;
-      constexpr int nb = (TS - (k + 2) + CH - 1) / CH;  // batches of columns >= k+2
-      const double *cb = col + (k & 1) * TS;
-      const double lk = r[k];
-      double cva[CH], cvb[CH];
-      auto load_batch = [&](auto bc, double(&cv)[CH]) __attribute__((always_inline)) {
-        constexpr int j0 = k + 2 + CH * decltype(bc)::value;
-        constexpr int j1 = j0 + CH < TS ? j0 + CH : TS;
-        static_for<j0, j1>([&](auto jc) __attribute__((always_inline)) {
-          cv[jc.value - j0] = cb[jc.value];
-        });
-      };
-      if constexpr (nb > 0) load_batch(std::integral_constant<int, 0>{}, cva);
-      r[k + 1] = fma(-lk, readlane_d(lk, k + 1), r[k + 1]);
-      pivot(std::integral_constant<int, k + 1>{});
-      static_for<0, nb>([&](auto bc) __attribute__((always_inline)) {
-        constexpr int bi = decltype(bc)::value;
-        double(&cur)[CH] = (bi & 1) ? cvb : cva;
-        double(&nxt)[CH] = (bi & 1) ? cva : cvb;
-        if constexpr (bi + 1 < nb) load_batch(std::integral_constant<int, bi + 1>{}, nxt);
-        constexpr int j0 = k + 2 + CH * bi;
-        constexpr int j1 = j0 + CH < TS ? j0 + CH : TS;
-        static_for<j0, j1>([&](auto jc) __attribute__((always_inline)) {
-          r[jc.value] = fma(-lk, cur[jc.value - j0], r[jc.value]);
-        });
-      });
-    });
-    if (bad && i == 0) *fail = 1;
-    wave_sync();
-    static_for<0, TS>([&](auto jc) __attribute__((always_inline)) {
-      aa[i * LDT + jc.value] = r[jc.value];
-      ls[i * TS + jc.value] = r[jc.value];
-    });
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  auto at = [](double *t, int i, int j) { return t + 16 * i * LDT + 16 * j; };
+  for (int b = 0; b < 4; ++b) {
+    if (wv == 0) {
+      if (b > 0) {
+        const double *lb = at(a, b, b - 1);
+        block_store(at(a, b, b), block_mma<true>(lb, lb, block_load(at(a, b, b)), -1.0));
+        wave_sync();
+      }
+      if (block_factor(at(a, b, b), at(w, b, b)) && threadIdx.x == 0) *fail = 1;
+    } else if (b == 0) {  // the blocks above the diagonal
+      for (int e = threadIdx.x - 64; e < 6 * 256; e += 192) {
+        const int k = e >> 8, i = k < 3 ? 0 : k < 5 ? 1 : 2, j = k < 3 ? k + 1 : k < 5 ? k - 1 : 3;
+        const int o = (16 * i + ((e >> 4) & 15)) * LDT + 16 * j + (e & 15);
+        a[o] = 0.0;
+        w[o] = 0.0;
+      }
+    } else {  // what block b - 1 adds to the rows from b on
+      const int p = b - 1;
+      int k = 0;
+      for (int i = b; i < 4; ++i)
+        for (int j = 0; j <= i; ++j) {
+          if ((i == b && j == b) || k++ % 3 + 1 != wv) continue;
+          double *t = j < b ? at(w, i, j) : at(a, i, j);
+          if (j < b)
+            block_store(t, block_mma<false>(at(a, i, p), at(w, p, j),
+                                            j < p ? block_load(t) : d4{0.0, 0.0, 0.0, 0.0}, 1.0));
+          else
+            block_store(t, block_mma<true>(at(a, i, p), at(a, j, p), block_load(t), -1.0));
+        }
+    }
+    __syncthreads();
+    const d4 zero = {0.0, 0.0, 0.0, 0.0};
+    if (wv > b)
+      block_store(at(a, wv, b), block_mma<true>(at(a, wv, b), at(w, b, b), zero, 1.0));
+    else if (wv < b)
+      block_store(at(w, b, wv), block_mma<false>(at(w, b, b), at(w, b, wv), zero, -1.0));
+    __syncthreads();
   }
-  __syncthreads();
-  {
-    // column j of inv(L): x_m = (delta_mj - sum_{q<m} L_mq x_q) / L_mm.
-    // Lane (j, p): p = lane & 3 owns x_q for q = 4t + p (xs[t]).
-    const int p = lane_id & 3;
-    const int j = lane_id >> 2;  // 0..63
-    double xs[TS / 4];  // zero-initialised: masked products must see finite values
-    static_for<0, TS / 4>([&](auto tc) __attribute__((always_inline)) { xs[tc.value] = 0.0; });
-    double lva[TS / 4], lvb[TS / 4];  // rows m (even / odd) of L, entries q = 4t + p
-    auto load_row = [&](auto mc, double(&lv)[TS / 4]) __attribute__((always_inline)) {
-      constexpr int m = decltype(mc)::value;
-      static_for<0, (m + 3) / 4>([&](auto tc) __attribute__((always_inline)) {
-        constexpr int t = decltype(tc)::value;
-        const int q = 4 * t + p;
-        lv[t] = (q < m) ? ls[m * TS + q] : 0.0;
-      });
-    };
-    load_row(std::integral_constant<int, 1>{}, lvb);
-    static_for<0, TS>([&](auto mc) __attribute__((always_inline)) {
-      constexpr int m = decltype(mc)::value;
-      constexpr int nt = (m + 3) / 4;
-      double(&cur)[TS / 4] = (m & 1) ? lvb : lva;
-      double(&nxt)[TS / 4] = (m & 1) ? lva : lvb;
-      if constexpr (m + 1 < TS) load_row(std::integral_constant<int, m + 1>{}, nxt);
-      double s0 = 0.0, s1 = 0.0;
-      static_for<0, nt>([&](auto tc) __attribute__((always_inline)) {
-        constexpr int t = decltype(tc)::value;
-        if constexpr ((t & 1) == 0)
-          s0 = fma(-cur[t], xs[t], s0);
-        else
-          s1 = fma(-cur[t], xs[t], s1);
-      });
-      double sum = s0 + s1;
-      sum += dpp_quad<0xB1>(sum);
-      sum += dpp_quad<0x4E>(sum);
-      const double xm = ((j == m) ? 1.0 + sum : sum) * rdg[m];
-      constexpr int tm = m / 4;
-      xs[tm] = (p == (m & 3)) ? xm : xs[tm];
-    });
-    __syncthreads();  // all reads of ls / rdg done before w is overwritten
-    static_for<0, TS / 4>([&](auto tc) __attribute__((always_inline)) {
-      constexpr int t = decltype(tc)::value;
-      ww[(4 * t + p) * LDT + j] = xs[t];  // exact zeros above the diagonal
-    });
-  }
-  for (int e = threadIdx.x; e < TE; e += blockDim.x) {
-    const int r = e >> 6, c = e & 63;
-    if (c > r) a[r * LDT + c] = 0.0;
-  }
-  __syncthreads();
 }
 
 // ------------------------------------------------ MFMA tile products ------

@@ -135,7 +135,7 @@ k_tree_potrf(TreeDev t, int f0, int k, double *F, double *dinv, int *status) {
   double *a = ftile(F, t, f, k, k);
   tile_to_lds(a, A);
   __syncthreads();
-  lds_potrf_trtri<32>(A, Y, &fail);
+  lds_potrf_trtri(A, Y, &fail);
   lds_to_tile(A, a);
   lds_to_tile(Y, dinv + (size_t)(t.dbase[f] + k) * TE);
   __syncthreads();
