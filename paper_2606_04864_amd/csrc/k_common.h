@@ -229,32 +229,34 @@ __device__ __forceinline__ float quad_sum(float v) {
 // A non-positive or non-finite pivot sets *fail and is replaced by 1 so that
 // the result stays finite.  Needs blockDim.x == 256.
 
-// c += X Y^T or X Y of 16x16 blocks in LDS (row stride LDT), one wavefront;
+// c += X Y^T or X Y of 16x16 blocks in LDS (row stride LD), one wavefront;
 // element r of c is row lane / 16 + 4r, column lane % 16.
-template <bool YT>
+template <bool YT, int LD = LDT>
 __device__ __forceinline__ d4 block_mma(const double *X, const double *Y, d4 c, double sign) {
   const int l = threadIdx.x & 63, i = l & 15, q = l >> 4;
   double x[4], y[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    x[s] = X[i * LDT + 4 * q + s];
-    y[s] = YT ? Y[i * LDT + 4 * q + s] : Y[(4 * q + s) * LDT + i];
+    x[s] = X[i * LD + 4 * q + s];
+    y[s] = YT ? Y[i * LD + 4 * q + s] : Y[(4 * q + s) * LD + i];
   }
 #pragma unroll
   for (int s = 0; s < 4; ++s) c = mfma16x16x4(sign * x[s], y[s], c);
   return c;
 }
+template <int LD = LDT>
 __device__ __forceinline__ d4 block_load(const double *X) {
   const int l = threadIdx.x & 63;
   d4 c;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) c[r] = X[((l >> 4) + 4 * r) * LDT + (l & 15)];
+  for (int r = 0; r < 4; ++r) c[r] = X[((l >> 4) + 4 * r) * LD + (l & 15)];
   return c;
 }
+template <int LD = LDT>
 __device__ __forceinline__ void block_store(double *X, d4 c) {
   const int l = threadIdx.x & 63;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) X[((l >> 4) + 4 * r) * LDT + (l & 15)] = c[r];
+  for (int r = 0; r < 4; ++r) X[((l >> 4) + 4 * r) * LD + (l & 15)] = c[r];
 }
 
 // Lane K of every 16 lanes' value in all 16 of them (DPP, folds into the use).
@@ -264,29 +266,32 @@ __device__ __forceinline__ double row_bcast(double v) {
 }
 
 // One diagonal block (one wavefront): L over its lower triangle in a, inv(L) in
-// w, zeros above both diagonals.  Returns whether a pivot was bad.
-__device__ __forceinline__ bool block_factor(double *a, double *w) {
+// w, zeros above both diagonals.  A pivot not above lo (or not finite) is bad and
+// its root's inverse replaced by alt; returns whether one was.
+template <int LD = LDT>
+__device__ __forceinline__ bool block_factor(double *a, double *w, double lo = 0.0,
+                                             double alt = 1.0) {
   const int l = threadIdx.x & 63, c = l & 15;
   double v[16], x[16];  // column c of the block and of the identity, in every 16 lanes
   static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
     constexpr int i = decltype(ic)::value;
-    v[i] = a[max(i, c) * LDT + min(i, c)];
+    v[i] = a[max(i, c) * LD + min(i, c)];
     x[i] = i == c ? 1.0 : 0.0;
   });
   wave_sync();
   // lanes 0 .. 15 store row k of L^T, the others (repeatedly) row k of inv(L)
   const bool left = l < 16;
-  double *out = left ? a + c * LDT : w + c;
-  const int step = left ? 1 : LDT, kept = left ? c : 16;  // (inv(L) is zero above by itself)
+  double *out = left ? a + c * LD : w + c;
+  const int step = left ? 1 : LD, kept = left ? c : 16;  // (inv(L) is zero above by itself)
   bool bad = false;
   static_for<0, 16>([&](auto kc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc)::value;
     const double d = row_bcast<k>(v[k]);
-    const bool bk = !(d > 0.0) || !isfinite(d);
+    const bool bk = !(d > lo) || !isfinite(d);
     bad = bad || bk;
     double inv = rsqrt_d(d);
     __asm__ volatile("" : "+v"(inv));  // no branch around it
-    inv = bk ? 1.0 : inv;
+    inv = bk ? alt : inv;
     const double uv = v[k] * inv, ux = x[k] * inv;
     if constexpr (k < 15) {
       const double m = row_bcast<k>(v[k + 1]) * inv;

@@ -17,6 +17,7 @@
 namespace amsp {
 
 constexpr int HP = EIGP + 1;  // padded row stride of the small matrices
+constexpr int GR = EIG_GRAM_ROWS;
 static_assert(WG == EIGP * EIGP, "one thread per entry of the EIGP x EIGP Gram matrices");
 
 __device__ __forceinline__ double hash_uniform(unsigned a, unsigned b) {
@@ -45,93 +46,89 @@ __global__ void __launch_bounds__(WG) k_eig_init(Plan p, const double *__restric
   }
 }
 
-// Cyclic Jacobi on the symmetric EIGP x EIGP matrix H (LDS, stride HP) by
-// one wavefront; V accumulates the rotations.  Round-robin ordering: EIGP/2
-// disjoint pairs per round, EIGP-1 rounds per sweep.  Lane (i, j) = (t / 8,
-// t % 8) forms the rotations of pairs i and j itself (the same arithmetic in
-// every lane that needs them) and rotates the 2 x 2 block of H at the rows
-// of pair i and the columns of pair j, rows first (J^T H) then columns (H J),
-// and the same block of V by columns, into the other buffer of each pair
-// (Hs, Vs): one barrier per round.  H and V end up pointing at the result.
-__device__ void jacobi16(double *&H, double *&V, double *Hs, double *Vs, int *flag,
-                         double off_rel2) {
+// Cyclic Jacobi on the symmetric EIGP x EIGP matrix H (LDS, stride HS) by one
+// wavefront; V (EIGP rows) accumulates the rotations.  Round-robin ordering:
+// EIGP/2 disjoint pairs per round, EIGP-1 rounds per sweep.  The index pairs of
+// a round sit in the slots (2k, 2k + 1) of H and of V's columns, and every round
+// writes its results to the next round's slots, a fixed permutation that a sweep
+// closes: all addresses are constants of the lane.  Lane (i, j) = (t / 8, t % 8)
+// forms the rotations of pairs i and j itself (the same arithmetic in every lane
+// that needs them) and rotates the 2 x 2 block of H at the rows of pair i and the
+// columns of pair j, rows first (J^T H) then columns (H J), and rows 2i, 2i + 1
+// of V at the columns of pair j.  LDS operations of a wavefront are in order,
+// so one buffer is enough.
+constexpr int HS = EIGP + 2;  // row stride of H and V (16-byte pieces)
+
+// Slot of index p (and index in slot p's mirror image) at the start of a sweep.
+__device__ __forceinline__ int jacobi_slot(int p) { return p < 8 ? 2 * p : 2 * (EIGP - 1 - p) + 1; }
+
+// Rotation (c, s) that clears the entry b2 / 2 between diagonals differing by a:
+// tan from tau = a / b2, formed as c^2 = (1 + |a| / r) / 2, s = b2 / (2 r c) with
+// r^2 = a^2 + b2^2 (two inverse roots, no divisions), a and b2 scaled by a
+// common power of two.
+__device__ __forceinline__ void jacobi_rotation(double a, double b2, double &c, double &s) {
+  const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(a), fabs(b2)));
+  const double as = ldexp(a, e), bs = ldexp(b2, e);
+  const double ri = rsqrt_d(fma(as, as, bs * bs));
+  const double x = 0.5 * fma(fabs(as), ri, 1.0);
+  const double xi = rsqrt_d(x);
+  const double sv = 0.5 * bs * ri * xi;
+  c = b2 != 0.0 ? x * xi : 1.0;
+  s = b2 != 0.0 ? (a < 0.0 ? -sv : sv) : 0.0;
+}
+
+__device__ void jacobi16(double *H, double *V, double off_rel2) {
   static_assert(EIGP == 16, "lane (i, j) of one wavefront per pair of pairs");
-  const int t = threadIdx.x;
-  for (int e = t; e < EIGP * EIGP; e += 64) V[(e / EIGP) * HP + e % EIGP] = (e / EIGP == e % EIGP) ? 1.0 : 0.0;
-  __syncthreads();
-  const int i = t >> 3, j = t & 7;
+  const int t = threadIdx.x, i = t >> 3, j = t & 7;
+  for (int e = t; e < EIGP * EIGP; e += 64)
+    V[(e / EIGP) * HS + jacobi_slot(e % EIGP)] = (e / EIGP == e % EIGP) ? 1.0 : 0.0;
+  // slots of pair k's indices in the next round
+  auto next = [](int k, int &s0, int &s1) {
+    s0 = k == 0 ? 3 : 2 * k - 2;
+    s1 = k == 0 ? 1 : k == 7 ? 14 : 2 * k + 3;
+  };
+  int r0, r1, c0, c1;
+  next(i, r0, r1);
+  next(j, c0, c1);
+  const double *const hi = H + 2 * i * HS + 2 * i, *const hj = H + 2 * j * HS + 2 * j;
+  const double *const hb = H + 2 * i * HS + 2 * j, *const vb = V + 2 * i * HS + 2 * j;
+  wave_sync();
   for (int sweep = 0; sweep < 30; ++sweep) {
-    {  // off-diagonal and total Frobenius norms
-      double off = 0.0, tot = 0.0;
-      for (int e = t; e < EIGP * EIGP; e += 64) {
-        const int a = e / EIGP, b = e % EIGP;
-        const double h2 = H[a * HP + b] * H[a * HP + b];
-        tot += h2;
-        if (a != b) off += h2;
-      }
-      off = wave_sum(off);
-      tot = wave_sum(tot);
-      // stop once the off-diagonal part is below sqrt(off_rel2) relative
-      // (never below 1e-14: rounding keeps it near 1e-16 relative)
-      if (t == 0) *flag = (off <= off_rel2 * tot) ? 1 : 0;
+    // stop once the off-diagonal part is below sqrt(off_rel2) relative
+    // (never below 1e-14: rounding keeps it near 1e-16 relative)
+    double off = 0.0, tot = 0.0;
+#pragma unroll
+    for (int e = t; e < EIGP * EIGP; e += 64) {
+      const int a = e / EIGP, b = e % EIGP;
+      const double h2 = H[a * HS + b] * H[a * HS + b];
+      tot += h2;
+      off += a != b ? h2 : 0.0;
     }
-    __syncthreads();
-    if (*flag) break;
+    off = wave_sum(off);
+    tot = wave_sum(tot);
+    if (__all(off <= off_rel2 * tot)) break;
+#pragma unroll 1
     for (int rnd = 0; rnd < EIGP - 1; ++rnd) {
-      auto pair = [&](int k, int &pp, int &qq) {
-        if (k == 0) {
-          pp = rnd;
-          qq = EIGP - 1;
-        } else {
-          pp = (rnd + k) % (EIGP - 1);
-          qq = (rnd - k + (EIGP - 1)) % (EIGP - 1);
-        }
-        if (pp > qq) {
-          const int tmp = pp;
-          pp = qq;
-          qq = tmp;
-        }
-      };
-      auto rotation = [&](int pp, int qq, double &c, double &s) {
-        const double apq = H[pp * HP + qq];
-        c = 1.0;
-        s = 0.0;
-        if (apq != 0.0) {
-          const double tau = (H[qq * HP + qq] - H[pp * HP + pp]) / (2.0 * apq);
-          const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + tt * tt);
-          s = tt * c;
-        }
-      };
-      int pi, qi, pj, qj;
-      pair(i, pi, qi);
-      pair(j, pj, qj);
+      const d2 di = *reinterpret_cast<const d2 *>(hi), dj = *reinterpret_cast<const d2 *>(hj);
+      const double ei = hi[HS + 1], ej = hj[HS + 1];
+      const d2 hp = *reinterpret_cast<const d2 *>(hb), hq = *reinterpret_cast<const d2 *>(hb + HS);
+      const d2 vp = *reinterpret_cast<const d2 *>(vb), vq = *reinterpret_cast<const d2 *>(vb + HS);
       double ci, si, cj, sj;
-      rotation(pi, qi, ci, si);
-      rotation(pj, qj, cj, sj);
-      const double hpp = H[pi * HP + pj], hpq = H[pi * HP + qj];
-      const double hqp = H[qi * HP + pj], hqq = H[qi * HP + qj];
-      const double vpp = V[pi * HP + pj], vpq = V[pi * HP + qj];
-      const double vqp = V[qi * HP + pj], vqq = V[qi * HP + qj];
-      // rows pi, qi (pair i's rotation), columns pj and qj
-      const double rpp = ci * hpp - si * hqp, rqp = si * hpp + ci * hqp;
-      const double rpq = ci * hpq - si * hqq, rqq = si * hpq + ci * hqq;
-      // then columns pj, qj (pair j's rotation)
-      Hs[pi * HP + pj] = cj * rpp - sj * rpq;
-      Hs[pi * HP + qj] = sj * rpp + cj * rpq;
-      Hs[qi * HP + pj] = cj * rqp - sj * rqq;
-      Hs[qi * HP + qj] = sj * rqp + cj * rqq;
-      Vs[pi * HP + pj] = cj * vpp - sj * vpq;
-      Vs[pi * HP + qj] = sj * vpp + cj * vpq;
-      Vs[qi * HP + pj] = cj * vqp - sj * vqq;
-      Vs[qi * HP + qj] = sj * vqp + cj * vqq;
-      __syncthreads();
-      double *x = H;
-      H = Hs;
-      Hs = x;
-      x = V;
-      V = Vs;
-      Vs = x;
+      jacobi_rotation(ei - di[0], 2.0 * di[1], ci, si);
+      jacobi_rotation(ej - dj[0], 2.0 * dj[1], cj, sj);
+      // rows of pair i's rotation, columns of pair j
+      const double rpp = ci * hp[0] - si * hq[0], rqp = si * hp[0] + ci * hq[0];
+      const double rpq = ci * hp[1] - si * hq[1], rqq = si * hp[1] + ci * hq[1];
+      wave_sync();
+      H[r0 * HS + c0] = cj * rpp - sj * rpq;
+      H[r0 * HS + c1] = sj * rpp + cj * rpq;
+      H[r1 * HS + c0] = cj * rqp - sj * rqq;
+      H[r1 * HS + c1] = sj * rqp + cj * rqq;
+      V[2 * i * HS + c0] = cj * vp[0] - sj * vp[1];
+      V[2 * i * HS + c1] = sj * vp[0] + cj * vp[1];
+      V[(2 * i + 1) * HS + c0] = cj * vq[0] - sj * vq[1];
+      V[(2 * i + 1) * HS + c1] = sj * vq[0] + cj * vq[1];
+      wave_sync();
     }
   }
 }
@@ -139,8 +136,8 @@ __device__ void jacobi16(double *&H, double *&V, double *Hs, double *Vs, int *fl
 // Rayleigh-Ritz on the span of the solve output Y (n_i x EIGP), without
 // forming an orthonormal basis: with G = Y^T Y = L L^T and K = Y^T B Y, the
 // Ritz problem is H = L^{-1} K L^{-T}, H V = V Theta, and the Ritz vectors
-// are X = Y C with C = L^{-T} V.  Per sweep: BY = B Y (flat sparse product),
-// G and K (MFMA over Y and BY), the small Ritz problems, then X = Y C and
+// are X = Y C with C = L^{-T} V.  Per sweep: BY = B Y (sparse
+// product) with G and K (MFMA), the small Ritz problems, then X = Y C and
 // the residuals (BY) C - X Theta (MFMA again).
 
 // Off-diagonal entries of B_i = S^{-1/2} hat A_i S^{-1/2} for every local CSR
@@ -159,209 +156,164 @@ __global__ void __launch_bounds__(WG) k_eig_bval(Plan p, const double *__restric
   }
 }
 
-// BY = B Y for the real rows of every unconverged region: grid (row block,
-// region), 16 rows per workgroup, thread = (row, column); 16 consecutive
-// threads share a row and read 128 contiguous bytes of each neighbour row.
-__global__ void __launch_bounds__(WG) k_eig_spmm(Plan p, const double *__restrict__ bval,
+// BY = B Y for the real rows of every unconverged region and, in the same pass,
+// the Gram matrices G = Y^T Y and K = Y^T (B Y): workgroup (b, i) takes rows
+// GR b .. of region i and leaves its part of both in GK[i][b].  Four lanes per
+// row, four columns each (32-byte pieces of each neighbour row; a row's entry
+// indices and values are loaded by four lanes); a wavefront's 16 rows of Y and BY
+// then go through LDS to the matrix cores' layout (four rows per MFMA, lane l
+// row l / 16 and column l % 16 as both operands).
+// Bound by memory.  64 regions of 1284 rows take 12 us, 1024 of them 153; with
+// the Gram matrices as a pass of their own over Y and BY 10 + 20 and 119 + 60.
+// (GR: 64 rows 13 and 176, 256 rows 14 and 172.)
+// Regions with n_i <= EIGP store G = I and K = dense B_i padded with a diagonal
+// above [0, 2].
+__global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) k_eig_spmm(Plan p, const double *__restrict__ val,
+                                                 const double *__restrict__ sdiag,
+                                                 const double *__restrict__ bval,
                                                  const double *__restrict__ Y,
                                                  double *__restrict__ BY,
+                                                 double *__restrict__ GK, int parts,
                                                  const int *__restrict__ conv) {
   const int i = blockIdx.y;
-  if (conv[i]) return;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
-  // four lanes per row, four columns each (32-byte row pieces): a row's
-  // entry indices and values are loaded by four lanes instead of sixteen
-  const int l = blockIdx.x * (WG / 4) + (threadIdx.x >> 2), a = 4 * (threadIdx.x & 3);
-  if (l >= ni) return;
+  if (conv[i] || (int)blockIdx.x * GR >= ni) return;
+  __shared__ __attribute__((aligned(32))) double sh[WG / 64][2][EIGP * EIGP];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int a = 4 * (t & 3);
   const size_t base = (size_t)p.vp_ptr[i] * EIGP;
-  const d4 y0 = *reinterpret_cast<const d4 *>(Y + base + (size_t)l * EIGP + a);
-  double acc[4] = {y0[0], y0[1], y0[2], y0[3]};
-  const int e0 = p.loc_rowptr[r0 + l], e1 = p.loc_rowptr[r0 + l + 1];
-  // the first SU entries: all index and value loads, then all row loads,
-  // then the products in entry order; longer rows continue one by one
-  constexpr int SU = 8;
-  int c[SU];
-  double b[SU];
-  d4 y[SU];
+  double *out = GK + ((size_t)i * parts + blockIdx.x) * 2 * EIGP * EIGP;
+  d4 g = {0.0, 0.0, 0.0, 0.0}, k = {0.0, 0.0, 0.0, 0.0};
+  for (int rb = (int)blockIdx.x * GR; rb < min(ni, (int)(blockIdx.x + 1) * GR); rb += WG / 4) {
+    const int row = rb + (t >> 2), l = min(row, ni - 1);
+    const d4 y0 = *reinterpret_cast<const d4 *>(Y + base + (size_t)l * EIGP + a);
+    double acc[4] = {y0[0], y0[1], y0[2], y0[3]};
+    const int e0 = p.loc_rowptr[r0 + l], e1 = p.loc_rowptr[r0 + l + 1];
+    // the first SU entries (a row has at least its diagonal): all index and
+    // value loads, then all row loads, then the products in entry order;
+    // longer rows continue one by one
+    constexpr int SU = 8;
+    int c[SU];
+    double b[SU];
+    d4 y[SU];
 #pragma unroll
-  for (int u = 0; u < SU; ++u) {
-    const bool in = e0 + u < e1;
-    c[u] = in ? p.loc_col[e0 + u] : l;
-    b[u] = in ? bval[e0 + u] : 0.0;
-  }
-#pragma unroll
-  for (int u = 0; u < SU; ++u) y[u] = *reinterpret_cast<const d4 *>(Y + base + (size_t)c[u] * EIGP + a);
-#pragma unroll
-  for (int u = 0; u < SU; ++u)
-    if (e0 + u < e1) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = fma(b[u], y[u][j], acc[j]);
+    for (int u = 0; u < SU; ++u) {
+      const int e = min(e0 + u, e1 - 1);
+      c[u] = p.loc_col[e];
+      b[u] = bval[e];
     }
-  for (int e = e0 + SU; e < e1; ++e) {
-    const double be = bval[e];
-    const d4 ye = *reinterpret_cast<const d4 *>(Y + base + (size_t)p.loc_col[e] * EIGP + a);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = fma(be, ye[j], acc[j]);
+    for (int u = 0; u < SU; ++u) y[u] = *reinterpret_cast<const d4 *>(Y + base + (size_t)c[u] * EIGP + a);
+#pragma unroll
+    for (int u = 0; u < SU; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const double f = fma(b[u], y[u][j], acc[j]);
+        acc[j] = e0 + u < e1 ? f : acc[j];
+      }
+    for (int e = e0 + SU; e < e1; ++e) {
+      const double be = bval[e];
+      const d4 ye = *reinterpret_cast<const d4 *>(Y + base + (size_t)p.loc_col[e] * EIGP + a);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = fma(be, ye[j], acc[j]);
+    }
+    const bool real = row < ni;
+    const d4 zero = {0.0, 0.0, 0.0, 0.0}, by = {acc[0], acc[1], acc[2], acc[3]};
+    if (real) *reinterpret_cast<d4 *>(BY + base + (size_t)l * EIGP + a) = by;
+    *reinterpret_cast<d4 *>(&sh[w][0][(lane >> 2) * EIGP + a]) = real ? y0 : zero;
+    *reinterpret_cast<d4 *>(&sh[w][1][(lane >> 2) * EIGP + a]) = real ? by : zero;
+    wave_sync();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double ys = sh[w][0][64 * s + lane], bs = sh[w][1][64 * s + lane];
+      g = mfma16x16x4(ys, ys, g);
+      k = mfma16x16x4(ys, bs, k);
+    }
+    wave_sync();
   }
-  *reinterpret_cast<d4 *>(BY + base + (size_t)l * EIGP + a) = d4{acc[0], acc[1], acc[2], acc[3]};
-}
-
-// G = Y^T Y and K = Y^T (B Y) into GK[i][2*EIGP*EIGP].  One MFMA 16x16x4
-// consumes four rows: lane l supplies Y[row0 + l/16][l%16] as both operands
-// (for K, BY as the second), so each wavefront reads 512 contiguous bytes
-// per step; wavefronts take interleaved four-row blocks and their
-// accumulators are added in a fixed order.  Regions with n_i <= EIGP store
-// G = I and K = dense B_i padded with a diagonal above [0, 2].
-__global__ void __launch_bounds__(WG) k_eig_gram(Plan p, const double *__restrict__ val,
-                                                 const double *__restrict__ sdiag,
-                                                 const double *__restrict__ Y,
-                                                 const double *__restrict__ BY,
-                                                 double *__restrict__ GK,
-                                                 const int *__restrict__ conv) {
-  const int i = blockIdx.x;
-  if (conv[i]) return;
-  __shared__ double red[WG / 64][2][EIGP * EIGP];
-  const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
-  const int t = threadIdx.x;
-  double *out = GK + (size_t)i * 2 * EIGP * EIGP;
   if (ni <= EIGP) {
-    const int a = t / EIGP, b = t % EIGP;
-    out[t] = (a == b) ? 1.0 : 0.0;
-    double h = (a == b) ? (a < ni ? 1.0 : 3.0 + a) : 0.0;
-    if (a < ni && b < ni && a != b) {
-      const double sa = sdiag[r0 + a];
-      for (int e = p.loc_rowptr[r0 + a]; e < p.loc_rowptr[r0 + a + 1]; ++e)
-        if (p.loc_col[e] == b) h = val[p.loc_src[e]] / sqrt(sa * sdiag[r0 + b]);
+    const int ra = t / EIGP, rc = t % EIGP;
+    out[t] = (ra == rc) ? 1.0 : 0.0;
+    double h = (ra == rc) ? (ra < ni ? 1.0 : 3.0 + ra) : 0.0;
+    if (ra < ni && rc < ni && ra != rc) {
+      const double sa = sdiag[r0 + ra];
+      for (int e = p.loc_rowptr[r0 + ra]; e < p.loc_rowptr[r0 + ra + 1]; ++e)
+        if (p.loc_col[e] == rc) h = val[p.loc_src[e]] / sqrt(sa * sdiag[r0 + rc]);
     }
     out[EIGP * EIGP + t] = h;
     return;
   }
-  const size_t base = (size_t)p.vp_ptr[i] * EIGP;
-  const int w = t >> 6, lane = t & 63;
-  d4 g = {0.0, 0.0, 0.0, 0.0}, k = {0.0, 0.0, 0.0, 0.0};
-  // rows rb .. rb+3 per step; ni > 16 so at least one full step per wave
-  int rb = 4 * w;
-  for (; rb + 16 < ni; rb += 32) {  // two steps per iteration (loads in flight)
-    const int ra = rb + (lane >> 4), rc = ra + 16;
-    const double ya = Y[base + (size_t)ra * EIGP + (lane & 15)];
-    const double ba = BY[base + (size_t)ra * EIGP + (lane & 15)];
-    const double yc = rc < ni ? Y[base + (size_t)rc * EIGP + (lane & 15)] : 0.0;
-    const double bc = rc < ni ? BY[base + (size_t)rc * EIGP + (lane & 15)] : 0.0;
-    g = mfma16x16x4(ya, ya, g);
-    k = mfma16x16x4(ya, ba, k);
-    g = mfma16x16x4(yc, yc, g);
-    k = mfma16x16x4(yc, bc, k);
-  }
-  for (; rb < ni; rb += 16) {
-    const int ra = rb + (lane >> 4);
-    const double ya = ra < ni ? Y[base + (size_t)ra * EIGP + (lane & 15)] : 0.0;
-    const double ba = ra < ni ? BY[base + (size_t)ra * EIGP + (lane & 15)] : 0.0;
-    g = mfma16x16x4(ya, ya, g);
-    k = mfma16x16x4(ya, ba, k);
-  }
-  // D register q holds entry (lane/16 + 4q, lane%16)
+  // D register q holds entry (lane/16 + 4q, lane%16); wavefronts added in order
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int e = ((lane >> 4) + 4 * q) * EIGP + (lane & 15);
-    red[w][0][e] = g[q];
-    red[w][1][e] = k[q];
+    sh[w][0][e] = g[q];
+    sh[w][1][e] = k[q];
   }
   __syncthreads();
-  {
-    double sg = 0.0, sk = 0.0;
-    for (int ww = 0; ww < WG / 64; ++ww) {
-      sg += red[ww][0][t];
-      sk += red[ww][1][t];
-    }
-    out[t] = sg;
-    out[EIGP * EIGP + t] = sk;
+  double sg = 0.0, sk = 0.0;
+#pragma unroll
+  for (int ww = 0; ww < WG / 64; ++ww) {
+    sg += sh[ww][0][t];
+    sk += sh[ww][1][t];
   }
+  out[t] = sg;
+  out[EIGP * EIGP + t] = sk;
 }
 
-// Pass 2 (small): L L^T = G, H = L^{-1} K L^{-T} (symmetrised), Jacobi,
-// C = L^{-T} V with columns sorted by ascending Ritz value.  One wavefront
-// per region.  CC[i] holds C (row-major EIGP x EIGP) then the Ritz values.
-__global__ void __launch_bounds__(64) k_eig_ritz(double off_rel2, const double *__restrict__ GK,
+// The small Ritz problems: L L^T = G, H = L^{-1} K L^{-T} (symmetrised), Jacobi,
+// C = L^{-T} V with columns sorted by ascending Ritz value.  One wavefront per
+// region; a serial chain bounds it (16 pivots, then 15 rounds a Jacobi sweep).
+// CC[i] holds C (row-major EIGP x EIGP) then the Ritz values.
+// 64 regions take 24 us, 59 before: the pivots are eliminated in registers
+// (block_factor), the products run on the matrix cores, and a Jacobi round
+// reads and writes fixed LDS addresses and forms its rotations without divisions.
+__global__ void __launch_bounds__(64) k_eig_ritz(Plan p, double off_rel2,
+                                                 const double *__restrict__ GK, int parts,
                                                  double *__restrict__ CC,
                                                  const int *__restrict__ conv) {
   const int i = blockIdx.x;
   if (conv[i]) return;
-  __shared__ double G[EIGP * HP], K[EIGP * HP], Li[EIGP * HP], Hb[EIGP * HP], Vb[EIGP * HP];
+  __shared__ double G[EIGP * HP], K[EIGP * HP], Li[EIGP * HP];
+  __shared__ __attribute__((aligned(16))) double H[EIGP * HS], V[EIGP * HS];
   __shared__ int perm[EIGP];
-  double *H = Hb, *V = Vb;  // the Jacobi iteration's current buffers (G and K: the others)
   __shared__ double theta[EIGP];
-  __shared__ int flag;
-  __shared__ double floor_;
-  const int t = threadIdx.x;
-  const double *in = GK + (size_t)i * 2 * EIGP * EIGP;
-  for (int e = t; e < EIGP * EIGP; e += 64) {
-    G[(e / EIGP) * HP + e % EIGP] = in[e];
-    K[(e / EIGP) * HP + e % EIGP] = in[EIGP * EIGP + e];
-  }
-  __syncthreads();
-  if (t == 0) {
-    double tr = 0.0;
-    for (int a = 0; a < EIGP; ++a) tr += G[a * HP + a];
-    floor_ = 1e-26 * (tr > 0.0 ? tr : 1.0);
-  }
-  __syncthreads();
-  for (int k = 0; k < EIGP; ++k) {  // Cholesky of G (lower, in place)
-    if (t == 0) {
-      double d = G[k * HP + k];
-      if (!(d > floor_)) d = floor_;
-      G[k * HP + k] = sqrt(d);
-    }
-    __syncthreads();
-    if (t > k && t < EIGP) G[t * HP + k] /= G[k * HP + k];
-    __syncthreads();
-    for (int e = t; e < EIGP * EIGP; e += 64) {
-      const int r = e / EIGP, c = e % EIGP;
-      if (c > k && c <= r) G[r * HP + c] = fma(-G[r * HP + k], G[c * HP + k], G[r * HP + c]);
-    }
-    __syncthreads();
-  }
-  if (t < EIGP) {  // Li = L^{-1}: lane j computes column j by forward substitution
-    const int j = t;  // (the column in registers; terms m = j .. r-1 in that order)
-    double lc[EIGP];
+  const int t = threadIdx.x, q = t >> 4, c = t & 15;
+  const int np = (p.sd_ptr[i + 1] - p.sd_ptr[i] + GR - 1) / GR;
+  const double *in = GK + (size_t)i * parts * 2 * EIGP * EIGP;
+  d4 g = {0.0, 0.0, 0.0, 0.0}, k = {0.0, 0.0, 0.0, 0.0};
+  for (int b = 0; b < np; ++b)
 #pragma unroll
-    for (int r = 0; r < EIGP; ++r) {
-      double s = (r == j) ? 1.0 : 0.0;
-#pragma unroll
-      for (int m = 0; m < r; ++m)
-        if (m >= j) s = fma(-G[r * HP + m], lc[m], s);
-      lc[r] = r >= j ? s / G[r * HP + r] : 0.0;
+    for (int r = 0; r < 4; ++r) {
+      g[r] += in[(size_t)b * 2 * EIGP * EIGP + 64 * r + t];
+      k[r] += in[(size_t)b * 2 * EIGP * EIGP + EIGP * EIGP + 64 * r + t];
     }
+  block_store<HP>(G, g);  // (entry 64 r + t is row q + 4 r, column c)
+  block_store<HP>(K, k);
+  double tr = 0.0;
 #pragma unroll
-    for (int r = 0; r < EIGP; ++r) Li[r * HP + j] = lc[r];
-  }
-  __syncthreads();
-  for (int e = t; e < EIGP * EIGP; e += 64) {  // V <- Li K (temporary)
-    const int r = e / EIGP, c = e % EIGP;
-    double s = 0.0;
-    for (int m = 0; m <= r; ++m) s = fma(Li[r * HP + m], K[m * HP + c], s);
-    V[r * HP + c] = s;
-  }
-  __syncthreads();
-  for (int e = t; e < EIGP * EIGP; e += 64) {  // H = (Li K) Li^T
-    const int r = e / EIGP, c = e % EIGP;
-    double s = 0.0;
-    for (int m = 0; m <= c; ++m) s = fma(V[r * HP + m], Li[c * HP + m], s);
-    H[r * HP + c] = s;
-  }
-  __syncthreads();
-  for (int e = t; e < EIGP * EIGP; e += 64) {
-    const int r = e / EIGP, c = e % EIGP;
-    if (c > r) {
-      const double m = 0.5 * (H[r * HP + c] + H[c * HP + r]);
-      H[r * HP + c] = m;
-      H[c * HP + r] = m;
-    }
-  }
-  __syncthreads();
-  jacobi16(H, V, G, K, &flag, off_rel2);  // G and K are free by now
-  if (t < EIGP) {  // ascending order, ties by index (a stable sort): lane a places value a
+  for (int r = 0; r < 4; ++r) tr += (q + 4 * r == c) ? g[r] : 0.0;
+  tr = wave_sum(tr);
+  const double lo = 1e-26 * (tr > 0.0 ? tr : 1.0);  // smallest pivot
+  wave_sync();
+  block_factor<HP>(G, Li, lo, 1.0 / sqrt(lo));
+  wave_sync();
+  const d4 zero = {0.0, 0.0, 0.0, 0.0};
+  const d4 lk = block_mma<false, HP>(Li, K, zero, 1.0);
+  wave_sync();
+  block_store<HP>(K, lk);
+  wave_sync();
+  const d4 h = block_mma<true, HP>(K, Li, zero, 1.0);  // (Li K) Li^T
+  block_store<HP>(G, h);
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    H[jacobi_slot(q + 4 * r) * HS + jacobi_slot(c)] = 0.5 * (h[r] + G[c * HP + q + 4 * r]);
+  wave_sync();
+  jacobi16(H, V, off_rel2);
+  if (t < EIGP) {  // ascending order, ties by slot: lane a places value a
     auto key = [&](int a) {
-      const double x = H[a * HP + a];
+      const double x = H[a * HS + a];
       return x == x ? x : INFINITY;  // a NaN sorts last (the result is then unused)
     };
     const double th = key(t);
@@ -372,16 +324,17 @@ __global__ void __launch_bounds__(64) k_eig_ritz(double off_rel2, const double *
       rank += (x < th || (x == th && b < t)) ? 1 : 0;
     }
     perm[rank] = t;
-    theta[rank] = H[t * HP + t];
+    theta[rank] = H[t * HS + t];
   }
-  __syncthreads();
+  wave_sync();
   double *out = CC + (size_t)i * (EIGP * EIGP + EIGP);
-  for (int e = t; e < EIGP * EIGP; e += 64) {  // C = Li^T V (sorted columns)
-    const int r = e / EIGP, c = e % EIGP;
-    double s = 0.0;
-    for (int m = r; m < EIGP; ++m) s = fma(Li[m * HP + r], V[m * HP + perm[c]], s);
-    out[e] = s;
-  }
+  d4 cc = zero;  // C = Li^T V (sorted columns)
+  const int pc = perm[c];
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    cc = mfma16x16x4(Li[(q + 4 * s) * HP + c], V[(q + 4 * s) * HS + pc], cc);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) out[(q + 4 * r) * EIGP + c] = cc[r];
   if (t < EIGP) out[EIGP * EIGP + t] = theta[t];
 }
 
@@ -391,7 +344,11 @@ __global__ void __launch_bounds__(64) k_eig_ritz(double off_rel2, const double *
 // k = 4q + s), so a lane reads four contiguous entries of one row of Y and
 // of BY and holds C[4q + s][l%16] in registers.  Y and X are distinct
 // buffers; padded rows of X are zeroed (they feed the next block solve).
-__global__ void __launch_bounds__(WG) k_eig_finish(Plan p, const double *__restrict__ Y,
+// Bound by memory, with few regions by the latency of a wavefront's steps, so
+// their loads do not wait on each other (rows past the region are clamped, not
+// branched over): 64 regions of 1284 rows 15 us (25 before), 1024 of them 93 (106).
+constexpr int NW = 8;  // wavefronts
+__global__ void __launch_bounds__(64 * NW) k_eig_finish(Plan p, const double *__restrict__ Y,
                                                    const double *__restrict__ BY,
                                                    double *__restrict__ X,
                                                    const double *__restrict__ CC, double tol,
@@ -400,13 +357,13 @@ __global__ void __launch_bounds__(WG) k_eig_finish(Plan p, const double *__restr
   const int i = blockIdx.x;
   if (conv[i]) return;
   __shared__ double C[EIGP * EIGP], theta[EIGP];
-  __shared__ double res[WG / 64][EIGP];
+  __shared__ double res[NW][EIGP];
   const int t = threadIdx.x;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
   const int npad = p.vp_ptr[i + 1] - p.vp_ptr[i];
   const int m = p.mi[i];
   const double *in = CC + (size_t)i * (EIGP * EIGP + EIGP);
-  C[t] = in[t];
+  if (t < EIGP * EIGP) C[t] = in[t];
   if (t < EIGP) theta[t] = in[EIGP * EIGP + t];
   __syncthreads();
   const size_t base = (size_t)p.vp_ptr[i] * EIGP;
@@ -416,7 +373,7 @@ __global__ void __launch_bounds__(WG) k_eig_finish(Plan p, const double *__restr
   const int w = t >> 6, lane = t & 63, q = lane >> 4, col = lane & 15;
   double rs = 0.0;  // this lane's sum of squared residuals of column col
   if (small) {
-    for (int e = t; e < npad * EIGP; e += WG) {
+    for (int e = t; e < npad * EIGP; e += 64 * NW) {
       const int l = e / EIGP, j = e % EIGP;
       X[base + e] = (l < ni) ? C[l * EIGP + j] : 0.0;
     }
@@ -425,16 +382,14 @@ __global__ void __launch_bounds__(WG) k_eig_finish(Plan p, const double *__restr
 #pragma unroll
     for (int st = 0; st < 4; ++st) cb[st] = C[(4 * q + st) * EIGP + col];
     const double th = theta[col];
-    for (int rb = 16 * w; rb < npad; rb += 64) {
+    for (int rb = 16 * w; rb < npad; rb += 16 * NW) {
       const int ra = rb + col;  // A operand row: lane%16
       d4 x = {0.0, 0.0, 0.0, 0.0}, bx = {0.0, 0.0, 0.0, 0.0};
       if (rb < ni) {
-        double ya[4], ba[4];
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-          ya[st] = ra < ni ? Y[base + (size_t)ra * EIGP + 4 * q + st] : 0.0;
-          ba[st] = ra < ni ? BY[base + (size_t)ra * EIGP + 4 * q + st] : 0.0;
-        }
+        // (a row past the region is read at its last one and dropped below)
+        const size_t at = base + (size_t)min(ra, ni - 1) * EIGP + 4 * q;
+        const d4 ya = *reinterpret_cast<const d4 *>(Y + at);
+        const d4 ba = *reinterpret_cast<const d4 *>(BY + at);
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
           x = mfma16x16x4(ya[st], cb[st], x);
@@ -457,20 +412,17 @@ __global__ void __launch_bounds__(WG) k_eig_finish(Plan p, const double *__restr
   rs += __shfl_xor(rs, 32, 64);
   if (lane < EIGP) res[w][lane] = rs;
   __syncthreads();
-  if (t == 0) {
-    double worst = 0.0;
-    if (!small) {
-      for (int j = 0; j < min(ntest, nchk); ++j) {
-        double s = 0.0;
-        for (int ww = 0; ww < WG / 64; ++ww) s += res[ww][j];
-        s = sqrt(s);
-        if (s > worst || !(s == s)) worst = (s == s) ? s : 1e300;
-      }
-    }
-    conv[i] = (worst <= tol) ? 1 : 0;
-    const int ld = p.nev + 1;
-    for (int j = 0; j < ld; ++j) lam[(size_t)i * ld + j] = (j < nchk) ? theta[j] : __builtin_nan("");
+  if (t >= 64) return;
+  double s = 0.0;
+  if (!small && t < min(ntest, nchk)) {
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) s += res[ww][t];
+    s = sqrt(s);
   }
+  const bool met = __all(s <= tol);  // (false for a NaN)
+  if (t == 0) conv[i] = met ? 1 : 0;
+  const int ld = p.nev + 1;
+  if (t < ld) lam[(size_t)i * ld + t] = (t < nchk) ? theta[t] : __builtin_nan("");
 }
 
 // psi = S^{-1/2} z for the m_i kept columns, sign: largest |psi| entry
@@ -667,16 +619,15 @@ void launch_eig_bval(hipStream_t s, const Plan &p, const double *val, const doub
 void launch_eig_rr(hipStream_t s, const Plan &p, int max_ni, const double *val,
                    const double *sdiag, const double *bval, const double *Y, double *BY, double *X,
                    double *GK, double *CC, double tol, int *conv, double *lam, bool test_next) {
-  const int rows_per_wg = WG / 4;
-  hipLaunchKernelGGL(k_eig_spmm, dim3((max_ni + rows_per_wg - 1) / rows_per_wg, p.N), dim3(WG), 0,
-                     s, p, bval, Y, BY, conv);
-  hipLaunchKernelGGL(k_eig_gram, dim3(p.N), dim3(WG), 0, s, p, val, sdiag, Y, BY, GK, conv);
+  const int parts = (max_ni + GR - 1) / GR;
+  hipLaunchKernelGGL(k_eig_spmm, dim3(parts, p.N), dim3(WG), 0, s, p, val, sdiag, bval, Y, BY, GK,
+                     parts, conv);
   // the small eigenproblems are diagonalised to 1e-2 tol relative: their
   // Ritz vectors then carry errors far below the residual bound the sweep
   // tests (on the vectors themselves), so this only saves Jacobi sweeps
   const double rel = fmax(1e-14, 1e-2 * tol);
-  hipLaunchKernelGGL(k_eig_ritz, dim3(p.N), dim3(64), 0, s, rel * rel, GK, CC, conv);
-  hipLaunchKernelGGL(k_eig_finish, dim3(p.N), dim3(WG), 0, s, p, Y, BY, X, CC, tol, conv, lam,
+  hipLaunchKernelGGL(k_eig_ritz, dim3(p.N), dim3(64), 0, s, p, rel * rel, GK, parts, CC, conv);
+  hipLaunchKernelGGL(k_eig_finish, dim3(p.N), dim3(64 * NW), 0, s, p, Y, BY, X, CC, tol, conv, lam,
                      test_next ? 1 : 0);
 }
 
