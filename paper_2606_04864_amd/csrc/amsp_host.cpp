@@ -1027,15 +1027,20 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
       h->mem.free_one(alpha);
     }
     double t5 = now_ms();
-    // Tiled right-looking Cholesky with lookahead.  Main stream: diagonal
-    // factor, panel, then the update of the next tile column only, so the
-    // next diagonal step can start while a second stream applies the rest of
-    // the trailing update.  A third stream forms the inverse factor
-    // W0 = inv(L0) by a right-looking solve of L0 X = I; its step k needs
-    // only column k of L0, final once the panel of step k is done.
-    //   main:  trsm(k) [panel] ... wait [rest of k-1] next(k)+potrf(k+1)
-    //   bulk:  wait [panel] rest(k) [rest]
-    //   inv:   wait [panel] inv_row(k) inv_update(k)
+    // Tiled right-looking Cholesky with lookahead, two tile columns a step (the
+    // trailing update is bound by reading and writing every remaining tile).
+    // Main stream: diagonal factor and panel of columns k and k + 1, each behind
+    // its own column's update, so the next step's columns are ready while a
+    // second stream applies the rest of the trailing update (columns k + 4 on).
+    // A third stream forms the inverse factor W0 = inv(L0) by a right-looking
+    // solve of L0 X = I; its step needs only columns k and k + 1 of L0, final
+    // once their panels are done.
+    //   main:  trsm(k) next(k+1) trsm(k+1) [panel] ... wait [rest of k-2] next(k+2)
+    //   bulk:  wait [panel] rest(k, k+1) [rest]
+    //   inv:   wait [panel] inv_rows(k, k+1) inv_update(k, k+1)
+    // 96 tile columns take 6.0 ms, 7.2 with one column a step.  (7.7 with the
+    // inverse behind the factorisation: next(k) is then faster, 22 us instead of
+    // 29, but nothing runs beside it.)
     ALLOC(h->W0, double, (size_t)T0 * T0 * TE);
     SideStream bulk, inv;
     HIP_TRY(bulk.create());
@@ -1046,19 +1051,23 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
     HIP_TRY(hipStreamWaitEvent(bulk.s, ev_panel, 0));
     HIP_TRY(hipEventRecord(ev_rest, bulk.s));
     launch_tiles_identity(inv.s, h->W0, T0);
-    // the diagonal factor of step k + 1 runs in the same launch as step k's
-    // update of column k + 1 (launch_dense_next_potrf)
+    // a column's diagonal factor runs in the same launch as its update
     launch_dense_potrf_diag(h->stream, A0t, T0, 0, dinv, cstat);
-    for (int k = 0; k < T0; ++k) {
+    for (int k = 0; k < T0; k += 2) {
+      const int nk = std::min(2, T0 - k);
       launch_dense_trsm_panel(h->stream, A0t, T0, k, dinv);
+      if (nk == 2) {
+        launch_dense_next_potrf(h->stream, A0t, T0, std::max(k - 2, 0), k + 1, dinv, cstat);
+        launch_dense_trsm_panel(h->stream, A0t, T0, k + 1, dinv);
+      }
       HIP_TRY(hipEventRecord(ev_panel, h->stream));
       HIP_TRY(hipStreamWaitEvent(inv.s, ev_panel, 0));
-      launch_dense_inv_row(inv.s, h->W0, T0, k, dinv);
-      launch_dense_inv_update(inv.s, A0t, h->W0, T0, k);
-      HIP_TRY(hipStreamWaitEvent(h->stream, ev_rest, 0));  // rest of step k-1
-      launch_dense_next_potrf(h->stream, A0t, T0, k, dinv, cstat);
+      launch_dense_inv_rows(inv.s, A0t, h->W0, T0, k, nk, dinv);
+      launch_dense_inv_update(inv.s, A0t, h->W0, T0, k, nk);
+      HIP_TRY(hipStreamWaitEvent(h->stream, ev_rest, 0));  // rest of step k-2
+      launch_dense_next_potrf(h->stream, A0t, T0, k, k + 2, dinv, cstat);
       HIP_TRY(hipStreamWaitEvent(bulk.s, ev_panel, 0));
-      launch_dense_syrk_rest(bulk.s, A0t, T0, k);
+      launch_dense_syrk_rest(bulk.s, A0t, T0, k, nk, k + 4);
       HIP_TRY(hipEventRecord(ev_rest, bulk.s));
     }
     HIP_TRY(hipEventRecord(ev_inv, inv.s));

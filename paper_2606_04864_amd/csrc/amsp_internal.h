@@ -276,15 +276,16 @@ void launch_singular_regularize(hipStream_t s, const Plan &p, const double *phi,
                                 int T0, int nc, double *u, double *alpha);
 void launch_dense_potrf_diag(hipStream_t s, double *A0t, int T0, int k, double *dinv, int *status);
 void launch_dense_trsm_panel(hipStream_t s, double *A0t, int T0, int k, const double *dinv);
-// Trailing update of Cholesky step k split for lookahead: the next tile
-// column (j = k + 1), in one launch with step k + 1's diagonal factor (the
-// next diagonal tile is factored by the workgroup that updates it), and the
-// rest (j >= k + 2).
-void launch_dense_next_potrf(hipStream_t s, double *A0t, int T0, int k, double *dinv,
+// Updates of the blocked Cholesky, split for lookahead: tile column j with the
+// columns k .. j - 1, in one launch with its diagonal factor (by the workgroup
+// that updates the diagonal tile), and the columns j0 .. with the nk columns
+// from k on.
+void launch_dense_next_potrf(hipStream_t s, double *A0t, int T0, int k, int j, double *dinv,
                              int *status);
-void launch_dense_syrk_rest(hipStream_t s, double *A0t, int T0, int k);
-void launch_dense_inv_row(hipStream_t s, double *Wt, int T0, int k, const double *dinv);
-void launch_dense_inv_update(hipStream_t s, const double *Lt, double *Wt, int T0, int k);
+void launch_dense_syrk_rest(hipStream_t s, double *A0t, int T0, int k, int nk, int j0);
+void launch_dense_inv_rows(hipStream_t s, const double *Lt, double *Wt, int T0, int k, int nk,
+                           const double *dinv);
+void launch_dense_inv_update(hipStream_t s, const double *Lt, double *Wt, int T0, int k, int nk);
 void launch_tiles_identity(hipStream_t s, double *Wt, int T0);
 void launch_dense_tiles_to_f32(hipStream_t s, const double *src, float *dst, int T0);
 // y = W x (transpose 0) or W^T x (transpose 1) over the lower tiles of W;

@@ -200,56 +200,80 @@ __global__ void __launch_bounds__(WG) k_dense_trsm_panel(double *A0t, int T0, in
   acc_store(o, a);
 }
 
-// A_ij -= L_ik L_jk^T over the tiles j0 <= j <= i (tri = 1), or over the
-// single tile column j = j0, i >= j0 (tri = 0).
-__global__ void __launch_bounds__(WG) k_dense_syrk_update(double *A0t, int T0, int k, int j0,
-                                                          int tri) {
-  const int b = blockIdx.x;
-  int ii = b, jj = 0;
-  if (!tri) __builtin_amdgcn_s_setprio(3);  // next tile column: critical path
-  if (tri) {
-    ii = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
-    while ((ii + 1) * (ii + 2) / 2 <= b) ++ii;
-    while (ii * (ii + 1) / 2 > b) --ii;
-    jj = b - ii * (ii + 1) / 2;
+// The trailing update and the inverse read and write every remaining tile once
+// per launch and are bound by that traffic, so each launch applies two tile
+// columns (K = 128): tile (i, j) -= sum over k .. k + nk - 1 of L_ik L_jk^T, in
+// that order.  The next column's tile is fetched while the current one is
+// multiplied.
+// c -= sum over kk of X(kk) Y(kk)^T (AB: X(kk) Y(kk)); Y staged in Ly, which
+// every wavefront reads whole.  Ends without a barrier.
+template <bool AB, typename FX, typename FY>
+__device__ __forceinline__ void acc_update(Acc4 &c, int nk, FX &&x, FY &&y, double *Ly) {
+  double f[TE / WG];
+  auto fetch = [&](int kk) {
+    const double *g = y(kk);
+#pragma unroll
+    for (int u = 0; u < TE / WG; ++u) f[u] = g[u * WG + threadIdx.x];
+  };
+  fetch(0);
+  for (int kk = 0; kk < nk; ++kk) {
+    if (kk) __syncthreads();  // Ly read by every wavefront
+#pragma unroll
+    for (int u = 0; u < TE / WG; ++u) {
+      const int e = u * WG + threadIdx.x;
+      Ly[(e >> 6) * LDT + (e & 63)] = f[u];
+    }
+    __syncthreads();
+    if (kk + 1 < nk) fetch(kk + 1);
+    if (AB)
+      acc_mma_ab(c, x(kk), TS, Ly, LDT, -1.0);
+    else
+      acc_mma_abt(c, x(kk), TS, Ly, LDT, -1.0);
   }
-  const int i = j0 + ii, j = j0 + jj;
-  // every wavefront multiplies by the whole L_jk: stage it once in LDS
+}
+
+// A_ij -= sum over kk of L_ik L_jk^T for the tiles j0 <= j <= i.  Over the 96
+// steps of a 6144-row matrix this and the inverse's update, side by side, took
+// 3.6 and 3.5 ms with one column a launch, now 2.8 and 2.5.
+__global__ void __launch_bounds__(WG) k_dense_syrk_update(double *A0t, int T0, int k, int nk,
+                                                          int j0) {
+  const int b = blockIdx.x;
+  int ii = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
+  while ((ii + 1) * (ii + 2) / 2 <= b) ++ii;
+  while (ii * (ii + 1) / 2 > b) --ii;
+  const int i = j0 + ii, j = j0 + b - ii * (ii + 1) / 2;
   __shared__ double Ly[TS * LDT];
-  tile_to_lds(tile_ptr(A0t, T0, j, k), Ly);
   double *c = tile_ptr(A0t, T0, i, j);
   Acc4 o;
   acc_load(o, c);
-  __syncthreads();
-  acc_mma_abt(o, tile_ptr(A0t, T0, i, k), TS, Ly, LDT, -1.0);
+  acc_update<false>(o, nk, [&](int kk) { return tile_ptr(A0t, T0, i, k + kk); },
+                    [&](int kk) { return tile_ptr(A0t, T0, j, k + kk); }, Ly);
   acc_store(o, c);
 }
 
-// Step k's update of the next tile column, fused with step k+1's diagonal
-// factor: tile (k+1+b, k+1) -= L_{k+1+b,k} L_{k+1,k}^T for every b (as
-// k_dense_syrk_update over that column); workgroup 0 holds the next diagonal
-// tile, which it then factors in LDS as k_dense_potrf_diag does (L in place,
-// its inverse in dinv).  One launch and one launch gap less per step on the
-// critical path.
+// Update of tile column j with the columns k .. j - 1 that no trailing update
+// covers, fused with its diagonal factor: tile (j + b, j) for every b (as
+// k_dense_syrk_update); workgroup 0 holds the diagonal tile, which it then
+// factors in LDS as k_dense_potrf_diag does (L in place, its inverse in dinv).
+// One launch and one launch gap less per step on the critical path.
 __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_dense_next_potrf(double *A0t, int T0, int k, double *dinv, int *status) {
+k_dense_next_potrf(double *A0t, int T0, int k, int j, double *dinv, int *status) {
   extern __shared__ double lds[];
   double *Ly = lds, *Y = lds + TS * LDT;  // Ly then holds the tile to factor
   __shared__ int fail;
-  const int b = blockIdx.x, j = k + 1, i = j + b;
+  const int b = blockIdx.x, i = j + b;
   __builtin_amdgcn_s_setprio(3);  // critical path
   if (threadIdx.x == 0) fail = 0;
-  tile_to_lds(tile_ptr(A0t, T0, j, k), Ly);
   double *c = tile_ptr(A0t, T0, i, j);
   Acc4 o;
   acc_load(o, c);
-  __syncthreads();
-  acc_mma_abt(o, tile_ptr(A0t, T0, i, k), TS, Ly, LDT, -1.0);
+  acc_update<false>(o, j - k, [&](int kk) { return tile_ptr(A0t, T0, i, k + kk); },
+                    [&](int kk) { return tile_ptr(A0t, T0, j, k + kk); }, Ly);
   if (b != 0) {  // uniform over the workgroup
     acc_store(o, c);
     return;
   }
-  __syncthreads();  // every wavefront has finished reading L_{k+1,k}
+  __syncthreads();  // every wavefront has finished reading L_{j,j-1}
   acc_to_lds(o, Ly);
   __syncthreads();
   lds_potrf_trtri(Ly, Y, &fail);
@@ -259,34 +283,53 @@ k_dense_next_potrf(double *A0t, int T0, int k, double *dinv, int *status) {
   if (threadIdx.x == 0 && fail) *status |= 1;
 }
 
-// Inverse factor by a right-looking solve of L X = I, step k:
-//   row k:   X_kj <- inv(L_kk) B_kj  (j <= k)
-//   update:  B_ij -= L_ik X_kj        (i > k, j <= k)
-__global__ void __launch_bounds__(WG) k_dense_inv_row(double *Wt, int T0, int k,
-                                                      const double *dinv) {
+// Inverse factor by a right-looking solve of L X = I, two rows a launch:
+//   rows k, k + 1:  X_kj <- inv(L_kk) B_kj  (j <= k), B_{k+1,j} -= L_{k+1,k} X_kj,
+//                   X_{k+1,j} <- inv(L_{k+1,k+1}) B_{k+1,j}  (j <= k + 1)
+//   update:         B_ij -= sum of L_ik X_kj over the two  (i > k + 1)
+__global__ void __launch_bounds__(WG) k_dense_inv_rows(const double *Lt, double *Wt, int T0, int k,
+                                                       int nk, const double *dinv) {
   extern __shared__ double lds[];
-  const int j = blockIdx.x;  // 0..k
-  double *w = tile_ptr(Wt, T0, k, j);
-  tile_to_lds(w, lds);
-  __syncthreads();
+  const int j = blockIdx.x;  // 0 .. k + nk - 1
   Acc4 o;
+  if (j <= k) {
+    double *w = tile_ptr(Wt, T0, k, j);
+    tile_to_lds(w, lds);
+    __syncthreads();
+    acc_zero(o);
+    acc_mma_ab(o, dinv + (size_t)k * TE, TS, lds, LDT, 1.0);
+    acc_store(o, w);
+  }
+  if (nk < 2) return;
+  double *w = tile_ptr(Wt, T0, k + 1, j);
+  if (j <= k) {
+    __syncthreads();  // lds read by every wavefront
+    acc_to_lds(o, lds);
+    acc_load(o, w);
+    __syncthreads();
+    acc_mma_ab(o, Lt + ((size_t)(k + 1) * T0 + k) * TE, TS, lds, LDT, -1.0);
+    __syncthreads();
+    acc_to_lds(o, lds);
+  } else {
+    tile_to_lds(w, lds);
+  }
+  __syncthreads();
   acc_zero(o);
-  acc_mma_ab(o, dinv + (size_t)k * TE, TS, lds, LDT, 1.0);
+  acc_mma_ab(o, dinv + (size_t)(k + 1) * TE, TS, lds, LDT, 1.0);
   acc_store(o, w);
 }
 
 __global__ void __launch_bounds__(WG) k_dense_inv_update(const double *Lt, double *Wt, int T0,
-                                                         int k) {
-  const int i = k + 1 + blockIdx.x / (k + 1);
-  const int j = blockIdx.x % (k + 1);
-  // every wavefront multiplies by the whole X_kj: stage it once in LDS
+                                                         int k, int nk) {
+  const int i = k + nk + blockIdx.x / (k + nk);
+  const int j = blockIdx.x % (k + nk), k0 = max(k, j);  // (X_kj = 0 for j > k)
   __shared__ double Xk[TS * LDT];
-  tile_to_lds(Wt + ((size_t)k * T0 + j) * TE, Xk);
   double *c = tile_ptr(Wt, T0, i, j);
   Acc4 o;
   acc_load(o, c);
-  __syncthreads();
-  acc_mma_ab(o, Lt + ((size_t)i * T0 + k) * TE, TS, Xk, LDT, -1.0);
+  acc_update<true>(o, k + nk - k0,
+                   [&](int kk) { return Lt + ((size_t)i * T0 + k0 + kk) * TE; },
+                   [&](int kk) { return Wt + ((size_t)(k0 + kk) * T0 + j) * TE; }, Xk);
   acc_store(o, c);
 }
 
@@ -420,30 +463,31 @@ void launch_dense_trsm_panel(hipStream_t s, double *A0t, int T0, int k, const do
   hipLaunchKernelGGL(k_dense_trsm_panel, dim3(nb), dim3(WG), 0, s, A0t, T0, k, dinv);
 }
 
-void launch_dense_next_potrf(hipStream_t s, double *A0t, int T0, int k, double *dinv,
+void launch_dense_next_potrf(hipStream_t s, double *A0t, int T0, int k, int j, double *dinv,
                              int *status) {
-  const int m = T0 - k - 1;
-  if (m <= 0) return;
+  if (j >= T0) return;
   allow_lds(k_dense_next_potrf, two_tiles_lds());
-  hipLaunchKernelGGL(k_dense_next_potrf, dim3(m), dim3(WG), two_tiles_lds(), s, A0t, T0, k, dinv,
-                     status);
+  hipLaunchKernelGGL(k_dense_next_potrf, dim3(T0 - j), dim3(WG), two_tiles_lds(), s, A0t, T0, k, j,
+                     dinv, status);
 }
 
-void launch_dense_syrk_rest(hipStream_t s, double *A0t, int T0, int k) {
-  const int m = T0 - k - 2;
+void launch_dense_syrk_rest(hipStream_t s, double *A0t, int T0, int k, int nk, int j0) {
+  const int m = T0 - j0;
   if (m <= 0) return;
-  hipLaunchKernelGGL(k_dense_syrk_update, dim3(m * (m + 1) / 2), dim3(WG), 0, s, A0t, T0, k, k + 2,
-                     1);
+  hipLaunchKernelGGL(k_dense_syrk_update, dim3(m * (m + 1) / 2), dim3(WG), 0, s, A0t, T0, k, nk,
+                     j0);
 }
 
-void launch_dense_inv_row(hipStream_t s, double *Wt, int T0, int k, const double *dinv) {
-  hipLaunchKernelGGL(k_dense_inv_row, dim3(k + 1), dim3(WG), one_tile_lds(), s, Wt, T0, k, dinv);
+void launch_dense_inv_rows(hipStream_t s, const double *Lt, double *Wt, int T0, int k, int nk,
+                           const double *dinv) {
+  hipLaunchKernelGGL(k_dense_inv_rows, dim3(k + nk), dim3(WG), one_tile_lds(), s, Lt, Wt, T0, k,
+                     nk, dinv);
 }
 
-void launch_dense_inv_update(hipStream_t s, const double *Lt, double *Wt, int T0, int k) {
-  const int m = T0 - k - 1;
+void launch_dense_inv_update(hipStream_t s, const double *Lt, double *Wt, int T0, int k, int nk) {
+  const int m = T0 - k - nk;
   if (m <= 0) return;
-  hipLaunchKernelGGL(k_dense_inv_update, dim3(m * (k + 1)), dim3(WG), 0, s, Lt, Wt, T0, k);
+  hipLaunchKernelGGL(k_dense_inv_update, dim3(m * (k + nk)), dim3(WG), 0, s, Lt, Wt, T0, k, nk);
 }
 
 void launch_tiles_identity(hipStream_t s, double *Wt, int T0) {
