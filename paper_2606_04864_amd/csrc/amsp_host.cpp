@@ -1179,7 +1179,7 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
   HIP_TRY(hipMemsetAsync(h->cvec, 0, ncp * sizeof(double), h->stream));
   HIP_TRY(hipMemsetAsync(h->t1, 0, ncp * sizeof(double), h->stream));
   HIP_TRY(hipMemsetAsync(h->tvec, 0, ncp * sizeof(double), h->stream));
-  ALLOC(h->trmv_part, double, h->tree ? 1 : (size_t)std::max(1, T0 * T0) * TS);
+  ALLOC(h->trmv_part, double, h->tree ? 1 : (size_t)std::max(1, T0 * (T0 + 1)) * TS);
   ALLOC(h->r, double, h->n);
   if (h->opt.cycle == 1) {
     ALLOC(h->mq, double, h->n);
@@ -1396,11 +1396,11 @@ static amsp_status apply_one(amsp_handle *h, const double *r, double *z, int par
     if (h->tree) {
       coarse_solve_tree(h, h->stream, h->cvec, h->tvec, done);
     } else if (!mixed) {
-      launch_trmv<double>(h->stream, h->W0, h->T0, h->cvec, h->trmv_part, h->t1, 0, done);
-      launch_trmv<double>(h->stream, h->W0, h->T0, h->t1, h->trmv_part, t2, 1, done);
+      launch_coarse_products<double>(h->stream, h->W0, h->T0, h->cvec, h->trmv_part, h->t1, t2,
+                                     done);
     } else {
-      launch_trmv<float>(h->stream, h->W0f, h->T0, h->cvec, h->trmv_part, h->t1, 0, done);
-      launch_trmv<float>(h->stream, h->W0f, h->T0, h->t1, h->trmv_part, t2, 1, done);
+      launch_coarse_products<float>(h->stream, h->W0f, h->T0, h->cvec, h->trmv_part, h->t1, t2,
+                                    done);
     }
     tstop(h, 2, tk);
   }
@@ -2330,12 +2330,9 @@ extern "C" amsp_status amsp_gmres(amsp_handle *h, const double *f_dev, double *u
     amsp_status st = apply_prec(h, vj, zj, nullptr, nullptr);
     if (st != AMSP_OK) return st;
     launch_spmv_sell(s, n, h->sptr, h->scol, h->sval, zj, w);
-    launch_gs_dots(s, n, V, ld, j + 1, w, part, sc);
-    launch_gs_update(s, n, V, ld, j + 1, sc, w, nullptr);
-    launch_gs_dots(s, n, V, ld, j + 1, w, part, sc + 64);
-    launch_gs_update(s, n, V, ld, j + 1, sc + 64, w, pn);
-    launch_sum_partials(s, pn, nb, sc + 128);
-    launch_gs_normalize(s, n, w, sc + 128, V + (size_t)(j + 1) * ld);
+    launch_gs_round(s, n, V, ld, j + 1, w, part, sc, nullptr);
+    launch_gs_round(s, n, V, ld, j + 1, w, part, sc + 64, pn);
+    launch_gs_normalize(s, n, w, sc + 128, pn, V + (size_t)(j + 1) * ld);
     HIP_TRY(hipMemcpyAsync(h->gm_host + (j & 1) * 129, sc, 129 * sizeof(double),
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipEventRecord(h->gm_ev[j & 1], s));
@@ -2362,7 +2359,7 @@ extern "C" amsp_status amsp_gmres(amsp_handle *h, const double *f_dev, double *u
     int it = 0, cycles = 0;
     bool conv = nf == 0.0;
     while (!conv && it < maxit) {
-      launch_gs_normalize(s, n, h->r, sc + 128, V);  // v_0 = r / beta
+      launch_gs_normalize(s, n, h->r, sc + 128, nullptr, V);  // v_0 = r / beta
       std::fill(g.begin(), g.end(), 0.0);
       g[0] = beta;
       int k = 0;

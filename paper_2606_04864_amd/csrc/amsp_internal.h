@@ -88,14 +88,14 @@ void launch_residual(hipStream_t s, int n, const double *f, const double *Ax, do
                      double *partial);
 void launch_copy_scale(hipStream_t s, int n, const double *a, double *b, double alpha);
 // GMRES (restarted, flexible right preconditioning) building blocks.  The
-// basis columns are V + k * ldv.  out[k] = V_k . w for k < k1 (part holds
-// k1 * reduce_blocks(n) partials); w -= V h with optional w.w partials;
-// v = w / sqrt(*nrm2); x += Z y.
-void launch_gs_dots(hipStream_t s, int n, const double *V, size_t ldv, int k1, const double *w,
-                    double *part, double *out);
-void launch_gs_update(hipStream_t s, int n, const double *V, size_t ldv, int k1, const double *h,
-                      double *w, double *part);
-void launch_gs_normalize(hipStream_t s, int n, const double *w, const double *nrm2, double *v);
+// basis columns are V + k * ldv.  One Gram-Schmidt round: out[k] = V_k . w for
+// k < k1 (part holds k1 * reduce_blocks(n) partials), w -= V out, with optional
+// w.w partials in nrm; v = w / sqrt(*nrm2), *nrm2 summed from part first unless
+// that is null; x += Z y.
+void launch_gs_round(hipStream_t s, int n, const double *V, size_t ldv, int k1, double *w,
+                     double *part, double *out, double *nrm);
+void launch_gs_normalize(hipStream_t s, int n, const double *w, double *nrm2, const double *part,
+                         double *v);
 void launch_basis_combine(hipStream_t s, int n, const double *Z, size_t ldz, int k, const double *y,
                           double *x);
 
@@ -151,8 +151,8 @@ void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const
 // with the coarse solution t (else nullptr) the prolongation Phi_i t_i is
 // added to each region's output (phi: the copy made by
 // launch_basis_to_natural).  With tpart (else nullptr) the coarse solution
-// is instead summed from the per-tile products of W0^T (launch_trmv with
-// y == nullptr; T0 tiles), as the reduction would sum them.  diag: the packed
+// is instead summed from the per-tile products of W0^T
+// (launch_coarse_products with y == nullptr; T0 tiles), as the reduction would sum them.  diag: the packed
 // inverse diagonal tiles (DE entries per tile row), erow/ecol: the envelope
 // (with two entries of padding behind it).  ev_start / ev_stop (optional,
 // created with timing): bound to the dispatch itself (no extra packets in the
@@ -288,16 +288,16 @@ void launch_dense_inv_rows(hipStream_t s, const double *Lt, double *Wt, int T0, 
 void launch_dense_inv_update(hipStream_t s, const double *Lt, double *Wt, int T0, int k, int nk);
 void launch_tiles_identity(hipStream_t s, double *Wt, int T0);
 void launch_dense_tiles_to_f32(hipStream_t s, const double *src, float *dst, int T0);
-// y = W x (transpose 0) or W^T x (transpose 1) over the lower tiles of W;
-// part: T0*T0*64 doubles of scratch holding the per-tile products.  With
-// y == nullptr only the per-tile products are formed: entry O*64 + r of
-// W^T x is then the sum over K = O .. T0-1 of part[(O*T0 + K)*64 + r], split
-// into TRMV_RG consecutive pieces of K (piece g: K from O + len*g/TRMV_RG,
-// len = T0 - O), each summed in order and the pieces added in order from 0.
+// y = W^T (W x) over the lower tiles of W.  part: (T0*T0 + T0)*64 doubles of
+// scratch holding the per-tile products; t1: T0*64 doubles.  With y == nullptr
+// the second product's sums are left to the reader: entry O*64 + r is the sum
+// over K = O .. T0-1 of part[(O*T0 + K)*64 + r], split into TRMV_RG consecutive
+// pieces of K (piece g: K from O + len*g/TRMV_RG, len = T0 - O), each summed in
+// order and the pieces added in order from 0.
 constexpr int TRMV_RG = 16;
 template <typename T>
-void launch_trmv(hipStream_t s, const T *Wt, int T0, const double *x, double *part, double *y,
-                 int transpose, const int *done);
+void launch_coarse_products(hipStream_t s, const T *Wt, int T0, const double *x, double *part,
+                            double *t1, double *y, const int *done);
 
 // ------------------- CG on several columns and problems (k_batch.hip) ---
 // Row blocks (never across a problem boundary) and the recurrences' scalars,

@@ -353,17 +353,39 @@ __global__ void k_tiles_to_f32_lower(const double *__restrict__ src, float *__re
 }
 
 // ------------------------------------------------ coarse solve (TRMV) -----
-// y = W x (transpose = 0) or y = W^T x (transpose = 1) for the lower tiles
-// of W.  Stage 1: one workgroup per lower tile writes its 64-vector product
-// into part[(out tile) * T0 + (in tile)]; stage 2 sums in tile order.
+// W^T (W x) for the lower tiles of W.  One workgroup per lower tile writes its
+// 64-vector product into part[(out tile) * T0 + (in tile)] (the first product's
+// diagonal tiles behind them, at T0 * T0 + I: the rest of the two products are
+// different triangles), and every entry is summed over its input tiles in a
+// fixed order: RG consecutive pieces of the range, each in order, added in
+// order.
+constexpr int RG = TRMV_RG;
+constexpr int TRMV_FOLD = 32;
+
+__device__ __forceinline__ size_t part_at(int O, int K, int T0, int transpose) {
+  return ((!transpose && O == K) ? (size_t)T0 * T0 + O : (size_t)O * T0 + K) * TS;
+}
+
+// Piece g of entry r of output tile O.
+__device__ __forceinline__ double trmv_piece(const double *__restrict__ part, int T0, int O, int r,
+                                             int transpose, int g) {
+  const int k0 = transpose ? O : 0, len = (transpose ? T0 : O + 1) - k0;
+  const int a = k0 + (len * g) / RG, b = k0 + (len * (g + 1)) / RG;
+  double s = 0.0;
+#pragma unroll 4
+  for (int K = a; K < b; ++K) s += part[part_at(O, K, T0, transpose) + r];
+  return s;
+}
+
+// The second product (transpose) with x == nullptr reads the first one's
+// products and sums its own input entries.
 template <typename T>
 __global__ void __launch_bounds__(WG) k_trmv_tiles(const T *__restrict__ Wt, int T0,
-                                                   const double *__restrict__ x,
-                                                   double *__restrict__ part, int transpose,
-                                                   const int *__restrict__ done) {
+                                                   const double *__restrict__ x, double *part,
+                                                   int transpose, const int *__restrict__ done) {
   if (done && *done) return;
   __shared__ double xs[TS];
-  __shared__ double red[4][TS];
+  __shared__ double red[RG][TS];
   const int b = blockIdx.x;
   int I = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
   while ((I + 1) * (I + 2) / 2 <= b) ++I;
@@ -371,47 +393,55 @@ __global__ void __launch_bounds__(WG) k_trmv_tiles(const T *__restrict__ Wt, int
   const int J = b - I * (I + 1) / 2;  // J <= I
   const T *w = Wt + ((size_t)I * T0 + J) * TE;
   const int t = threadIdx.x;
+  T wv[16];  // (in flight while the input entries are fetched or summed)
   if (!transpose) {
+    const int r = t >> 2, q = t & 3;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) wv[c] = w[r * TS + 16 * q + c];
     if (t < TS) xs[t] = x[J * TS + t];
     __syncthreads();
-    const int r = t >> 2, q = t & 3;
     double s = 0.0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) s = fma((double)w[r * TS + 16 * q + c], xs[16 * q + c], s);
+    for (int c = 0; c < 16; ++c) s = fma((double)wv[c], xs[16 * q + c], s);
     s += __shfl_xor(s, 1, 64);
     s += __shfl_xor(s, 2, 64);
-    if (q == 0) part[((size_t)I * T0 + J) * TS + r] = s;
+    if (q == 0) part[part_at(I, J, T0, 0) + r] = s;
   } else {
-    if (t < TS) xs[t] = x[I * TS + t];
-    __syncthreads();
     const int c = t & 63, g = t >> 6;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) wv[r] = w[(16 * g + r) * TS + c];
+    if (x) {
+      if (t < TS) xs[t] = x[I * TS + t];
+    } else {
+#pragma unroll
+      for (int u = 0; u < RG / 4; ++u)
+        red[RG / 4 * g + u][c] = trmv_piece(part, T0, I, c, 0, RG / 4 * g + u);
+      __syncthreads();
+      if (g == 0) {
+        double tot = 0.0;
+#pragma unroll
+        for (int u = 0; u < RG; ++u) tot += red[u][c];
+        xs[c] = tot;
+      }
+    }
+    __syncthreads();
     double s = 0.0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s = fma((double)w[(16 * g + r) * TS + c], xs[16 * g + r], s);
+    for (int r = 0; r < 16; ++r) s = fma((double)wv[r], xs[16 * g + r], s);
     red[g][c] = s;
     __syncthreads();
-    if (g == 0) part[((size_t)J * T0 + I) * TS + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+    if (g == 0) part[part_at(J, I, T0, 1) + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
   }
 }
 
-// y[O*64 + r] = sum over input tiles K (in order) of part[(O*T0 + K)*64 + r],
-// K ranging over J <= O (no transpose) or I >= O (transpose).  RG groups of
-// 64 threads per output tile split the K range into fixed consecutive
-// pieces (a few loads each, issued together), combined in group order.
-constexpr int RG = TRMV_RG;
+// y[O*64 + r]: the sums as a launch of their own, 64 RG threads per output tile.
 __global__ void __launch_bounds__(RG * TS) k_trmv_reduce(int T0, const double *__restrict__ part,
                                                          double *__restrict__ y, int transpose,
                                                          const int *__restrict__ done) {
   if (done && *done) return;
   __shared__ double red[RG][TS];
   const int O = blockIdx.x, r = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int k0 = transpose ? O : 0, k1 = transpose ? T0 : O + 1;
-  const int len = k1 - k0;
-  const int a = k0 + (len * g) / RG, b = k0 + (len * (g + 1)) / RG;
-  double s = 0.0;
-#pragma unroll 4
-  for (int K = a; K < b; ++K) s += part[((size_t)O * T0 + K) * TS + r];
-  red[g][r] = s;
+  red[g][r] = trmv_piece(part, T0, O, r, transpose, g);
   __syncthreads();
   if (g == 0) {
     double tot = 0.0;
@@ -504,17 +534,25 @@ void launch_dense_tiles_to_f32(hipStream_t s, const double *src, float *dst, int
   hipLaunchKernelGGL(k_tiles_to_f32_lower, dim3((unsigned)b), dim3(WG), 0, s, src, dst, T0);
 }
 
+// The second product sums the first one's pieces itself where there are few: a
+// launch less.  An application with one tile column takes 27.7 us (28.9 with the
+// sums launched), with 24 85.9 (86.5); with 96, where every workgroup reads 48
+// pieces on average, 257.8 against 254.0.
 template <typename T>
-void launch_trmv(hipStream_t s, const T *Wt, int T0, const double *x, double *part, double *y,
-                 int transpose, const int *done) {
+void launch_coarse_products(hipStream_t s, const T *Wt, int T0, const double *x, double *part,
+                            double *t1, double *y, const int *done) {
   const int nb = T0 * (T0 + 1) / 2;
-  hipLaunchKernelGGL((k_trmv_tiles<T>), dim3(nb), dim3(WG), 0, s, Wt, T0, x, part, transpose, done);
-  if (y)
-    hipLaunchKernelGGL(k_trmv_reduce, dim3(T0), dim3(RG * TS), 0, s, T0, part, y, transpose, done);
+  const bool fold = T0 <= TRMV_FOLD;
+  hipLaunchKernelGGL((k_trmv_tiles<T>), dim3(nb), dim3(WG), 0, s, Wt, T0, x, part, 0, done);
+  if (!fold)
+    hipLaunchKernelGGL(k_trmv_reduce, dim3(T0), dim3(RG * TS), 0, s, T0, part, t1, 0, done);
+  hipLaunchKernelGGL((k_trmv_tiles<T>), dim3(nb), dim3(WG), 0, s, Wt, T0, fold ? nullptr : t1, part,
+                     1, done);
+  if (y) hipLaunchKernelGGL(k_trmv_reduce, dim3(T0), dim3(RG * TS), 0, s, T0, part, y, 1, done);
 }
-template void launch_trmv<double>(hipStream_t, const double *, int, const double *, double *,
-                                  double *, int, const int *);
-template void launch_trmv<float>(hipStream_t, const float *, int, const double *, double *,
-                                 double *, int, const int *);
+template void launch_coarse_products<double>(hipStream_t, const double *, int, const double *,
+                                             double *, double *, double *, const int *);
+template void launch_coarse_products<float>(hipStream_t, const float *, int, const double *,
+                                            double *, double *, double *, const int *);
 
 }  // namespace amsp

@@ -608,9 +608,18 @@ __global__ void __launch_bounds__(WG) k_gs_update(int n, const double *__restric
 
 // v = w / sqrt(*nrm2) (zero when the norm is zero: the Krylov space is exhausted)
 __global__ void __launch_bounds__(WG) k_gs_normalize(int n, const double *__restrict__ w,
-                                                     const double *__restrict__ nrm2,
+                                                     double *__restrict__ nrm2,
+                                                     const double *__restrict__ part, int nb,
                                                      double *__restrict__ v) {
-  const double nr = sqrt(*nrm2);
+  __shared__ double sh[WG / 64];
+  double n2;
+  if (part) {  // the squared norm from its partial sums
+    n2 = sum_partials(part, nb, sh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nrm2 = n2;
+  } else {
+    n2 = *nrm2;
+  }
+  const double nr = sqrt(n2);
   for (int i = blockIdx.x * WG + threadIdx.x; i < n; i += gridDim.x * WG)
     v[i] = nr > 0.0 ? w[i] / nr : 0.0;
 }
@@ -627,21 +636,24 @@ __global__ void __launch_bounds__(WG) k_basis_combine(int n, const double *__res
   }
 }
 
-void launch_gs_dots(hipStream_t s, int n, const double *V, size_t ldv, int k1, const double *w,
-                    double *part, double *out) {
+// w -= V (V^T w), coefficients to out, partials of w.w to nrm (if not null).
+// (With the coefficients' sums inside the update, every workgroup summing them,
+// a step of 65536 rows was 4 percent slower.)
+void launch_gs_round(hipStream_t s, int n, const double *V, size_t ldv, int k1, double *w,
+                     double *part, double *out, double *nrm) {
   const int nb = reduce_blocks(n);
   hipLaunchKernelGGL(k_gs_dots, dim3(nb, (k1 + GSC - 1) / GSC), dim3(WG), 0, s, n, V, ldv, k1, w,
                      part);
   hipLaunchKernelGGL(k_gs_reduce, dim3(k1), dim3(WG), 0, s, nb, part, out);
+  hipLaunchKernelGGL(k_gs_update, dim3(nb), dim3(WG), 0, s, n, V, ldv, k1, out, w, nrm);
 }
 
-void launch_gs_update(hipStream_t s, int n, const double *V, size_t ldv, int k1, const double *h,
-                      double *w, double *part) {
-  hipLaunchKernelGGL(k_gs_update, dim3(reduce_blocks(n)), dim3(WG), 0, s, n, V, ldv, k1, h, w, part);
-}
-
-void launch_gs_normalize(hipStream_t s, int n, const double *w, const double *nrm2, double *v) {
-  hipLaunchKernelGGL(k_gs_normalize, dim3(reduce_blocks(n)), dim3(WG), 0, s, n, w, nrm2, v);
+// v = w / |w|, |w|^2 in *nrm2 (summed from part first, unless null: a launch
+// less a step, 4 percent of one with 65536 rows and 64 regions)
+void launch_gs_normalize(hipStream_t s, int n, const double *w, double *nrm2, const double *part,
+                         double *v) {
+  const int nb = reduce_blocks(n);
+  hipLaunchKernelGGL(k_gs_normalize, dim3(nb), dim3(WG), 0, s, n, w, nrm2, part, nb, v);
 }
 
 void launch_basis_combine(hipStream_t s, int n, const double *Z, size_t ldz, int k, const double *y,
