@@ -140,8 +140,8 @@ size_t local_apply_stream_lds_bytes(int max_npad);
 template <typename TB>
 void launch_restrict(hipStream_t s, const Plan &p, const double *r, const TB *phi, double *cvec,
                      const int *done);
-// The mixed-form local apply on the streams (same operation as
-// launch_local_apply with float factors).
+// The mixed forms' local apply on the streams (the operation of
+// launch_local_apply, which it calls for few regions).
 template <typename TB>
 void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const double *r,
                                const float *fst, const float *bst, const TB *phi, const double *t,
@@ -152,15 +152,17 @@ void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const
 // added to each region's output (phi: the copy made by
 // launch_basis_to_natural).  With tpart (else nullptr) the coarse solution
 // is instead summed from the per-tile products of W0^T
-// (launch_coarse_products with y == nullptr; T0 tiles), as the reduction would sum them.  diag: the packed
-// inverse diagonal tiles (DE entries per tile row), erow/ecol: the envelope
-// (with two entries of padding behind it).  ev_start / ev_stop (optional,
-// created with timing): bound to the dispatch itself (no extra packets in the
-// stream).
+// (launch_coarse_products with y == nullptr; T0 tiles), as the reduction would
+// sum them.  T = double: diag holds the packed inverse diagonal tiles (DE entries
+// per tile row), frow / fcol the envelope (with two entries of padding behind
+// it); T = float: frow / fcol are the two sweeps' streams, diag is not read.
+// ev_start / ev_stop (optional, created with timing): bound to the dispatch
+// itself (no extra packets in the stream).
+template <typename T, typename TB>
 void launch_local_apply(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                        const double *diag, const double *erow, const double *ecol,
-                        const double *phi, const double *t, const double *tpart, int T0,
-                        double *xloc, const int *done, hipEvent_t ev_start = nullptr,
+                        const T *diag, const T *frow, const T *fcol, const TB *phi,
+                        const double *t, const double *tpart, int T0, double *xloc,
+                        const int *done, hipEvent_t ev_start = nullptr,
                         hipEvent_t ev_stop = nullptr);
 void launch_selftest_mfma(hipStream_t s, const double *A, const double *B, double *D);
 // The regions' dofs in ascending order and their local indices (Plan::asc,

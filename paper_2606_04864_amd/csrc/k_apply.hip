@@ -216,11 +216,16 @@ __device__ __forceinline__ void coarse_partial_finish(const Plan &p, int i, doub
 // Deeper prefetch (two and three blocks) measured the same.
 // Measured (blocks of 64 rows, float64, whole kernel): 64 regions of 21 blocks
 // 97 -> 54 us; 1024 regions 222 -> 165 us (0.93 GB, 5.6 TB/s: what a copy
-// reaches); 1331 regions of 12 blocks in three dimensions 231 us.
+// reaches); 1331 regions of 12 blocks in three dimensions 231 us.  The float32 factor's
+// figures stand at launch_local_apply_stream.
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
-template <bool FWD, int EVU, typename T>
+// The float64 factor is read as an envelope form (block starts in ptr) and packed
+// tiles; the float32 one (STREAM) as one stream per sweep, block I's envelope
+// entries at boff[I] and its tile behind them (at the next multiple of four).
+template <bool FWD, int EVU, bool STREAM, typename T>
 __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
+                                            const int *__restrict__ boff,
                                             const T *__restrict__ env,
                                             const T *__restrict__ diag, T *v, T *tmp, T *Ev, T *Dt) {
   constexpr int EVC = EVU * WG;
@@ -231,19 +236,20 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
   // Segment bounds of a block, as loaded (Raw) and as used: this row's first
   // entry within the block's entries [base, base + total) and its length.
   struct Raw {
-    int b0, b1, e0, e1;
+    int b0, b1, e0, e1, at;
   };
   struct Seg {
-    int off, len, base, total;
+    int off, len, base, total;  // base: position of the block's entries in env
   };
   auto row0 = [&](int I) { return (FWD ? I : nt - 1 - I) * TS; };
   auto seg_load = [&](int I) {
-    const int *b = ptr + row0(min(I, nt - 1));
-    return Raw{b[0], b[TS], b[rr], b[rr + 1]};
+    const int at = row0(min(I, nt - 1)), *b = ptr + at;
+    return Raw{b[0], b[TS], b[rr], b[rr + 1], STREAM ? boff[at / TS] : 0};
   };
   auto seg_of = [&](const Raw &r) {
     const int base = __builtin_amdgcn_readfirstlane(r.b0);
-    return Seg{r.e0 - base, r.e1 - r.e0, base, __builtin_amdgcn_readfirstlane(r.b1) - base};
+    return Seg{r.e0 - base, r.e1 - r.e0, STREAM ? __builtin_amdgcn_readfirstlane(r.at) : base,
+               __builtin_amdgcn_readfirstlane(r.b1) - base};
   };
   // two neighbouring entries per load, clamped into the block (a block without
   // entries reads the one before it or the array's padding)
@@ -258,9 +264,10 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
   // the packed diagonal tile, in 16-byte pieces (the pieces past its end: the
   // last one again)
   constexpr int DV = DE * (int)sizeof(T) / 16, DU = (DV + WG - 1) / WG;
-  auto load_d = [&](int I, v4u(&d)[DU]) {
-    const v4u *tile =
-        reinterpret_cast<const v4u *>(diag + (size_t)(row0(min(I, nt - 1)) / TS) * DE);
+  auto load_d = [&](int I, const Seg &g, v4u(&d)[DU]) {
+    const T *at = STREAM ? env + g.base + ((g.total + 3) & ~3)
+                         : diag + (size_t)(row0(min(I, nt - 1)) / TS) * DE;
+    const v4u *tile = reinterpret_cast<const v4u *>(at);
 #pragma unroll
     for (int u = 0; u < DU; ++u) d[u] = tile[min(t + WG * u, DV - 1)];
   };
@@ -269,7 +276,7 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
   Seg g = seg_of(seg_load(0));
   Raw raw = seg_load(1);
   ev_load(g, ev);
-  load_d(0, dt);
+  load_d(0, g, dt);
   for (int I = 0; I < nt; ++I) {
     const int r0 = row0(I);
 #pragma unroll
@@ -279,7 +286,7 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
     for (int u = 0; u < DU; ++u) reinterpret_cast<v4u *>(Dt)[min(t + WG * u, DV - 1)] = dt[u];
     const Seg gn = seg_of(raw);
     ev_load(gn, ev);
-    load_d(I + 1, dt);
+    load_d(I + 1, gn, dt);
     raw = seg_load(I + 2);
     const int v0 = FWD ? r0 - g.len : r0 + TS;
     const int ltop = __builtin_amdgcn_readlane(g.len, FWD ? 0 : 60);  // the wavefront's longest
@@ -354,26 +361,27 @@ size_t local_apply_lds_bytes(int max_npad) {
   return (size_t)(max_npad + TS) * sizeof(double) + 2 * (size_t)(max_npad + 1) * sizeof(int);
 }
 
-// Fused additive-Schwarz local kernel of the FP64 form for one region per
-// workgroup: gather r on the region, forward/backward substitution with the
-// factor, store the local correction (plus Phi_i t_i when t is given) into
-// xloc.
-template <int EVU>
+// Fused additive-Schwarz local kernel (the FP64 form's, and the mixed forms' with
+// up to 640 regions) for one region per workgroup: gather r on the region,
+// forward/backward substitution with the factor, store the local correction
+// (plus Phi_i t_i when t is given) into xloc.
+template <int EVU, typename T, typename TB>
 __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(EVU <= 4 ? 4 : 2)))
-k_local_apply(Plan p, const double *__restrict__ r, const double *__restrict__ diag,
-              const double *__restrict__ erow, const double *__restrict__ ecol,
-              const double *__restrict__ phi, const double *__restrict__ t,
+k_local_apply(Plan p, const double *__restrict__ r, const T *__restrict__ diag,
+              const T *__restrict__ frow, const T *__restrict__ fcol,
+              const TB *__restrict__ phi, const double *__restrict__ t,
               const double *__restrict__ tpart, int T0, double *__restrict__ xloc,
               const int *__restrict__ done) {
   if (done && *done) return;
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ double tq_s[16];  // the region's coarse values
-  __shared__ __align__(16) double Ev[EVU * WG], Dt[DE], tmp[TS];
+  constexpr bool STREAM = sizeof(T) == 4;
+  __shared__ __align__(16) T Ev[EVU * WG], Dt[DE], tmp[TS];
   const int i = blockIdx.x;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
   const int g0 = p.trow_ptr[i], nt = p.trow_ptr[i + 1] - g0;
   const int npad = nt * TS;
-  double *v = reinterpret_cast<double *>(smem_raw);  // whole local vector (padded), TS zeros
+  T *v = reinterpret_cast<T *>(smem_raw);  // whole local vector (padded), TS zeros
   const double cps = tpart ? coarse_partial_load(p, i, tpart, T0) : 0.0;
   {  // gather, nothing conditional (as in the stream kernel; tmp takes the
      // stores of rows past the padding)
@@ -388,25 +396,27 @@ k_local_apply(Plan p, const double *__restrict__ r, const double *__restrict__ d
 #pragma unroll
       for (int u = 0; u < GU; ++u) {
         const int l = l0 + u * WG;
-        *(l < npad ? v + l : tmp + (threadIdx.x & (TS - 1))) = l < ni ? rv[u] : 0.0;
+        *(l < npad ? v + l : tmp + (threadIdx.x & (TS - 1))) = l < ni ? (T)rv[u] : T(0);
       }
     }
   }
-  if (threadIdx.x < TS) v[npad + threadIdx.x] = 0.0;
+  if (threadIdx.x < TS) v[npad + threadIdx.x] = T(0);
   if (tpart) coarse_partial_finish(p, i, cps, tq_s);
   const double *tq = tpart ? tq_s : (t ? t + p.coff[i] : nullptr);
   const int po = p.vp_ptr[i] + i;  // the region's segment starts
-  const double *dpool = diag + (size_t)g0 * DE;
-  local_sweep<true, EVU>(nt, p.eptr + po, erow + p.ebase[i], dpool, v, tmp, Ev, Dt);
-  local_sweep<false, EVU>(nt, p.uptr + po, ecol + p.ebase[i], dpool, v, tmp, Ev, Dt);
+  const T *dpool = STREAM ? nullptr : diag + (size_t)g0 * DE;
+  local_sweep<true, EVU, STREAM>(nt, p.eptr + po, p.sfb + g0,
+                                 frow + (STREAM ? p.sfr[i] : p.ebase[i]), dpool, v, tmp, Ev, Dt);
+  local_sweep<false, EVU, STREAM>(nt, p.uptr + po, p.sbb + g0,
+                                  fcol + (STREAM ? p.sbr[i] : p.ebase[i]), dpool, v, tmp, Ev, Dt);
   // local correction (+ prolongation) in the region's ascending-global-index
   // layout, so that the scatter reads contiguous runs
   store_local(p, i, r0, ni, v, phi, tq, xloc);
 }
 
 // ------------------------------------ local solves on the f32 streams -----
-// The mixed-form local apply reads each sweep's data as one contiguous
-// stream per region (envelope segments then packed diagonal tile, block by
+// The mixed forms' local apply with many regions reads each sweep's data as one
+// contiguous stream per region (envelope segments then packed diagonal tile, block by
 // block in sweep order).  The workgroup loads it in 4 KB units (16 bytes per
 // thread, every byte used), in batches of NS units: while one batch is used
 // the next is in flight.  An arriving batch is copied into an LDS ring of RU
@@ -673,40 +683,55 @@ template void launch_restrict<float>(hipStream_t, const Plan &, const double *, 
 template void launch_restrict<__hip_bfloat16>(hipStream_t, const Plan &, const double *,
                                               const __hip_bfloat16 *, double *, const int *);
 
-template <int EVU>
+template <int EVU, typename T, typename TB>
 static void local_apply_launch(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                               const double *diag, const double *erow, const double *ecol,
-                               const double *phi, const double *t, const double *tpart, int T0,
-                               double *xloc, const int *done, hipEvent_t ev_start,
-                               hipEvent_t ev_stop) {
-  const size_t sm = (size_t)(max_npad + TS) * sizeof(double);
-  allow_lds(k_local_apply<EVU>, sm);
+                               const T *diag, const T *frow, const T *fcol, const TB *phi,
+                               const double *t, const double *tpart, int T0, double *xloc,
+                               const int *done, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const size_t sm = (size_t)(max_npad + TS) * sizeof(T);
+  allow_lds(k_local_apply<EVU, T, TB>, sm);
   if (ev_start || ev_stop)  // events bound to this dispatch: exact kernel duration
-    hipExtLaunchKernelGGL((k_local_apply<EVU>), dim3(p.N), dim3(WG), sm, s, ev_start, ev_stop,
-                          0, p, r, diag, erow, ecol, phi, t, tpart, T0, xloc, done);
+    hipExtLaunchKernelGGL((k_local_apply<EVU, T, TB>), dim3(p.N), dim3(WG), sm, s, ev_start,
+                          ev_stop, 0, p, r, diag, frow, fcol, phi, t, tpart, T0, xloc, done);
   else
-    hipLaunchKernelGGL(k_local_apply<EVU>, dim3(p.N), dim3(WG), sm, s, p, r, diag, erow,
-                       ecol, phi, t, tpart, T0, xloc, done);
+    hipLaunchKernelGGL((k_local_apply<EVU, T, TB>), dim3(p.N), dim3(WG), sm, s, p, r, diag, frow,
+                       fcol, phi, t, tpart, T0, xloc, done);
 }
 
+template <typename T, typename TB>
 void launch_local_apply(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                        const double *diag, const double *erow, const double *ecol,
-                        const double *phi, const double *t, const double *tpart, int T0,
-                        double *xloc, const int *done, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                        const T *diag, const T *frow, const T *fcol, const TB *phi,
+                        const double *t, const double *tpart, int T0, double *xloc,
+                        const int *done, hipEvent_t ev_start, hipEvent_t ev_stop) {
   // staged entries per thread: as for the block solve (launch_env_solve_block)
   if (p.env_mean <= 700)
-    local_apply_launch<4>(s, p, max_npad, r, diag, erow, ecol, phi, t, tpart, T0, xloc, done,
+    local_apply_launch<4>(s, p, max_npad, r, diag, frow, fcol, phi, t, tpart, T0, xloc, done,
                           ev_start, ev_stop);
   else
-    local_apply_launch<16>(s, p, max_npad, r, diag, erow, ecol, phi, t, tpart, T0, xloc, done,
+    local_apply_launch<16>(s, p, max_npad, r, diag, frow, fcol, phi, t, tpart, T0, xloc, done,
                            ev_start, ev_stop);
 }
+template void launch_local_apply<double, double>(hipStream_t, const Plan &, int, const double *,
+                                                 const double *, const double *, const double *,
+                                                 const double *, const double *, const double *,
+                                                 int, double *, const int *, hipEvent_t,
+                                                 hipEvent_t);
 
 template <typename TB>
 void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const double *r,
                                const float *fst, const float *bst, const TB *phi, const double *t,
                                const double *tpart, int T0, double *xloc, const int *done,
                                hipEvent_t ev_start, hipEvent_t ev_stop) {
+  // With few regions a region's chain of blocks is what counts, and the FP64
+  // form's sweep has the shorter one; with many the stream's fuller loads are.
+  // PCG in float32, stream kernel / sweep: 64 regions 3.47 / 2.98 ms, 256 3.77 /
+  // 3.36, 512 in three dimensions 6.24 / 5.41, 576 5.02 / 4.60, 729 in three
+  // dimensions 8.19 / 8.26, 784 5.03 / 5.11, 1024 7.28 / 7.33.
+  if (p.N <= 640) {
+    launch_local_apply<float, TB>(s, p, max_npad, r, nullptr, fst, bst, phi, t, tpart, T0, xloc,
+                                  done, ev_start, ev_stop);
+    return;
+  }
   const size_t sm = local_apply_stream_lds_bytes(max_npad);
   allow_lds(k_local_apply_stream<TB>, sm);
   if (ev_start || ev_stop)  // events bound to this dispatch: exact kernel duration

@@ -91,3 +91,34 @@ def test_columns_without_coarse_space(cols):
         ref = O.local_part(st, R[j])
         assert np.linalg.norm(Z[j] - ref) <= 1e-10 * np.linalg.norm(ref)
     assert not Z2.any()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("name", ["one_block", "long_segments", "narrow_and_wide", "cubes",
+                                  "full_triangles", "640", "676"])
+def test_mixed_local_apply_edges(name, prec):
+    """One vector through the float32 factor: the same edges, and both sides of the number of
+    regions from which each region's factor is read as one stream.  Bar as above."""
+    if name.isdigit():  # regions of 16 .. 36 rows
+        ny, nx = {"640": (20, 32), "676": (26, 26)}[name]
+        A = darcy.tpfa_matrix(log_field((4 * ny, 4 * nx), 8))
+        at = lambda n: np.arange(4 * n) // 4  # noqa: E731
+        part, nparts, kw = (at(ny)[:, None] * nx + at(nx)).astype(np.int32).ravel(), ny * nx, {}
+    else:
+        A, part, nparts, kw = problem(name)
+    M = A.to_scipy()
+    st = O.setup(M, part, nparts, 2, 1)
+    alt = O.setup(M, part, nparts, 2, 1, local_order="descending")
+    print("mixed local apply", name, prec, file=sys.stderr, flush=True)
+    pc = P.setup(A, part, nparts, 2, overlap=1, precision=prec, **kw)
+    r = np.random.default_rng(9).standard_normal(A.n)
+    z = pc.apply(torch.tensor(r, device="cuda"), parts=1)
+    torch.cuda.synchronize()
+    z = z.cpu().numpy()
+    pc.close()
+    ref = O.local_part(st, r)
+    floor = np.linalg.norm(O.local_part(alt, r) - ref) / np.linalg.norm(ref)
+    err = np.linalg.norm(z - ref) / np.linalg.norm(ref)
+    bar = max(1e-5, 10 * floor * 6e-8 / 1.1e-16)
+    print("  err", err, "bar", bar, file=sys.stderr, flush=True)
+    assert err <= bar
