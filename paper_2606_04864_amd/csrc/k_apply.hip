@@ -156,7 +156,7 @@ __device__ __forceinline__ void store_local(const Plan &p, int i, int r0, int ni
 }
 
 // The region's coarse values from the per-tile products of W0^T t1
-// (launch_trmv with y == nullptr), summed exactly as k_trmv_reduce sums
+// (launch_coarse_products with y == nullptr), summed exactly as k_trmv_reduce sums
 // them.  Thread (q, g) = (t / TRMV_RG, t % TRMV_RG), q < m_i, adds piece g
 // of entry coff_i + q (coarse_partial_load, early: its loads then overlap the
 // gather); coarse_partial_finish adds the pieces in order inside each
