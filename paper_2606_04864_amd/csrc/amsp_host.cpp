@@ -854,7 +854,7 @@ static amsp_status device_setup(amsp_handle *h, const amsp_csr *A) {
     ALLOC(Yb, double, (size_t)sum_npad * EIGP);
     ALLOC(BY, double, (size_t)sum_npad * EIGP);
     ALLOC(bval, double, std::max<long long>(P.nloc, 1));
-    ALLOC(GK, double, (size_t)h->N * ((P.max_ni + EIG_GRAM_ROWS - 1) / EIG_GRAM_ROWS) * 2 * EIGP * EIGP);
+    ALLOC(GK, double, ((size_t)sum_npad / EIG_GRAM_ROWS + h->N) * 2 * EIGP * EIGP);
     ALLOC(CC, double, (size_t)h->N * (EIGP * EIGP + EIGP));
     ALLOC(conv, int, h->N);
     HIP_TRY(hipMemsetAsync(conv, 0, h->N * sizeof(int), h->stream));

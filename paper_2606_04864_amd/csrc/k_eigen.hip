@@ -156,9 +156,15 @@ __global__ void __launch_bounds__(WG) k_eig_bval(Plan p, const double *__restric
   }
 }
 
+// Region i's part b of the Gram matrices (its parts start at its padded rows'
+// share, one spare per region for the remainders).
+__device__ __forceinline__ size_t gram_part(const Plan &p, int i, int b) {
+  return (size_t)(p.vp_ptr[i] / GR + i + b) * 2 * EIGP * EIGP;
+}
+
 // BY = B Y for the real rows of every unconverged region and, in the same pass,
 // the Gram matrices G = Y^T Y and K = Y^T (B Y): workgroup (b, i) takes rows
-// GR b .. of region i and leaves its part of both in GK[i][b].  Four lanes per
+// GR b .. of region i and leaves its part of both at gram_part(i, b).  Four lanes per
 // row, four columns each (32-byte pieces of each neighbour row; a row's entry
 // indices and values are loaded by four lanes); a wavefront's 16 rows of Y and BY
 // then go through LDS to the matrix cores' layout (four rows per MFMA, lane l
@@ -173,7 +179,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) k_
                                                  const double *__restrict__ bval,
                                                  const double *__restrict__ Y,
                                                  double *__restrict__ BY,
-                                                 double *__restrict__ GK, int parts,
+                                                 double *__restrict__ GK,
                                                  const int *__restrict__ conv) {
   const int i = blockIdx.y;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
@@ -182,7 +188,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) k_
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   const int a = 4 * (t & 3);
   const size_t base = (size_t)p.vp_ptr[i] * EIGP;
-  double *out = GK + ((size_t)i * parts + blockIdx.x) * 2 * EIGP * EIGP;
+  double *out = GK + gram_part(p, i, blockIdx.x);
   d4 g = {0.0, 0.0, 0.0, 0.0}, k = {0.0, 0.0, 0.0, 0.0};
   for (int rb = (int)blockIdx.x * GR; rb < min(ni, (int)(blockIdx.x + 1) * GR); rb += WG / 4) {
     const int row = rb + (t >> 2), l = min(row, ni - 1);
@@ -269,7 +275,7 @@ __global__ void __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) k_
 // (block_factor), the products run on the matrix cores, and a Jacobi round
 // reads and writes fixed LDS addresses and forms its rotations without divisions.
 __global__ void __launch_bounds__(64) k_eig_ritz(Plan p, double off_rel2,
-                                                 const double *__restrict__ GK, int parts,
+                                                 const double *__restrict__ GK,
                                                  double *__restrict__ CC,
                                                  const int *__restrict__ conv) {
   const int i = blockIdx.x;
@@ -280,7 +286,7 @@ __global__ void __launch_bounds__(64) k_eig_ritz(Plan p, double off_rel2,
   __shared__ double theta[EIGP];
   const int t = threadIdx.x, q = t >> 4, c = t & 15;
   const int np = (p.sd_ptr[i + 1] - p.sd_ptr[i] + GR - 1) / GR;
-  const double *in = GK + (size_t)i * parts * 2 * EIGP * EIGP;
+  const double *in = GK + gram_part(p, i, 0);
   d4 g = {0.0, 0.0, 0.0, 0.0}, k = {0.0, 0.0, 0.0, 0.0};
   for (int b = 0; b < np; ++b)
 #pragma unroll
@@ -619,14 +625,13 @@ void launch_eig_bval(hipStream_t s, const Plan &p, const double *val, const doub
 void launch_eig_rr(hipStream_t s, const Plan &p, int max_ni, const double *val,
                    const double *sdiag, const double *bval, const double *Y, double *BY, double *X,
                    double *GK, double *CC, double tol, int *conv, double *lam, bool test_next) {
-  const int parts = (max_ni + GR - 1) / GR;
-  hipLaunchKernelGGL(k_eig_spmm, dim3(parts, p.N), dim3(WG), 0, s, p, val, sdiag, bval, Y, BY, GK,
-                     parts, conv);
+  hipLaunchKernelGGL(k_eig_spmm, dim3((max_ni + GR - 1) / GR, p.N), dim3(WG), 0, s, p, val, sdiag,
+                     bval, Y, BY, GK, conv);
   // the small eigenproblems are diagonalised to 1e-2 tol relative: their
   // Ritz vectors then carry errors far below the residual bound the sweep
   // tests (on the vectors themselves), so this only saves Jacobi sweeps
   const double rel = fmax(1e-14, 1e-2 * tol);
-  hipLaunchKernelGGL(k_eig_ritz, dim3(p.N), dim3(64), 0, s, p, rel * rel, GK, parts, CC, conv);
+  hipLaunchKernelGGL(k_eig_ritz, dim3(p.N), dim3(64), 0, s, p, rel * rel, GK, CC, conv);
   hipLaunchKernelGGL(k_eig_finish, dim3(p.N), dim3(64 * NW), 0, s, p, Y, BY, X, CC, tol, conv, lam,
                      test_next ? 1 : 0);
 }
