@@ -230,7 +230,7 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
                                             const T *__restrict__ diag, T *v, T *tmp, T *Ev, T *Dt) {
   constexpr int EVC = EVU * WG;
   // a lane's envelope entries and groups of the triangle per pass (registers)
-  constexpr int EB = EVU > 4 ? 8 : 4, NG = EVU > 4 ? 4 : 2;
+  constexpr int EB = sweep_batch(EVU), NG = EVU > 4 ? 4 : 2;
   const int t = threadIdx.x, rr = t >> 2, q = t & 3, i = (t & 63) >> 2;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   // Segment bounds of a block, as loaded (Raw) and as used: this row's first
@@ -288,23 +288,28 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
     ev_load(gn, ev);
     load_d(I + 1, gn, dt);
     raw = seg_load(I + 2);
-    const int v0 = FWD ? r0 - g.len : r0 + TS;
+    const int v0 = sweep_row(FWD, r0, g.len);
     const int ltop = __builtin_amdgcn_readlane(g.len, FWD ? 0 : 60);  // the wavefront's longest
     T s0 = 0, s1 = 0;
     T br = v[r0 + rr];
     __asm__ volatile("" : "+v"(br));  // read here, off the path after the sum
     if (g.total <= EVC) {
-      // reads past the segment (other entries, rows of v and the TS zeros
-      // behind them) are dropped
+      // entries past the segment are read (less than a pass of them: other
+      // entries and Dt behind Ev, rows of v and the TS zeros behind them; see
+      // sweep_step) and dropped
+      static_assert(4 * EB <= TS, "a pass past the last row");
       const T *as = Ev + g.off + q, *xs = v + v0 + q;
       int left = g.len - q;
-      for (int k0 = 0; k0 < ltop; k0 += 4 * EB, as += 4 * EB, xs += 4 * EB, left -= 4 * EB) {
+      for (int k0 = 0; k0 < ltop; k0 += 4 * EB, left -= 4 * EB) {
         T a[EB], x[EB];
 #pragma unroll
         for (int u = 0; u < EB; ++u) {
           a[u] = as[4 * u];
           x[u] = xs[4 * u];
         }
+        const int step = sweep_step(EB, k0, g.len);  // (while the loads are under way)
+        as += step;
+        xs += step;
 #pragma unroll
         for (int u = 0; u < EB; ++u) __asm__ volatile("" : "+v"(a[u]), "+v"(x[u]));
 #pragma unroll
@@ -376,7 +381,11 @@ k_local_apply(Plan p, const double *__restrict__ r, const T *__restrict__ diag,
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ double tq_s[16];  // the region's coarse values
   constexpr bool STREAM = sizeof(T) == 4;
-  __shared__ __align__(16) T Ev[EVU * WG], Dt[DE], tmp[TS];
+  // one block, so that reads a little past Ev stay inside it
+  __shared__ __align__(16) struct {
+    T Ev[EVU * WG], Dt[DE], tmp[TS];
+  } sh;
+  T *const Ev = sh.Ev, *const Dt = sh.Dt, *const tmp = sh.tmp;
   const int i = blockIdx.x;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
   const int g0 = p.trow_ptr[i], nt = p.trow_ptr[i + 1] - g0;

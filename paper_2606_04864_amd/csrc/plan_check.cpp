@@ -8,10 +8,12 @@
 // exit handler's teardown also runs under the sanitizers.  It checks the
 // plan's basic invariants (every core inside its region, pointers monotone,
 // regions sorted sets once ordered) and prints one line per case.
-// Exit status 0 means every case behaved.
+// Exit status 0 means every case behaved.  With the argument "sweep" it checks
+// instead that the local solves' LDS reads stay inside what they allocate.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <string>
 #include <thread>
 #include <vector>
@@ -143,6 +145,59 @@ void plan_case(const Grid &g, int nev, int overlap, int order, int dense, const 
   }
 }
 
+// Walks both sweeps of the one-vector local solves (local_sweep) over a plan, every
+// block, wavefront and lane, for both numbers of staged entries: the furthest row of
+// the vector and the furthest staged entry that a lane reads, against the npad + TS
+// rows and the staged entries with the diagonal tile behind them.
+void sweep_case(const Grid &g, int overlap, int order, int dense, const char *name) {
+  amsp_options opt{};
+  opt.overlap = overlap;
+  opt.local_order = order;
+  opt.dense_tiles = dense;
+  const amsp_csr A = g.csr();
+  std::string msg;
+  HostPlan P;
+  int s = build_plan(&A, g.part.data(), g.nparts, 2, opt, P, msg);
+  expect(s == AMSP_OK, std::string(name) + ": plan " + msg);
+  if (s != AMSP_OK) return;
+  for (int evu : {4, 16}) {
+    const int evc = evu * WG, eb = sweep_batch(evu);
+    int past_v = -1, past_e = -1, staged = 0;  // furthest past the region's rows, past evc
+    bool low = true, longest = true;
+    for (int i = 0; i < g.nparts; ++i) {
+      const int npad = P.vp_ptr[i + 1] - P.vp_ptr[i];
+      for (int fwd = 0; fwd < 2; ++fwd) {
+        const int *ptr = (fwd ? P.eptr : P.uptr).data() + P.vp_ptr[i] + i;
+        for (int r0 = 0; r0 < npad; r0 += TS) {
+          if (ptr[r0 + TS] - ptr[r0] > evc) continue;  // read from memory, exactly
+          ++staged;
+          for (int w = 0; w < 4; ++w) {
+            auto len = [&](int r) { return ptr[r + 1] - ptr[r]; };
+            const int top = len(r0 + 16 * w + (fwd ? 0 : 15));
+            for (int r = r0 + 16 * w; r < r0 + 16 * w + 16; ++r) {
+              longest &= len(r) <= top;
+              for (int k0 = 0, at = 0; k0 < top; k0 += 4 * eb) {
+                const int v = sweep_row(fwd, r0, len(r)) + at;
+                low &= v >= 0;
+                past_v = std::max(past_v, v + 3 + 4 * (eb - 1) - npad);
+                past_e = std::max(past_e, ptr[r] - ptr[r0] + at + 3 + 4 * (eb - 1) - evc);
+                at += sweep_step(eb, k0, len(r));
+              }
+            }
+          }
+        }
+      }
+    }
+    expect(longest, std::string(name) + ": a wavefront's longest segment");
+    expect(low && past_v < TS, std::string(name) + ": row " + std::to_string(past_v) +
+                                   " past the region's read");
+    expect(past_e < DE, std::string(name) + ": entry " + std::to_string(past_e) +
+                            " past the staged ones read");
+    std::printf("ok sweep %s, %d staged per thread: %d blocks, past the rows %d, past the entries %d\n",
+                name, evu, staged, past_v, past_e);
+  }
+}
+
 void reject_case(Grid g, int what, int want, const char *name) {
   const int nev = 4, overlap = 1;
   if (what == 0) std::swap(g.ci[1], g.ci[2]);           // unsorted columns
@@ -159,7 +214,17 @@ void reject_case(Grid g, int what, int want, const char *name) {
 
 }  // namespace
 
-int main() {
+int main(int argc, char **argv) {
+  if (argc > 1 && !std::strcmp(argv[1], "sweep")) {
+    // natural order: long segments beside the short ones of a region's last rows
+    sweep_case(make_grid(150, 24, 1, 1, 2, 1), 1, 1, 0, "150 x 13");
+    sweep_case(make_grid(169, 35, 1, 1, 1, 1), 0, 1, 0, "169 x 35");
+    sweep_case(make_grid(61, 53, 1, 5, 4, 1), 2, 0, 0, "2d");
+    sweep_case(make_grid(14, 13, 11, 3, 2, 2), 1, 0, 0, "3d");
+    sweep_case(make_grid(40, 40, 1, 2, 2, 1), 1, 0, 1, "full triangles");
+    std::printf("%s (%d failures)\n", failures ? "FAILED" : "PASSED", failures);
+    return failures ? 1 : 0;
+  }
   const Grid g2 = make_grid(61, 53, 1, 5, 4, 1);     // ragged 2D, 20 parts
   const Grid g3 = make_grid(14, 13, 11, 3, 2, 2);    // ragged 3D, 12 parts
   const Grid one = make_grid(9, 7, 1, 1, 1, 1);      // a single part
