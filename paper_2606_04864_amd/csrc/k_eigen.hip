@@ -59,8 +59,9 @@ __global__ void __launch_bounds__(WG) k_eig_init(Plan p, const double *__restric
 // so one buffer is enough.
 constexpr int HS = EIGP + 2;  // row stride of H and V (16-byte pieces)
 
-// Slot of index p (and index in slot p's mirror image) at the start of a sweep.
+// Slot of index p at the start and the end of a sweep, and the index in slot s.
 __device__ __forceinline__ int jacobi_slot(int p) { return p < 8 ? 2 * p : 2 * (EIGP - 1 - p) + 1; }
+__device__ __forceinline__ int jacobi_index(int s) { return s & 1 ? EIGP - 1 - s / 2 : s / 2; }
 
 // Rotation (c, s) that clears the entry b2 / 2 between diagonals differing by a:
 // tan from tau = a / b2, formed as c^2 = (1 + |a| / r) / 2, s = b2 / (2 r c) with
@@ -317,7 +318,7 @@ __global__ void __launch_bounds__(64) k_eig_ritz(Plan p, double off_rel2,
     H[jacobi_slot(q + 4 * r) * HS + jacobi_slot(c)] = 0.5 * (h[r] + G[c * HP + q + 4 * r]);
   wave_sync();
   jacobi16(H, V, off_rel2);
-  if (t < EIGP) {  // ascending order, ties by slot: lane a places value a
+  if (t < EIGP) {  // ascending order, ties by index (a stable sort): lane a places slot a's value
     auto key = [&](int a) {
       const double x = H[a * HS + a];
       return x == x ? x : INFINITY;  // a NaN sorts last (the result is then unused)
@@ -327,7 +328,7 @@ __global__ void __launch_bounds__(64) k_eig_ritz(Plan p, double off_rel2,
 #pragma unroll
     for (int b = 0; b < EIGP; ++b) {
       const double x = key(b);
-      rank += (x < th || (x == th && b < t)) ? 1 : 0;
+      rank += (x < th || (x == th && jacobi_index(b) < jacobi_index(t))) ? 1 : 0;
     }
     perm[rank] = t;
     theta[rank] = H[t * HS + t];
