@@ -256,9 +256,10 @@ amsp_status amsp_pcg(amsp_handle *h, const double *f_dev, double *u_dev, int32_t
  * columns run together: one CG recurrence per column, with the stopping rule
  * above applied per column, sharing every SpMV (matrix entries read once) and
  * every preconditioner application (the block path of amsp_apply).  The
- * workspace (four vectors of 8 n doubles for up to 8 columns, of 16 n for more)
- * is allocated per call from the handle's cache.  info sums the columns' iterations and reports the worst residuals;
- * a last single column takes the one-column path.  A column that meets
+ * workspace (the block path's and, for more than 8 columns, two vectors of 16 n
+ * doubles) is allocated per call from the handle's cache.  info sums the
+ * columns' iterations and reports the worst residuals; a last single column
+ * takes the one-column path.  A column that meets
  * p.Ap <= 0 or a non-finite value stops there (keeping its last iterate);
  * the others run to their own end, restarts included, and the call then
  * returns AMSP_ERR_BREAKDOWN with u and info written for every column. */
@@ -284,9 +285,8 @@ amsp_status amsp_pcg(amsp_handle *h, const double *f_dev, double *u_dev, int32_t
  * AMSP_ERR_BREAKDOWN if p.Ap <= 0 or a non-finite value stopped some
  * recurrence: the others (every other problem's, and the same problem's
  * other columns) run to their own end, and u, info, iterations and relres
- * are written for all of them.  Workspace:
- * four vectors of 8 n doubles (nrhs <= 8) or 16 n, and small tables, from the
- * handle's cache.  Blocks. */
+ * are written for all of them.  Workspace: the block path's, two vectors of
+ * 16 n doubles for nrhs > 8, and small tables, from the handle's cache.  Blocks. */
 amsp_status amsp_pcg_batched(amsp_handle *h, int32_t nprob, const int64_t *prob_ptr,
                              const double *f_dev, double *u_dev, int32_t nrhs, double rtol,
                              int32_t maxit, amsp_info *info, int32_t *iterations,

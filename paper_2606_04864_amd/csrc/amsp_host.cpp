@@ -1781,23 +1781,31 @@ static amsp_status pcg_rows(amsp_handle *h, const std::vector<long long> &ptr, c
   if (st != AMSP_OK) return st;
   bool ok = true;
   RowBlocks rb{nblk, nseg, upload(h, brow, ok), upload(h, bseg, ok), upload(h, sblk, ok)};
-  double *Z = h->mem.alloc<double>(tot), *P0 = h->mem.alloc<double>(tot),
-         *P1 = h->mem.alloc<double>(tot), *Q = h->mem.alloc<double>(tot);
+  // The vectors share the block workspace.  The residual is the preconditioner's
+  // input, in X.  Y and XN are free outside the preconditioner: Z (from its last
+  // kernel, the scatter, to the next direction) takes Y, Q (from the direction to the
+  // update) takes XN.  With rows of 8 the two directions take the second halves of X
+  // and Y, which hold rows of EIGP.
+  const size_t half = (size_t)h->hp.vp_ptr.back() * W;
+  const bool wide = W == EIGP;
+  double *const R = ws.X, *const Z = ws.Y, *const Q = ws.XN;
+  double *P0 = wide ? h->mem.alloc<double>(tot) : ws.X + half,
+         *P1 = wide ? h->mem.alloc<double>(tot) : ws.Y + half;
+  double *const own[2] = {wide ? P0 : nullptr, wide ? P1 : nullptr};  // (P0 and P1 swap roles)
   double *part = h->mem.alloc<double>((size_t)2 * nblk * W), *part_rr = part + (size_t)nblk * W;
   double *sc = h->mem.alloc<double>((size_t)5 * nrec);  // alpha or beta, sums; rz, f2, rr
   int *si = h->mem.alloc<int>((size_t)3 * nrec + 1);
   auto release = [&]() {
     for (const void *b : {(const void *)rb.brow, (const void *)rb.bseg, (const void *)rb.sblk,
-                          (const void *)Z, (const void *)P0, (const void *)P1, (const void *)Q,
-                          (const void *)part, (const void *)sc, (const void *)si})
+                          (const void *)own[0], (const void *)own[1], (const void *)part,
+                          (const void *)sc, (const void *)si})
       if (b) h->mem.free_one(const_cast<void *>(b));
   };
-  if (!ok || !Z || !P0 || !P1 || !Q || !part || !sc || !si) {
+  if (!ok || !P0 || !P1 || !part || !sc || !si) {
     release();
     h->err = "device allocation failed (several-column CG)";
     return AMSP_ERR_OOM;
   }
-  double *const R = ws.X;  // the residual is the preconditioner's input
   double *const coef = sc, *const sums = sc + nrec;
   const RowCgState cg{sc + 2 * nrec, sc + 3 * nrec, sc + 4 * nrec, si, si + nrec, si + 2 * nrec,
                       si + 3 * nrec, hist, hist_cap};
