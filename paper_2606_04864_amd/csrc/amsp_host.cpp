@@ -1321,11 +1321,8 @@ extern "C" amsp_status amsp_setup(const amsp_csr *A, const int32_t *partition, i
     delete h;
     return (amsp_status)s;
   }
-  // the local apply keeps a region's vector and envelope segment starts in
-  // LDS (160 KB per workgroup, less the kernel's 512 B of static LDS)
-  if ((o.precision == AMSP_FP64 ? local_apply_lds_bytes(h->hp.max_npad)
-                                 : local_apply_stream_lds_bytes(h->hp.max_npad)) >
-      160 * 1024 - 512) {
+  // the local apply keeps a region's vector in LDS
+  if (h->hp.max_npad > (o.precision == AMSP_FP64 ? LOCAL_MAX_NPAD_FP64 : LOCAL_MAX_NPAD_MIXED)) {
     g_setup_error = "largest region (" + std::to_string(h->hp.max_npad) +
                     " padded rows) exceeds the local apply's LDS capacity";
     delete h;

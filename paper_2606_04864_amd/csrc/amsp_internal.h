@@ -123,9 +123,13 @@ void launch_tiles_to_f32(hipStream_t s, const double *src, float *dst, size_t co
 template <typename T>
 void launch_env_from_tiles(hipStream_t s, const Plan &p, int ntilerows, const double *tiles,
                            T *erow, T *ecol);
-// LDS that the FP64 form's local apply is allowed for regions of up to
-// max_npad padded rows (larger regions are refused).
-size_t local_apply_lds_bytes(int max_npad);
+// Largest region (padded rows) of the local apply in the FP64 form and in the mixed
+// ones; larger ones are refused at setup.  The mixed line is what the stream kernel's
+// LDS holds.  The FP64 line is from a kernel that kept the segment starts beside the
+// vector (the present one would hold 14016 rows); it stays, so that what is refused does
+// not change.  k_apply.hip checks both lines against its kernels.
+constexpr size_t LDS_BYTES = 160 * 1024;  // of a workgroup
+constexpr int LOCAL_MAX_NPAD_FP64 = 10112, LOCAL_MAX_NPAD_MIXED = 17280;
 // Per-sweep streams of an f32 factor: for every region, its 64-row blocks in
 // sweep order (forward: ascending, envelope row form; backward: descending,
 // column form), each block's envelope segments zero-padded to a multiple of
@@ -134,7 +138,6 @@ size_t local_apply_lds_bytes(int max_npad);
 constexpr int STREAM_TAIL = 4 * WG;
 void launch_stream_from_tiles(hipStream_t s, const Plan &p, int ntilerows, const double *tiles,
                               float *fst, float *bst);
-size_t local_apply_stream_lds_bytes(int max_npad);
 // Coarse restriction c = R0 r: c_i = Phi_i^T r_i for every region (TB basis
 // type; the copy made by launch_basis_to_natural).
 template <typename TB>

@@ -362,9 +362,20 @@ __device__ __forceinline__ void local_sweep(int nt, const int *__restrict__ ptr,
   __syncthreads();  // v complete
 }
 
-size_t local_apply_lds_bytes(int max_npad) {
-  return (size_t)(max_npad + TS) * sizeof(double) + 2 * (size_t)(max_npad + 1) * sizeof(int);
-}
+// k_local_apply's LDS: the staged entries, a diagonal tile and scratch (one block, so
+// that reads a little past Ev stay inside it), the region's coarse values, and the
+// vector with TS zeros behind it (dynamic).
+template <int EVU, typename T>
+struct LocalLds {
+  T Ev[EVU * WG], Dt[DE], tmp[TS];
+};
+constexpr size_t TQ_BYTES = 16 * sizeof(double);
+static_assert(MAXNEV <= 16, "coarse values of one region");
+constexpr size_t local_vector_bytes(int npad, size_t size) { return (size_t)(npad + TS) * size; }
+static_assert(local_vector_bytes(LOCAL_MAX_NPAD_FP64, 8) + sizeof(LocalLds<16, double>) + TQ_BYTES <=
+                  LDS_BYTES, "largest region, FP64 form");
+static_assert(local_vector_bytes(LOCAL_MAX_NPAD_MIXED, 4) + sizeof(LocalLds<16, float>) + TQ_BYTES <=
+                  LDS_BYTES, "largest region, mixed forms up to 640 regions");
 
 // Fused additive-Schwarz local kernel (the FP64 form's, and the mixed forms' with
 // up to 640 regions) for one region per workgroup: gather r on the region,
@@ -379,12 +390,9 @@ k_local_apply(Plan p, const double *__restrict__ r, const T *__restrict__ diag,
               const int *__restrict__ done) {
   if (done && *done) return;
   extern __shared__ __align__(16) char smem_raw[];
-  __shared__ double tq_s[16];  // the region's coarse values
+  __shared__ double tq_s[TQ_BYTES / sizeof(double)];  // the region's coarse values
   constexpr bool STREAM = sizeof(T) == 4;
-  // one block, so that reads a little past Ev stay inside it
-  __shared__ __align__(16) struct {
-    T Ev[EVU * WG], Dt[DE], tmp[TS];
-  } sh;
+  __shared__ __align__(16) LocalLds<EVU, T> sh;
   T *const Ev = sh.Ev, *const Dt = sh.Dt, *const tmp = sh.tmp;
   const int i = blockIdx.x;
   const int r0 = p.sd_ptr[i], ni = p.sd_ptr[i + 1] - r0;
@@ -449,16 +457,15 @@ constexpr int RSZ = RU * UE;
 static_assert(NS >= 3, "a diagonal tile may start three units before the batch it ends in");
 }  // namespace stream
 
-// The region's coarse values (MAXNEV doubles, padded to 16 so that what
-// follows stays 16-byte aligned) head the stream kernel's LDS.
-constexpr size_t TQ_BYTES = 16 * sizeof(double);
-static_assert(MAXNEV <= 16, "coarse values of one region");
-
-size_t local_apply_stream_lds_bytes(int max_npad) {
-  // coarse values + v (npad) + tmp (64) + ring + one form's segment starts (npad + 1)
+// LDS: the region's coarse values (MAXNEV doubles, padded to 16 so that what
+// follows stays 16-byte aligned), v (npad), tmp (64), the ring and one form's
+// segment starts (npad + 1).
+constexpr size_t local_apply_stream_lds_bytes(int max_npad) {
   return TQ_BYTES + (size_t)(max_npad + TS + stream::RSZ) * sizeof(float) +
          (size_t)(max_npad + 1) * sizeof(int);
 }
+static_assert(local_apply_stream_lds_bytes(LOCAL_MAX_NPAD_MIXED) <= LDS_BYTES,
+              "largest region, mixed forms");
 
 // One sweep.  FWD: blocks I = 0 .. nt-1, row form, y_I = inv(L_II)(b_I - env);
 // otherwise blocks nt-1 .. 0, column form, x_I = inv(L_II)^T (y_I - env).
@@ -697,7 +704,7 @@ static void local_apply_launch(hipStream_t s, const Plan &p, int max_npad, const
                                const T *diag, const T *frow, const T *fcol, const TB *phi,
                                const double *t, const double *tpart, int T0, double *xloc,
                                const int *done, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  const size_t sm = (size_t)(max_npad + TS) * sizeof(T);
+  const size_t sm = local_vector_bytes(max_npad, sizeof(T));
   allow_lds(k_local_apply<EVU, T, TB>, sm);
   if (ev_start || ev_stop)  // events bound to this dispatch: exact kernel duration
     hipExtLaunchKernelGGL((k_local_apply<EVU, T, TB>), dim3(p.N), dim3(WG), sm, s, ev_start,
