@@ -1411,13 +1411,13 @@ static amsp_status apply_one(amsp_handle *h, const double *r, double *z, int par
       launch_local_apply(h->stream, p, h->hp.max_npad, r, h->dg64, h->erow64, h->ecol64,
                          (const double *)h->phi_nat, t, tpart, h->T0, h->xloc, done, e0, e1);
     else if (!bf)
-      launch_local_apply_stream<float>(h->stream, p, h->hp.max_npad, r, h->fst32, h->bst32,
-                                       (const float *)h->phi_nat, t, tpart, h->T0, h->xloc, done,
-                                       e0, e1);
+      launch_local_apply_mixed<float>(h->stream, p, h->hp.max_npad, r, h->fst32, h->bst32,
+                                      (const float *)h->phi_nat, t, tpart, h->T0, h->xloc, done,
+                                      e0, e1);
     else
-      launch_local_apply_stream<__hip_bfloat16>(h->stream, p, h->hp.max_npad, r, h->fst32,
-                                                h->bst32, (const __hip_bfloat16 *)h->phi_nat, t,
-                                                tpart, h->T0, h->xloc, done, e0, e1);
+      launch_local_apply_mixed<__hip_bfloat16>(h->stream, p, h->hp.max_npad, r, h->fst32,
+                                               h->bst32, (const __hip_bfloat16 *)h->phi_nat, t,
+                                               tpart, h->T0, h->xloc, done, e0, e1);
     tpair_done(h, 1, tk);
   }
   tk = tstart(h, 3);

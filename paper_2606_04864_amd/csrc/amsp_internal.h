@@ -34,7 +34,7 @@ struct Plan {
   int env_mean;             // envelope entries per 64-row block, on average
   const int *sfb, *sbb;     // [sum nt_i] start of each 64-row block in its region's forward
   const long long *sfr;     //   / backward stream; [N+1] region starts of the forward
-  const long long *sbr;     //   / backward streams (see launch_local_apply_stream)
+  const long long *sbr;     //   / backward streams (see launch_local_apply_mixed)
   const int *loc_rowptr;    // [sum n_i + 1] local CSR of A_i (rows in local order)
   const int *loc_col;       //   local column index
   const int *loc_src;       //   index of the value in the global CSR
@@ -143,13 +143,13 @@ void launch_stream_from_tiles(hipStream_t s, const Plan &p, int ntilerows, const
 template <typename TB>
 void launch_restrict(hipStream_t s, const Plan &p, const double *r, const TB *phi, double *cvec,
                      const int *done);
-// The mixed forms' local apply on the streams (the operation of
-// launch_local_apply, which it calls for few regions).
+// The mixed forms' local apply on the float32 factor's streams (the operation of
+// launch_local_apply, whose kernel it takes for up to 640 regions).
 template <typename TB>
-void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                               const float *fst, const float *bst, const TB *phi, const double *t,
-                               const double *tpart, int T0, double *xloc, const int *done,
-                               hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+void launch_local_apply_mixed(hipStream_t s, const Plan &p, int max_npad, const double *r,
+                              const float *fst, const float *bst, const TB *phi, const double *t,
+                              const double *tpart, int T0, double *xloc, const int *done,
+                              hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // Local apply: gather r, envelope forward/backward solve, store into xloc;
 // with the coarse solution t (else nullptr) the prolongation Phi_i t_i is
 // added to each region's output (phi: the copy made by

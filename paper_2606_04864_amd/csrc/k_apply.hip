@@ -217,7 +217,7 @@ __device__ __forceinline__ void coarse_partial_finish(const Plan &p, int i, doub
 // Measured (blocks of 64 rows, float64, whole kernel): 64 regions of 21 blocks
 // 97 -> 54 us; 1024 regions 222 -> 165 us (0.93 GB, 5.6 TB/s: what a copy
 // reaches); 1331 regions of 12 blocks in three dimensions 231 us.  The float32 factor's
-// figures stand at launch_local_apply_stream.
+// figures stand at launch_local_apply_mixed.
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 // The float64 factor is read as an envelope form (block starts in ptr) and packed
@@ -734,10 +734,10 @@ template void launch_local_apply<double, double>(hipStream_t, const Plan &, int,
                                                  hipEvent_t);
 
 template <typename TB>
-void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const double *r,
-                               const float *fst, const float *bst, const TB *phi, const double *t,
-                               const double *tpart, int T0, double *xloc, const int *done,
-                               hipEvent_t ev_start, hipEvent_t ev_stop) {
+void launch_local_apply_mixed(hipStream_t s, const Plan &p, int max_npad, const double *r,
+                              const float *fst, const float *bst, const TB *phi, const double *t,
+                              const double *tpart, int T0, double *xloc, const int *done,
+                              hipEvent_t ev_start, hipEvent_t ev_stop) {
   // With few regions a region's chain of blocks is what counts, and the FP64
   // form's sweep has the shorter one; with many the stream's fuller loads are.
   // PCG in float32, stream kernel / sweep: 64 regions 3.47 / 2.98 ms, 256 3.77 /
@@ -757,15 +757,15 @@ void launch_local_apply_stream(hipStream_t s, const Plan &p, int max_npad, const
     hipLaunchKernelGGL((k_local_apply_stream<TB>), dim3(p.N), dim3(WG), sm, s, p, r, fst, bst, phi,
                        t, tpart, T0, xloc, done);
 }
-template void launch_local_apply_stream<float>(hipStream_t, const Plan &, int, const double *,
-                                               const float *, const float *, const float *,
-                                               const double *, const double *, int, double *,
-                                               const int *, hipEvent_t, hipEvent_t);
-template void launch_local_apply_stream<__hip_bfloat16>(hipStream_t, const Plan &, int,
-                                                        const double *, const float *,
-                                                        const float *, const __hip_bfloat16 *,
-                                                        const double *, const double *, int,
-                                                        double *, const int *, hipEvent_t,
-                                                        hipEvent_t);
+template void launch_local_apply_mixed<float>(hipStream_t, const Plan &, int, const double *,
+                                              const float *, const float *, const float *,
+                                              const double *, const double *, int, double *,
+                                              const int *, hipEvent_t, hipEvent_t);
+template void launch_local_apply_mixed<__hip_bfloat16>(hipStream_t, const Plan &, int,
+                                                       const double *, const float *,
+                                                       const float *, const __hip_bfloat16 *,
+                                                       const double *, const double *, int,
+                                                       double *, const int *, hipEvent_t,
+                                                       hipEvent_t);
 
 }  // namespace amsp

@@ -23,8 +23,6 @@
 
 namespace amsp {
 
-int row_width(int nr);  // k_multi.hip
-
 template <typename F>
 static void with_width(int nr, F &&f) {
   if (row_width(nr) == 8)

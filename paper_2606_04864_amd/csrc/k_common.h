@@ -127,15 +127,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Broadcast lane `src` (a compile-time constant in the callers' unrolled
-// loops) of a double to the whole wavefront.
-__device__ __forceinline__ double readlane_d(double v, int src) {
-  const long long bits = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)bits, src);
-  const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), src);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // 1/sqrt(d) for d > 0 to double precision: hardware estimate y (24 bits or
 // more) refined by one third-order step, y (1 + e/2 + 3e^2/8) with e = 1 - d y^2.
 __device__ __forceinline__ double rsqrt_d(double d) {
@@ -226,8 +217,13 @@ __device__ __forceinline__ float quad_sum(float v) {
 // 8.2 us, 230 cycles a pivot; 23.3 with all 64 columns in one wavefront's
 // registers and the inverse solved row by row behind it.  (Multipliers as
 // wave-uniform lane reads: 10.5.)
-// A non-positive or non-finite pivot sets *fail and is replaced by 1 so that
-// the result stays finite.  Needs blockDim.x == 256.
+// Accuracy (condition numbers of general tiles; against 80-bit arithmetic): the
+// errors of L, of inv(L) and of a solve and |L L^T - A| are those of the elimination
+// column by column up to condition 1e6 and at most twice them at 2e9; |L inv(L) - I|,
+// 1e-15 there, grows with the 16-row blocks' condition (3e-15 at 3e6, 5e-14 at 2e9).
+// Tiles of Darcy matrices, also at a contrast of 1e6: 4e-16, as before.
+// A non-positive or non-finite pivot sets *fail; L and inv(L) then mean nothing (each
+// caller's setup ends with an error).  Needs blockDim.x == 256.
 
 // c += X Y^T or X Y of 16x16 blocks in LDS (row stride LD), one wavefront;
 // element r of c is row lane / 16 + 4r, column lane % 16.
