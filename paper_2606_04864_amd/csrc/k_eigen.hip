@@ -592,11 +592,12 @@ k_env_solve_block(Plan p, const T *__restrict__ diag, const T *__restrict__ erow
 // Entries staged per thread: the regions of a plane grid have some 300
 // envelope entries per block (four per thread cover 1024); where blocks
 // average more than 700, as in three dimensions, sixteen.  Blocks in flight:
-// two for a float64 factor (64 regions of 21 blocks: 91 us with one, 87-96
-// with two; 256: 141 / 105; 1024: 335 / 315), one for a float32 factor, whose
-// third and fourth workgroup per unit are worth more (256: 105 / 98; 1024:
-// 220 / 250), and where the staged entries already fill the registers (512
-// regions of 16 blocks in three dimensions: 155 / 170).
+// two for a float64 factor (64 regions of 21 blocks: 79 us with one, 75 with two;
+// 256: 90 / 84; 1024: 310 / 296), one for a float32 factor, whose third and fourth
+// workgroup per unit are worth more where there are regions for them (1024: 215 / 235;
+// 256: 83 / 80, 64: 78 / 76), and where the staged entries already fill the registers
+// (regions of 16 blocks in three dimensions, 512 with a float64 factor: 165 / 169, 1728
+// with a float32 one: 396 / 456).
 template <typename T>
 void launch_env_solve_block(hipStream_t s, const Plan &p, const T *diag, const T *erow,
                             const T *ecol, const double *X, double *Y, const int *skip) {

@@ -377,8 +377,9 @@ void launch_restrict_rows(hipStream_t s, const Plan &p, int nr, const TB *phi, c
 // Staged entries and blocks in flight as for launch_env_solve_block; KS: the
 // matrix-core steps of four coefficients that hold nev.  Workgroups per unit
 // with a float32 factor: four (128 registers, some spilled) where there are
-// regions for more than two (1024 regions, W = 8: 226 -> 199 us; the 2133
-// regions of 32 problems 446 -> 397), three otherwise (64 regions: 85 / 94).
+// regions for more than two (1024 regions, three / four: W = 8 229 / 196 us, W = 16
+// 258 / 235; the 2133 regions of 32 problems 446 / 397), three otherwise (64 regions:
+// 86 / 95, 256: 94 / 101).
 template <typename T, typename TB>
 void launch_solve_rows(hipStream_t s, const Plan &p, int nr, const T *diag, const T *erow,
                        const T *ecol, const double *R, const TB *phi, const double *t, double *Y,

@@ -45,11 +45,11 @@ namespace amsp {
 // With several workgroups per unit the instructions between the products count
 // (320 vector instructions a block): addresses are one base and constants,
 // masks are taken where a step needs one.
-// Measured in the eigensolver's sweeps (21 blocks of 64 rows per region, float64
-// / float32 factor): 64 regions 200 -> 75 / 67 us, 1024 regions 430 -> 305 /
-// 357 -> 204 us (5 TB/s of factor and rows); in three dimensions (1728 regions
-// of 16 blocks) 1320 -> 320 us with a float32 factor, whose segments of ~100
-// entries were a serial loop before.
+// Measured in the eigensolver's sweeps (21 blocks of 64 rows per region, all of them
+// at work, float64 / float32 factor): 64 regions 200 -> 75 / 202 -> 78 us, 1024 regions
+// 426 -> 297 / 352 -> 213 us (5.2 TB/s of factor and rows); in three dimensions (1728
+// regions of 16 blocks) 1442 -> 564 / 1396 -> 391 us, segments of ~100 entries having
+// been a serial loop before.
 constexpr int SOLVE_RING = 2 * TS;  // finished rows kept in LDS
 
 template <int EVU, int PF, typename T, typename IO>
