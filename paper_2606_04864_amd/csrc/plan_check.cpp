@@ -169,7 +169,7 @@ void sweep_case(const Grid &g, int overlap, int order, int dense, const char *na
       for (int fwd = 0; fwd < 2; ++fwd) {
         const int *ptr = (fwd ? P.eptr : P.uptr).data() + P.vp_ptr[i] + i;
         for (int r0 = 0; r0 < npad; r0 += TS) {
-          if (ptr[r0 + TS] - ptr[r0] > evc) continue;  // read from memory, exactly
+          if (ptr[r0 + TS] - ptr[r0] > evc) continue;  // read from memory, one past a segment
           ++staged;
           for (int w = 0; w < 4; ++w) {
             auto len = [&](int r) { return ptr[r + 1] - ptr[r]; };
