@@ -222,7 +222,11 @@ __global__ void k_x_to_f32(const double *__restrict__ src, float *__restrict__ d
 // Measured (three-dimensional tree of 13824 coarse dofs in 8 levels, float32,
 // both directions): 255 us with each lane walking 64-byte pieces of one tile
 // after the other, 151 us so.
-constexpr int TREE_B = 4;  // tiles per batch
+// A level whose fronts sum up to four tiles (SMALL) is latency alone: it loads just
+// those tiles, ahead of the gather, gathers a row per thread, and adds shares in LDS
+// without lane exchanges.  1024 coarse dofs of 256 regions (fronts of one to four
+// tiles, float32): the coarse part of an application takes 50.4 us, 54.5 without (four
+// tiles loaded behind the gather whatever their number).
 
 // v[k][e] = entry (16 b + 4k + (l >> 4), 4 (l & 15) + e) of a tile, lane l
 template <typename TX>
@@ -235,10 +239,11 @@ __device__ __forceinline__ void quarter_load(TX (&v)[4][4], const TX *__restrict
 }
 
 // cs[r] = c + the children's contributions to front row r (in order), r < rows
+// (U rows per thread with their loads together)
+template <int U>
 __device__ __forceinline__ void tree_gather(const TreeDev &t, int rb, int rows, int nthreads,
                                             const double *__restrict__ c,
                                             const double *v, double *cs) {
-  constexpr int U = 4;
   for (int r0 = threadIdx.x; r0 < rows; r0 += U * nthreads) {
     int rc[U], g0[U], g1[U];
     double s[U];
@@ -273,10 +278,10 @@ __device__ __forceinline__ void tree_gather(const TreeDev &t, int rb, int rows, 
 }
 
 // z[r] = y (own rows, r < own) or x (update rows) of front row r, a <= r < rows
+template <int U>
 __device__ __forceinline__ void tree_rows(const TreeDev &t, int rb, int a, int own, int rows,
                                           int nthreads, const double *y, const double *x,
                                           double *z) {
-  constexpr int U = 4;
   for (int r0 = a + threadIdx.x; r0 < rows; r0 += U * nthreads) {
     int rc[U];
     double s[U];
@@ -294,14 +299,13 @@ __device__ __forceinline__ void tree_rows(const TreeDev &t, int rb, int a, int o
 // input cs = c + the children's contributions, then rows 64I.. of X cs:
 // own rows give y (by coarse index), update rows give the front's update
 // vector v_f = (X cs) + the children's contributions to those rows.
-template <typename TX, int NJ, int NB>
+template <typename TX, int NJ, int NB, int B, bool SMALL>
 __global__ void __launch_bounds__(64 * NB * NJ) k_tree_fwd(TreeDev t, int f0, const TX *__restrict__ X,
                                                        const double *__restrict__ c,
                                                        double *__restrict__ y, double *v,
                                                        const int *__restrict__ done) {
   if (done && *done) return;
   extern __shared__ double cs[];  // 64 K
-  __shared__ double red[NJ][16 * NB];
   constexpr int NQ = 4 / NB;  // workgroups per row tile
   const int f = f0 + blockIdx.y, I = blockIdx.x / NQ;
   const int K = t.K[f];
@@ -309,16 +313,20 @@ __global__ void __launch_bounds__(64 * NB * NJ) k_tree_fwd(TreeDev t, int f0, co
   const int rb = t.rbase[f], jn = I < K ? I + 1 : K;  // inv(L11) is lower triangular
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, j = w / NB;
   const int b0 = NB * (blockIdx.x % NQ), b = b0 + w % NB;
-  tree_gather(t, rb, jn * TS, 64 * NB * NJ, c, v, cs);
+  TX x[B][4][4];
+  auto load = [&](int J0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < B; ++u)  // (past the last tile: the last one again, unused)
+      quarter_load(x[u], xtile(X, t, f, I, min(J0 + u * NJ, jn - 1)), b);
+  };
+  if (SMALL) load(j);
+  tree_gather<SMALL ? 1 : 4>(t, rb, jn * TS, 64 * NB * NJ, c, v, cs);
   __syncthreads();
   double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int J0 = j; J0 < jn; J0 += TREE_B * NJ) {
-    TX x[TREE_B][4][4];
+  for (int J0 = j; J0 < jn; J0 += B * NJ) {
+    if (!SMALL) load(J0);
 #pragma unroll
-    for (int u = 0; u < TREE_B; ++u)  // (past the last tile: the last one again, unused)
-      quarter_load(x[u], xtile(X, t, f, I, min(J0 + u * NJ, jn - 1)), b);
-#pragma unroll
-    for (int u = 0; u < TREE_B; ++u)
+    for (int u = 0; u < B; ++u)
       if (J0 + u * NJ < jn) {
         double cc[4];
 #pragma unroll
@@ -342,50 +350,64 @@ __global__ void __launch_bounds__(64 * NB * NJ) k_tree_fwd(TreeDev t, int f0, co
         a[k] = mine + __shfl_xor(other, 4 * o, 64);
       }
   const double sum = quad_sum(a[0]);
-  if ((l & 3) == 0) red[j][16 * (b - b0) + 4 * ((l >> 2) & 3) + (l >> 4)] = sum;
-  __syncthreads();
-  if (w != 0 || l >= 16 * NB) return;
-  double s = 0.0;
-#pragma unroll
-  for (int u = 0; u < NJ; ++u) s += red[u][l];
-  const int R = I * TS + 16 * b0 + l;
-  if (I < K) {
-    const int rc = t.row_coarse[rb + R];
-    if (rc >= 0) y[rc] = s;
-  } else {
-    const int u = R - K * TS;
-    if (u < t.udof[f]) {
-      for (int g = t.gptr[rb + R]; g < t.gptr[rb + R + 1]; ++g) s += v[t.gsrc[g]];
-      v[t.vbase[f] + u] = s;
+  const int rq = 4 * ((l >> 2) & 3) + (l >> 4);  // the lane's row of the quarter
+  auto out = [&](int R, double s) {
+    if (I < K) {
+      const int rc = t.row_coarse[rb + R];
+      if (rc >= 0) y[rc] = s;
+    } else {
+      const int u = R - K * TS;
+      if (u < t.udof[f]) {
+        for (int g = t.gptr[rb + R]; g < t.gptr[rb + R + 1]; ++g) s += v[t.gsrc[g]];
+        v[t.vbase[f] + u] = s;
+      }
     }
+  };
+  if constexpr (NJ == 1) {
+    if ((l & 3) == 0) out(I * TS + 16 * b + rq, sum);
+  } else {
+    __shared__ double red[NJ][16 * NB];
+    if ((l & 3) == 0) red[j][16 * (b - b0) + rq] = sum;
+    __syncthreads();
+    if (w != 0 || l >= 16 * NB) return;
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) s += red[u][l];
+    out(I * TS + 16 * b0 + l, s);
   }
 }
 
 // Backward, one level: workgroup (front f, column tile J) forms
 // z = [y on the own rows; x on the update rows (ancestors, solved)] and
 // x[own rows 64J..] = (X^T z) restricted to those columns.
-template <typename TX, int NJ>
+template <typename TX, int NJ, int B, bool SMALL>
 __global__ void __launch_bounds__(256 * NJ) k_tree_bwd(TreeDev t, int f0, const TX *__restrict__ X,
                                                        const double *__restrict__ y, double *x,
                                                        const int *__restrict__ done) {
   if (done && *done) return;
   extern __shared__ double z[];  // 64 T
-  __shared__ double red[4 * NJ][TS];
+  // the shares of the wavefronts, or of their four row groups
+  constexpr int NR = SMALL ? 16 * NJ : 4 * NJ;
+  __shared__ __align__(16) double red[NR][TS];
   const int f = f0 + blockIdx.y, J = blockIdx.x;
   const int K = t.K[f], T = t.T[f];
   if (J >= K) return;
   const int rb = t.rbase[f];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, b = w & 3, j = w >> 2;
-  tree_rows(t, rb, J * TS, K * TS, T * TS, 256 * NJ, y, x, z);
+  TX xt[B][4][4];
+  auto load = [&](int I0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      quarter_load(xt[u], xtile(X, t, f, min(I0 + u * NJ, T - 1), J), b);
+  };
+  if (SMALL) load(J + j);
+  tree_rows<SMALL ? 1 : 4>(t, rb, J * TS, K * TS, T * TS, 256 * NJ, y, x, z);
   __syncthreads();
   double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int I0 = J + j; I0 < T; I0 += TREE_B * NJ) {
-    TX xt[TREE_B][4][4];
+  for (int I0 = J + j; I0 < T; I0 += B * NJ) {
+    if (!SMALL) load(I0);
 #pragma unroll
-    for (int u = 0; u < TREE_B; ++u)
-      quarter_load(xt[u], xtile(X, t, f, min(I0 + u * NJ, T - 1), J), b);
-#pragma unroll
-    for (int u = 0; u < TREE_B; ++u)
+    for (int u = 0; u < B; ++u)
       if (I0 + u * NJ < T) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -395,17 +417,22 @@ __global__ void __launch_bounds__(256 * NJ) k_tree_bwd(TreeDev t, int f0, const 
         }
       }
   }
+  if (SMALL) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    a[e] += __shfl_xor(a[e], 16, 64);
-    a[e] += __shfl_xor(a[e], 32, 64);
-    if (l < 16) red[w][4 * l + e] = a[e];
+    for (int e = 0; e < 4; ++e) red[4 * w + (l >> 4)][4 * (l & 15) + e] = a[e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      a[e] += __shfl_xor(a[e], 16, 64);
+      a[e] += __shfl_xor(a[e], 32, 64);
+      if (l < 16) red[w][4 * l + e] = a[e];
+    }
   }
   __syncthreads();
   if (w != 0) return;
   double s = 0.0;
 #pragma unroll
-  for (int u = 0; u < 4 * NJ; ++u) s += red[u][l];
+  for (int u = 0; u < NR; ++u) s += red[u][l];
   const int rc = t.row_coarse[rb + J * TS + l];
   if (rc >= 0) x[rc] = s;
 }
@@ -426,7 +453,7 @@ __global__ void __launch_bounds__(1024) k_tree_bwd_quarter(TreeDev t, int f0,
   if (J >= K) return;
   const int rb = t.rbase[f];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  tree_rows(t, rb, J * TS, K * TS, T * TS, 1024, y, x, z);
+  tree_rows<4>(t, rb, J * TS, K * TS, T * TS, 1024, y, x, z);
   __syncthreads();
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   for (int I0 = J + w; I0 < T; I0 += 16 * 2) {
@@ -666,24 +693,38 @@ void launch_tree_solve(hipStream_t s, const TreeDev &t, const std::vector<int> &
                        double *x, const int *done) {
   const int nl = (int)lvl_ptr.size() - 1;
   const size_t smk = (size_t)maxK * TS * sizeof(double), smt = (size_t)maxT * TS * sizeof(double);
-  allow_lds(k_tree_fwd<TX, 1, 4>, smk);
-  allow_lds(k_tree_fwd<TX, 4, 4>, smk);
-  allow_lds(k_tree_fwd<TX, 16, 1>, smk);
-  allow_lds(k_tree_bwd<TX, 1>, smt);
-  allow_lds(k_tree_bwd<TX, 4>, smt);
+  allow_lds(k_tree_fwd<TX, 1, 4, 4, false>, smk);
+  allow_lds(k_tree_fwd<TX, 4, 4, 4, false>, smk);
+  allow_lds(k_tree_fwd<TX, 16, 1, 4, false>, smk);
+  allow_lds(k_tree_bwd<TX, 1, 4, false>, smt);
+  allow_lds(k_tree_bwd<TX, 4, 4, false>, smt);
   allow_lds(k_tree_bwd_quarter<TX>, smt);
+  // tiles per batch of the four-wavefront form, and whether one holds all
+  auto batch = [](int sum_tiles, auto &&go) {
+    constexpr std::true_type small{};
+    if (sum_tiles <= 1)
+      go(std::integral_constant<int, 1>{}, small);
+    else if (sum_tiles <= 2)
+      go(std::integral_constant<int, 2>{}, small);
+    else if (sum_tiles <= 4)
+      go(std::integral_constant<int, 4>{}, small);
+    else
+      go(std::integral_constant<int, 4>{}, std::false_type{});
+  };
   for (int h = 0; h < nl; ++h) {
     const int f0 = lvl_ptr[h], nf = lvl_ptr[h + 1] - f0, nt = lvl_maxT[h], nk = lvl_maxK[h];
     const size_t sm = (size_t)nk * TS * sizeof(double);
     if (tree_quarter(nt, nf, nk, 16))
-      hipLaunchKernelGGL((k_tree_fwd<TX, 16, 1>), dim3(4 * nt, nf), dim3(1024), sm, s, t, f0, X, c,
-                         y, v, done);
+      hipLaunchKernelGGL((k_tree_fwd<TX, 16, 1, 4, false>), dim3(4 * nt, nf), dim3(1024), sm, s, t, f0, X,
+                         c, y, v, done);
     else if (tree_wide(nk))
-      hipLaunchKernelGGL((k_tree_fwd<TX, 4, 4>), dim3(nt, nf), dim3(1024), sm, s, t, f0, X, c, y,
+      hipLaunchKernelGGL((k_tree_fwd<TX, 4, 4, 4, false>), dim3(nt, nf), dim3(1024), sm, s, t, f0, X, c, y,
                          v, done);
     else
-      hipLaunchKernelGGL((k_tree_fwd<TX, 1, 4>), dim3(nt, nf), dim3(256), sm, s, t, f0, X, c, y, v,
-                         done);
+      batch(nk, [&](auto b, auto small) {
+        hipLaunchKernelGGL((k_tree_fwd<TX, 1, 4, decltype(b)::value, decltype(small)::value>),
+                           dim3(nt, nf), dim3(256), sm, s, t, f0, X, c, y, v, done);
+      });
   }
   for (int h = nl - 1; h >= 0; --h) {
     const int f0 = lvl_ptr[h], nf = lvl_ptr[h + 1] - f0, nt = lvl_maxT[h], nk = lvl_maxK[h];
@@ -692,9 +733,13 @@ void launch_tree_solve(hipStream_t s, const TreeDev &t, const std::vector<int> &
       hipLaunchKernelGGL((k_tree_bwd_quarter<TX>), dim3(4 * nk, nf), dim3(1024), sm, s, t, f0, X, y,
                          x, done);
     else if (tree_wide(nt))
-      hipLaunchKernelGGL((k_tree_bwd<TX, 4>), dim3(nk, nf), dim3(1024), sm, s, t, f0, X, y, x, done);
+      hipLaunchKernelGGL((k_tree_bwd<TX, 4, 4, false>), dim3(nk, nf), dim3(1024), sm, s, t, f0, X, y, x,
+                         done);
     else
-      hipLaunchKernelGGL((k_tree_bwd<TX, 1>), dim3(nk, nf), dim3(256), sm, s, t, f0, X, y, x, done);
+      batch(nt, [&](auto b, auto small) {
+        hipLaunchKernelGGL((k_tree_bwd<TX, 1, decltype(b)::value, decltype(small)::value>),
+                           dim3(nk, nf), dim3(256), sm, s, t, f0, X, y, x, done);
+      });
   }
 }
 
